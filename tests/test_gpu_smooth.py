@@ -92,3 +92,19 @@ def test_resampling_matches_oracle(mode):
             e = rel_l2(g, ref)
             say(f"[resample sinc] dt {dt_in} -> {dt_out}: rel-L2 {e:.2e}")
             assert e <= 1e-6
+
+
+@pytest.mark.parametrize("nrec, nt_in, nt_out", [
+    (1, 1, 1), (1, 15, 64), (16, 16, 16), (17, 17, 65), (33, 31, 63), (70, 64, 129),
+    (129, 47, 300), (700, 33, 1100)])
+def test_sinc_resampling_tiles(nrec, nt_in, nt_out):
+    """Around the 16-sample and 16-trace tiles and every number of row tiles.
+    FP64 sums rounded once to FP32: at most 2^-24 of each value."""
+    torch = gpu_or_skip()
+    from oracle import resample as ors
+    from paper_2502_12350_amd import resample
+    d = np.random.default_rng(nrec).standard_normal((nrec, nt_in)).astype(np.float32)
+    for dt_out in (0.5e-3, 0.7e-3, 1.9e-3):   # on samples every second time, and never
+        ref = ors.resample(d, 1.0e-3, nt_out, dt_out, "sinc")
+        got = resample(torch.from_numpy(d).cuda(), 1.0e-3, nt_out, dt_out, "sinc")
+        assert rel_l2(got.cpu().numpy(), ref) <= 1e-7
