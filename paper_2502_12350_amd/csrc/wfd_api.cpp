@@ -2113,39 +2113,18 @@ wfd_status wfd_smooth(int32_t mode, const float *in, float *out, int32_t nx, int
   hipStream_t st = (hipStream_t)stream_;
   const int64_t n = (int64_t)nx * ny * nz;
   if (mode == WFD_SMOOTH_LAPLACE) {
-    if (out != in) HIP_TRY(hipMemcpyAsync(out, in, n * sizeof(float), hipMemcpyDeviceToDevice, st));
     const int len[3] = {nx, ny, nz};
     const int64_t lines[3] = {(int64_t)ny * nz, (int64_t)nx * nz, (int64_t)nx * ny};
-    double *dev = static_cast<double *>(work);
-    std::vector<double> host(2 * (size_t)(nx + ny + nz), 0.0);
-    size_t off = 0;
-    double a_of[3];
-    size_t off_of[3];
-    for (int d = 0; d < 3; ++d) {
-      const int m = len[d];
-      const double a = lengths[d] > 0.0 ? std::exp(-spacing[d] / lengths[d]) : 0.0;
-      a_of[d] = a;
-      off_of[d] = off;
-      double *cp = host.data() + off, *inv = host.data() + off + m;
-      for (int i = 0; i < m; ++i) {
-        double b = 1.0 + a * a;
-        if (m == 1) b = (1.0 - a) * (1.0 - a);
-        else if (i == 0 || i == m - 1) b = 1.0 + a * a - a;  // zero-flux ends
-        const double den = i == 0 ? b : b + a * cp[i - 1];
-        inv[i] = 1.0 / den;
-        cp[i] = -a / den;
-      }
-      off += 2 * (size_t)m;
-    }
-    HIP_TRY(hipMemcpyAsync(dev, host.data(), host.size() * sizeof(double), hipMemcpyHostToDevice,
-                           st));
+    const float *src = in;  // the first axis smoothed reads the input, the others out
     for (int d = 0; d < 3; ++d) {
       if (lengths[d] <= 0.0) continue;
-      const double a = a_of[d];
-      HIP_TRY(wfd::launch_tri_lines(out, d, len[d], lines[d], nx, ny, dev + off_of[d],
-                                    dev + off_of[d] + len[d], a, (1.0 - a) * (1.0 - a), st));
+      HIP_TRY(wfd::launch_tri_lines(src, out, d, len[d], lines[d], nx, ny,
+                                    spacing[d] / lengths[d], st));
+      src = out;
     }
-    HIP_TRY(hipStreamSynchronize(st));  // the host coefficients may go now
+    if (src != out)
+      HIP_TRY(hipMemcpyAsync(out, in, n * sizeof(float), hipMemcpyDeviceToDevice, st));
+    HIP_TRY(hipStreamSynchronize(st));
     if (iterations) *iterations = 0;
     return WFD_OK;
   }

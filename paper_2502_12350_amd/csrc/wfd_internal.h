@@ -242,9 +242,8 @@ hipError_t launch_pack_input(const float *grad, const float *illum, int64_t n, f
                              float *partial, int npart, uint16_t *out, hipStream_t stream);
 
 // ---- gradient smoothing kernels (wfd_smooth.hip) ----
-hipError_t launch_tri_lines(float *u, int axis, int n, int64_t nlines, int nx, int ny,
-                            const double *cp, const double *inv_den, double a, double scale,
-                            hipStream_t stream);
+hipError_t launch_tri_lines(const float *in, float *out, int axis, int n, int64_t nlines, int nx,
+                            int ny, double h_over_l, hipStream_t stream);
 hipError_t launch_bessel_apply(const float *x, float *y, int nx, int ny, int nz, float cx,
                                float cy, float cz, double *part, int npart, hipStream_t stream);
 hipError_t launch_cg_update(float *x, float *r, const float *p, const float *ap, int64_t n,

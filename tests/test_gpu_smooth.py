@@ -108,3 +108,23 @@ def test_sinc_resampling_tiles(nrec, nt_in, nt_out):
         ref = ors.resample(d, 1.0e-3, nt_out, dt_out, "sinc")
         got = resample(torch.from_numpy(d).cuda(), 1.0e-3, nt_out, dt_out, "sinc")
         assert rel_l2(got.cpu().numpy(), ref) <= 1e-7
+
+
+@pytest.mark.parametrize("shape", [
+    (1, 1, 1), (2, 3, 1), (5, 65, 64), (33, 130, 257), (3, 5, 1900), (2050, 3, 33), (2, 700, 40),
+    (1, 1, 4000), (1, 9000, 2)])
+def test_laplace_tiles(shape):
+    """Line tiles of every size, ragged ones, and lines too long for a tile.
+    Each axis rounds twice to FP32 (2^-24 relative to the line's largest
+    value), six roundings in all."""
+    torch = gpu_or_skip()
+    from paper_2502_12350_amd import smooth
+    g = np.random.default_rng(3).standard_normal(shape).astype(np.float32)
+    for lens in ((20.0, 30.0, 12.0), (500.0, 0.0, 1.0)):
+        ref = osm.laplace_filter(g, lens, H)
+        x = torch.from_numpy(g).cuda()
+        out, _ = smooth(x, "laplace", lens, H)
+        tol = 6 * 2.0 ** -24 * max(1.0, float(np.abs(g).max()))
+        assert float(np.abs(out.cpu().numpy() - ref).max()) <= tol
+        smooth(x, "laplace", lens, H, out=x)
+        assert torch.equal(x, out)
