@@ -43,32 +43,34 @@ __device__ __forceinline__ void line_of(int axis, int64_t L, int nx, int ny, int
 // The elimination's denominators and off-diagonals in closed form: with the
 // zero-flux ends the leading minors of (1 - a)^2 T are proportional to
 // 1 + a^(2i+1), so row i has den_i = (1 + a^(2i+3)) / (1 + a^(2i+1)), the last
-// row (1 - a)(1 - a^(2n)) / (1 + a^(2n-1)), and cp_i = -a / den_i.
+// row (1 - a)(1 - a^(2n)) / (1 + a^(2n-1)).  With s_i = (1 - a)^2 / den_i and
+// c_i = a / den_i the solution is one multiply-add per point each way:
+//   d_i = s_i g_i + c_i d_{i-1},   x_i = d_i + c_i x_{i+1}   (x_{n-1} = d_{n-1}).
 struct TriRow {
-  double inv_den, cp;
+  double s, c;
 };
 __device__ __forceinline__ TriRow tri_row(int i, int n, double log_a, double a) {
-  const double p = exp((2.0 * i + 1.0) * log_a);
+  const double p = exp((2.0 * i + 1.0) * log_a), q = expm1(log_a);
   const double inv = i + 1 < n ? (1.0 + p) / (1.0 + p * a * a)
-                               : (1.0 + p) / (expm1(log_a) * expm1(2.0 * n * log_a));
-  return TriRow{inv, -a * inv};
+                               : (1.0 + p) / (q * expm1(2.0 * n * log_a));
+  return TriRow{q * q * inv, a * inv};
 }
 
 // A block solves NL neighbouring lines: it loads them into LDS with every
-// thread, one thread per line runs the recursion there (FP64, d' kept in FP32),
+// thread, one thread per line runs the recursion there (FP64, d kept in FP32),
 // and every thread writes them back.  Each point moves once in and once out
 // (8 B) instead of twice each.  S1: the lines run along x and lie next to one
 // another; else their points i are `stride` apart and neighbouring lines are
-// neighbouring elements (y lines: within one plane).  200 x 200 x 160: the
-// three axes took 146, 106 and 69 us with a thread marching each line in memory.
+// neighbouring elements (y lines: within one plane).  200 x 200 x 160: 24, 31
+// and 24 us along x, y and z (load, march and store of a block follow one
+// another); 146, 106 and 69 us with a thread marching each line in memory.
 template <bool S1>
 __global__ void __launch_bounds__(256)
     k_tri_tile(const float *in, float *out, int n, int64_t nlines, int nx, int ny, int axis,
-               int nl, int pad, double log_a, double a, double scale) {
+               int nl, int pad, double log_a, double a) {
   extern __shared__ char smem[];
-  double *inv = reinterpret_cast<double *>(smem);
-  double *cp = inv + n;
-  float *u = reinterpret_cast<float *>(cp + n);
+  TriRow *row = reinterpret_cast<TriRow *>(smem);
+  float *u = reinterpret_cast<float *>(row + n);
   const int64_t l0 = (int64_t)blockIdx.x * nl;
   const int lines = (int)(nlines - l0 < nl ? nlines - l0 : nl);
   const int tid = threadIdx.x;
@@ -92,27 +94,21 @@ __global__ void __launch_bounds__(256)
 #pragma unroll 8
       for (int i = tid / nl; i < n; i += step) u[i * nl + l] = in[base + i * stride];
   }
-  for (int i = tid; i < n; i += 256) {
-    const TriRow t = tri_row(i, n, log_a, a);
-    inv[i] = t.inv_den;
-    cp[i] = t.cp;
-  }
+  for (int i = tid; i < n; i += 256) row[i] = tri_row(i, n, log_a, a);
   __syncthreads();
   if (tid < lines) {
     float *p = S1 ? u + tid * pad : u + tid;
     const int st = S1 ? 1 : nl;
     double d = 0.0;
-    // forward sweep: d'_i = (scale g_i + a d'_{i-1}) / den_i
 #pragma unroll 8
     for (int i = 0; i < n; ++i) {
-      d = (scale * (double)p[i * st] + a * d) * inv[i];
+      d = fma(row[i].c, d, row[i].s * (double)p[i * st]);
       p[i * st] = (float)d;
     }
-    // back substitution: x_i = d'_i - cp_i x_{i+1}
     double x = d;
 #pragma unroll 8
     for (int i = n - 2; i >= 0; --i) {
-      x = (double)p[i * st] - cp[i] * x;
+      x = fma(row[i].c, x, (double)p[i * st]);
       p[i * st] = (float)x;
     }
   }
@@ -140,7 +136,7 @@ __global__ void __launch_bounds__(256)
 // Lines too long for a tile (over kTileBytes even at 8 lines): one thread
 // marches each line in memory.
 __global__ void k_tri_lines(const float *in, float *out, int axis, int n, int64_t nlines, int nx,
-                            int ny, double log_a, double a, double scale) {
+                            int ny, double log_a, double a) {
   const int64_t L = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (L >= nlines) return;
   int64_t base, stride;
@@ -148,13 +144,14 @@ __global__ void k_tri_lines(const float *in, float *out, int axis, int n, int64_
   double d = 0.0;
   for (int i = 0; i < n; ++i) {
     const int64_t p = base + (int64_t)i * stride;
-    d = (scale * (double)in[p] + a * d) * tri_row(i, n, log_a, a).inv_den;
+    const TriRow t = tri_row(i, n, log_a, a);
+    d = fma(t.c, d, t.s * (double)in[p]);
     out[p] = (float)d;
   }
   double x = d;
   for (int i = n - 2; i >= 0; --i) {
     const int64_t p = base + (int64_t)i * stride;
-    x = (double)out[p] - tri_row(i, n, log_a, a).cp * x;
+    x = fma(tri_row(i, n, log_a, a).c, x, (double)out[p]);
     out[p] = (float)x;
   }
 }
@@ -244,27 +241,28 @@ __global__ void k_copy_zero(const float *__restrict__ g, float *__restrict__ r,
 
 hipError_t launch_tri_lines(const float *in, float *out, int axis, int n, int64_t nlines, int nx,
                             int ny, double h_over_l, hipStream_t stream) {
-  const double a = std::exp(-h_over_l), scale = std::expm1(-h_over_l) * std::expm1(-h_over_l);
+  const double a = std::exp(-h_over_l);
   // As many lines per block, 64 at most, as fit the LDS tile; fewer where
-  // that leaves compute units without a block.
+  // that leaves compute units without a block (200 x 200 x 160, three axes: 78
+  // us with at least one block a unit, 83 with two, 95 with four).
   const int pad = n | 1;  // odd: a wavefront's x lines start in different banks
   auto bytes = [&](int nl) {
-    return 2 * (size_t)n * sizeof(double) + (size_t)nl * (axis == 0 ? pad : n) * sizeof(float);
+    return (size_t)n * sizeof(TriRow) + (size_t)nl * (axis == 0 ? pad : n) * sizeof(float);
   };
   int nl = 64;
-  while (nl > 8 && (bytes(nl) > kTileBytes || nlines < (int64_t)nl * 512)) nl /= 2;
+  while (nl > 8 && (bytes(nl) > kTileBytes || nlines < (int64_t)nl * 256)) nl /= 2;
   if (bytes(nl) > kTileBytes) {
     hipLaunchKernelGGL(k_tri_lines, dim3((unsigned)((nlines + 255) / 256)), dim3(256), 0, stream,
-                       in, out, axis, n, nlines, nx, ny, -h_over_l, a, scale);
+                       in, out, axis, n, nlines, nx, ny, -h_over_l, a);
     return hipGetLastError();
   }
   const dim3 grid((unsigned)((nlines + nl - 1) / nl));
   if (axis == 0)
     hipLaunchKernelGGL(k_tri_tile<true>, grid, dim3(256), bytes(nl), stream, in, out, n, nlines,
-                       nx, ny, axis, nl, pad, -h_over_l, a, scale);
+                       nx, ny, axis, nl, pad, -h_over_l, a);
   else
     hipLaunchKernelGGL(k_tri_tile<false>, grid, dim3(256), bytes(nl), stream, in, out, n, nlines,
-                       nx, ny, axis, nl, pad, -h_over_l, a, scale);
+                       nx, ny, axis, nl, pad, -h_over_l, a);
   return hipGetLastError();
 }
 
