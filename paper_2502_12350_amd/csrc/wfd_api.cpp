@@ -2065,21 +2065,10 @@ wfd_status wfd_cnn_pack_input(const float *grad, const float *illum, int64_t n, 
 // ---- gradient smoothing ------------------------------------------------------
 
 namespace {
-constexpr int kSmoothPartials = 512;
-
 size_t smooth_bytes(int mode, int nx, int ny, int nz) {
   const size_t vol = (size_t)nx * ny * nz;
   if (mode == WFD_SMOOTH_LAPLACE) return align_up(2 * (size_t)(nx + ny + nz) * sizeof(double));
-  return align_up(3 * vol * sizeof(float)) + align_up(kSmoothPartials * sizeof(double));
-}
-
-double sum_partials_host(const double *dev, std::vector<double> &host, hipStream_t s,
-                         hipError_t &err) {
-  err = hipMemcpyAsync(host.data(), dev, host.size() * sizeof(double), hipMemcpyDeviceToHost, s);
-  if (err == hipSuccess) err = hipStreamSynchronize(s);
-  double t = 0.0;
-  for (double v : host) t += v;
-  return t;
+  return align_up(3 * vol * sizeof(float)) + align_up(wfd::cg_scratch_bytes());
 }
 }  // namespace
 
@@ -2132,42 +2121,34 @@ wfd_status wfd_smooth(int32_t mode, const float *in, float *out, int32_t nx, int
   if (out == in) return fail(WFD_E_ARG, "the Bessel filter needs out != in");
   if (max_iter < 1) return fail(WFD_E_ARG, "max_iter must be >= 1");
   if (!(tol > 0.0)) return fail(WFD_E_ARG, "tol must be > 0");
-  char *base = static_cast<char *>(work);
-  float *r = reinterpret_cast<float *>(base);
-  float *p = r + n;
-  float *ap = p + n;
-  double *part = reinterpret_cast<double *>(base + align_up(3 * (size_t)n * sizeof(float)));
+  float *vols = static_cast<float *>(work);
+  void *scratch = static_cast<char *>(work) + align_up(3 * (size_t)n * sizeof(float));
   const float cx = (float)(lengths[0] * lengths[0] / (spacing[0] * spacing[0]));
   const float cy = (float)(lengths[1] * lengths[1] / (spacing[1] * spacing[1]));
   const float cz = (float)(lengths[2] * lengths[2] / (spacing[2] * spacing[2]));
-  std::vector<double> hp(kSmoothPartials);
-  hipError_t e = hipSuccess;
-  HIP_TRY(wfd::launch_cg_start(in, r, out, n, part, kSmoothPartials, st));
-  const double gg = sum_partials_host(part, hp, st, e);
-  if (e != hipSuccess) return fail(WFD_E_HIP, "smoothing: %s", hipGetErrorString(e));
-  if (iterations) *iterations = 0;
-  if (gg == 0.0) return WFD_OK;
-  HIP_TRY(wfd::launch_cg_direction(p, r, n, 0.0f, kSmoothPartials, st));
-  double rr = gg;
-  int it = 0;
-  while (it < max_iter && rr > tol * tol * gg) {
-    HIP_TRY(wfd::launch_bessel_apply(p, ap, nx, ny, nz, cx, cy, cz, part, kSmoothPartials, st));
-    const double pap = sum_partials_host(part, hp, st, e);
-    if (e != hipSuccess) return fail(WFD_E_HIP, "smoothing: %s", hipGetErrorString(e));
-    const double alpha = rr / pap;
-    HIP_TRY(wfd::launch_cg_update(out, r, p, ap, n, (float)alpha, part, kSmoothPartials, st));
-    const double rr_new = sum_partials_host(part, hp, st, e);
-    if (e != hipSuccess) return fail(WFD_E_HIP, "smoothing: %s", hipGetErrorString(e));
-    ++it;
-    if (rr_new <= tol * tol * gg) {
-      rr = rr_new;
-      break;
-    }
-    HIP_TRY(wfd::launch_cg_direction(p, r, n, (float)(rr_new / rr), kSmoothPartials, st));
-    rr = rr_new;
+  const double tol2 = tol * tol;
+  const int blocks = wfd::cg_blocks(nx, ny, nz);
+  HIP_TRY(wfd::launch_cg_start(in, out, vols, n, blocks, scratch, st));
+  // Iterations are enqueued in groups; the host looks after each at the
+  // residual and sizes the next group from its decrease so far.  Iterations
+  // enqueued past convergence change nothing.
+  int it = 0, group = 8;
+  double rr = 0.0, gg = 0.0;
+  for (int k = 0;;) {
+    const int end = (int)std::min<int64_t>(max_iter, (int64_t)k + group);
+    for (; k < end; ++k)
+      HIP_TRY(wfd::launch_cg_iteration(k, tol2, nx, ny, nz, cx, cy, cz, out, vols, scratch, st));
+    double *dev = nullptr, host[3];
+    HIP_TRY(wfd::launch_cg_check(blocks, scratch, &dev, st));
+    HIP_TRY(hipMemcpyAsync(host, dev, sizeof(host), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    rr = host[0], gg = host[1], it = (int)host[2];
+    if (!(rr > tol2 * gg) || k >= max_iter) break;
+    const double rate = std::log(gg / rr) / k, left = std::log(rr / (tol2 * gg));
+    group = rate > 0.0 && left / rate < 32.0 ? std::max(2, (int)std::ceil(left / rate)) : 32;
   }
   if (iterations) *iterations = it;
-  if (rr > tol * tol * gg)
+  if (rr > tol2 * gg)
     return fail(WFD_E_RANGE, "smoothing: no convergence in %d iterations (residual %.3g)", it,
                 std::sqrt(rr / gg));
   return WFD_OK;

@@ -244,14 +244,18 @@ hipError_t launch_pack_input(const float *grad, const float *illum, int64_t n, f
 // ---- gradient smoothing kernels (wfd_smooth.hip) ----
 hipError_t launch_tri_lines(const float *in, float *out, int axis, int n, int64_t nlines, int nx,
                             int ny, double h_over_l, hipStream_t stream);
-hipError_t launch_bessel_apply(const float *x, float *y, int nx, int ny, int nz, float cx,
-                               float cy, float cz, double *part, int npart, hipStream_t stream);
-hipError_t launch_cg_update(float *x, float *r, const float *p, const float *ap, int64_t n,
-                            float alpha, double *part, int npart, hipStream_t stream);
-hipError_t launch_cg_direction(float *p, const float *r, int64_t n, float beta, int npart,
+// Bessel filter: conjugate gradients with device-side scalars.  vols holds
+// three volumes (r and two of p), scratch cg_scratch_bytes() bytes.  start:
+// r = in, x = 0.  iteration k = 0, 1, ..: nothing once rr <= tol2 <in, in>.
+// check writes {rr, <in, in>, iterations} to *out (device).
+size_t cg_scratch_bytes();
+int cg_blocks(int nx, int ny, int nz);
+hipError_t launch_cg_start(const float *in, float *x, float *vols, int64_t n, int blocks,
+                           void *scratch, hipStream_t stream);
+hipError_t launch_cg_iteration(int k, double tol2, int nx, int ny, int nz, float cx, float cy,
+                               float cz, float *x, float *vols, void *scratch,
                                hipStream_t stream);
-hipError_t launch_cg_start(const float *g, float *r, float *x, int64_t n, double *part, int npart,
-                           hipStream_t stream);
+hipError_t launch_cg_check(int blocks, void *scratch, double **out, hipStream_t stream);
 hipError_t launch_resample(const float *in, int nrec, int nt_in, double dt_in, float *out,
                            int nt_out, double dt_out, int sinc, hipStream_t stream);
 

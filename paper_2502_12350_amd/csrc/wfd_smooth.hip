@@ -22,6 +22,7 @@
 namespace wfd {
 namespace {
 
+constexpr int kCgBlocks = 2048;  // blocks of a conjugate-gradient kernel: 8 per CU
 constexpr size_t kTileBytes = 64 << 10;  // LDS of a block's lines: two blocks per CU at least
 
 // Line L of an axis: first point and stride between consecutive points.
@@ -156,85 +157,162 @@ __global__ void k_tri_lines(const float *in, float *out, int axis, int n, int64_
   }
 }
 
-// y = B x and a per-block partial of <p, y> when p is given.
-__global__ void k_bessel_apply(const float *__restrict__ x, float *__restrict__ y, int nx, int ny,
-                               int nz, float cx, float cy, float cz, double *__restrict__ part) {
-  __shared__ double red[256];
-  const int64_t n = (int64_t)nx * ny * nz;
-  double s = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const int ix = (int)(i % nx), iy = (int)((i / nx) % ny), iz = (int)(i / ((int64_t)nx * ny));
-    const float c = x[i];
-    // zero-flux ends: a missing neighbour contributes no difference
-    float dxx = 0.0f, dyy = 0.0f, dzz = 0.0f;
-    if (ix > 0) dxx += x[i - 1] - c;
-    if (ix < nx - 1) dxx += x[i + 1] - c;
-    if (iy > 0) dyy += x[i - nx] - c;
-    if (iy < ny - 1) dyy += x[i + nx] - c;
-    if (iz > 0) dzz += x[i - (int64_t)nx * ny] - c;
-    if (iz < nz - 1) dzz += x[i + (int64_t)nx * ny] - c;
-    const float v = c - (cx * dxx + cy * dyy + cz * dzz);
-    y[i] = v;
-    s += (double)c * (double)v;
-  }
-  red[threadIdx.x] = s;
+// Conjugate gradients on B u = g from u = 0, two kernels per iteration whose
+// scalars stay on the device, so that iterations are enqueued without waiting:
+//   direction: beta = rr_k / rr_{k-1};  p_k = r + beta p_{k-1};  <p, B p>
+//   update:    alpha = rr_k / <p, B p>;  x += alpha p;  r -= alpha B p;  <r, r>
+// Each kernel first sums the partials of the one before (every block, in the
+// same order) and does nothing once rr_k <= tol^2 <g, g>.  Both form B p at
+// their points themselves (the direction kernel from r and p_{k-1} of the
+// seven points), so B p is never stored: 12 and 20 B per point.  A block
+// marches 256 consecutive points of an x-y plane (rows of any length fill its
+// lanes) along z; the z neighbours are kept in registers, the others come
+// through the caches.
+struct Cg {
+  double rr[2];  // rr_k in [k & 1]
+  double gg;
+  int it, pad;   // iterations begun
+};
+constexpr int kCgBlock = 256;
+
+struct CgGrid {
+  int nx, ny, nz, zc, nch;  // z planes per chunk, chunks
+  int64_t plane, pblocks, items;
+  float cx, cy, cz;
+};
+
+// Sum over the block of one FP64 value per thread, to every thread.
+__device__ __forceinline__ double cg_block_sum(double v) {
+  __shared__ double part[kCgBlock / 64];
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
-}
-
-// x += alpha p; r -= alpha Ap; per-block partial of <r, r>.
-__global__ void k_cg_update(float *__restrict__ x, float *__restrict__ r,
-                            const float *__restrict__ p, const float *__restrict__ ap, int64_t n,
-                            float alpha, double *__restrict__ part) {
-  __shared__ double red[256];
-  double s = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    x[i] += alpha * p[i];
-    const float ri = r[i] - alpha * ap[i];
-    r[i] = ri;
-    s += (double)ri * (double)ri;
-  }
-  red[threadIdx.x] = s;
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
+  return (part[0] + part[1]) + (part[2] + part[3]);
+}
+__device__ __forceinline__ double cg_partials(const double *__restrict__ part, int np) {
+  double v = 0.0;
+  for (int i = threadIdx.x; i < np; i += kCgBlock) v += part[i];
+  return cg_block_sum(v);
+}
+
+// Calls f(i, c, v) for the block's points: element i, c = p, v = (B p).
+// at(i) gives p at element i.
+template <class At, class F>
+__device__ __forceinline__ void cg_march(const CgGrid &g, At at, F f) {
+  for (int64_t item = blockIdx.x; item < g.items; item += gridDim.x) {
+    const int64_t ch = item / g.pblocks, l = (item - ch * g.pblocks) * kCgBlock + threadIdx.x;
+    if (l >= g.plane) continue;
+    const int iy = (int)(l / g.nx), ix = (int)(l - (int64_t)iy * g.nx);
+    const int z0 = (int)ch * g.zc, z1 = z0 + g.zc < g.nz ? z0 + g.zc : g.nz;
+    // a neighbour past an end reads the point itself: no difference (zero flux)
+    const int64_t xm = ix > 0 ? -1 : 0, xp = ix < g.nx - 1 ? 1 : 0;
+    const int64_t ym = iy > 0 ? -(int64_t)g.nx : 0, yp = iy < g.ny - 1 ? g.nx : 0;
+    int64_t i = z0 * g.plane + l;
+    float c = at(i), zm = z0 > 0 ? at(i - g.plane) : c;
+    for (int z = z0; z < z1; ++z, i += g.plane) {
+      const float zp = z < g.nz - 1 ? at(i + g.plane) : c;
+      float dxx = 0.0f, dyy = 0.0f, dzz = 0.0f;
+      dxx += at(i + xm) - c;
+      dxx += at(i + xp) - c;
+      dyy += at(i + ym) - c;
+      dyy += at(i + yp) - c;
+      dzz += zm - c;
+      dzz += zp - c;
+      f(i, c, c - (g.cx * dxx + g.cy * dyy + g.cz * dzz));
+      zm = c;
+      c = zp;
+    }
   }
-  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
-// p = r + beta p (beta = 0: p = r); optionally also x = 0 and r = g first.
-__global__ void k_cg_direction(float *__restrict__ p, const float *__restrict__ r, int64_t n,
-                               float beta) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = r[i] + beta * p[i];
-}
-
-__global__ void k_copy_zero(const float *__restrict__ g, float *__restrict__ r,
-                            float *__restrict__ x, int64_t n, double *__restrict__ part) {
-  __shared__ double red[256];
+template <bool FIRST>
+__global__ void __launch_bounds__(kCgBlock, 8)
+    k_cg_direction(CgGrid g, int k, double tol2, const float *__restrict__ r,
+                   const float *__restrict__ p_old, float *__restrict__ p, Cg *cg,
+                   const double *__restrict__ part_rr, double *__restrict__ part_pap) {
+  const double rr = cg_partials(part_rr, gridDim.x);
+  const double gg = FIRST ? rr : cg->gg;
+  const bool go = rr > tol2 * gg;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    cg->rr[k & 1] = rr;
+    if (FIRST) cg->gg = gg;
+    if (go) cg->it = k + 1;
+  }
+  if (!go) return;
+  const float beta = FIRST ? 0.0f : (float)(rr / cg->rr[(k + 1) & 1]);
   double s = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
+  cg_march(g, [&](int64_t i) { return FIRST ? r[i] : r[i] + beta * p_old[i]; },
+           [&](int64_t i, float c, float v) {
+             p[i] = c;
+             s += (double)c * (double)v;
+           });
+  s = cg_block_sum(s);
+  if (threadIdx.x == 0) part_pap[blockIdx.x] = s;
+}
+
+__global__ void __launch_bounds__(kCgBlock, 8)
+    k_cg_update(CgGrid g, int k, double tol2, float *__restrict__ x, float *__restrict__ r,
+                const float *__restrict__ p, const Cg *cg, const double *__restrict__ part_pap,
+                double *__restrict__ part_rr) {
+  const double rr = cg->rr[k & 1];
+  if (!(rr > tol2 * cg->gg)) return;
+  const float alpha = (float)(rr / cg_partials(part_pap, gridDim.x));
+  double s = 0.0;
+  cg_march(g, [&](int64_t i) { return p[i]; },
+           [&](int64_t i, float c, float v) {
+             x[i] += alpha * c;
+             const float ri = r[i] - alpha * v;
+             r[i] = ri;
+             s += (double)ri * (double)ri;
+           });
+  s = cg_block_sum(s);
+  if (threadIdx.x == 0) part_rr[blockIdx.x] = s;
+}
+
+// rr after the iterations enqueued so far, for the host.
+__global__ void __launch_bounds__(kCgBlock)
+    k_cg_check(int np, const double *__restrict__ part_rr, const Cg *__restrict__ cg,
+               double *__restrict__ out) {
+  const double rr = cg_partials(part_rr, np);
+  if (threadIdx.x == 0) {
+    out[0] = rr;
+    out[1] = cg->gg;
+    out[2] = (double)cg->it;
+  }
+}
+
+__global__ void __launch_bounds__(kCgBlock)
+    k_cg_start(const float *__restrict__ g, float *__restrict__ r, float *__restrict__ x,
+               int64_t n, Cg *cg, double *__restrict__ part_rr) {
+  double s = 0.0;
+  for (int64_t i = (int64_t)blockIdx.x * kCgBlock + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * kCgBlock) {
     const float v = g[i];
     r[i] = v;
     x[i] = 0.0f;
     s += (double)v * (double)v;
   }
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
+  s = cg_block_sum(s);
+  if (threadIdx.x == 0) part_rr[blockIdx.x] = s;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    cg->it = 0;
+    cg->gg = 0.0;
   }
-  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
+}
+
+CgGrid cg_grid(int nx, int ny, int nz, float cx, float cy, float cz) {
+  CgGrid g{};
+  g.nx = nx, g.ny = ny, g.nz = nz;
+  g.plane = (int64_t)nx * ny;
+  g.pblocks = (g.plane + kCgBlock - 1) / kCgBlock;
+  // as many z chunks as make one item per block of a full device
+  const int64_t want = std::max<int64_t>(1, std::min<int64_t>(nz, kCgBlocks / g.pblocks));
+  g.zc = (int)((nz + want - 1) / want);
+  g.nch = (nz + g.zc - 1) / g.zc;
+  g.items = g.pblocks * g.nch;
+  g.cx = cx, g.cy = cy, g.cz = cz;
+  return g;
 }
 
 }  // namespace
@@ -266,28 +344,47 @@ hipError_t launch_tri_lines(const float *in, float *out, int axis, int n, int64_
   return hipGetLastError();
 }
 
-hipError_t launch_bessel_apply(const float *x, float *y, int nx, int ny, int nz, float cx,
-                               float cy, float cz, double *part, int npart, hipStream_t stream) {
-  hipLaunchKernelGGL(k_bessel_apply, dim3(npart), dim3(256), 0, stream, x, y, nx, ny, nz, cx, cy,
-                     cz, part);
+size_t cg_scratch_bytes() { return sizeof(Cg) + (2 * kCgBlocks + 4) * sizeof(double); }
+
+hipError_t launch_cg_start(const float *in, float *x, float *vols, int64_t n, int blocks,
+                           void *scratch, hipStream_t stream) {
+  Cg *cg = static_cast<Cg *>(scratch);
+  hipLaunchKernelGGL(k_cg_start, dim3(blocks), dim3(kCgBlock), 0, stream, in, vols, x, n, cg,
+                     reinterpret_cast<double *>(cg + 1));
   return hipGetLastError();
 }
 
-hipError_t launch_cg_update(float *x, float *r, const float *p, const float *ap, int64_t n,
-                            float alpha, double *part, int npart, hipStream_t stream) {
-  hipLaunchKernelGGL(k_cg_update, dim3(npart), dim3(256), 0, stream, x, r, p, ap, n, alpha, part);
-  return hipGetLastError();
+int cg_blocks(int nx, int ny, int nz) {
+  return (int)std::min<int64_t>(kCgBlocks, cg_grid(nx, ny, nz, 0, 0, 0).items);
 }
 
-hipError_t launch_cg_direction(float *p, const float *r, int64_t n, float beta, int npart,
+hipError_t launch_cg_iteration(int k, double tol2, int nx, int ny, int nz, float cx, float cy,
+                               float cz, float *x, float *vols, void *scratch,
                                hipStream_t stream) {
-  hipLaunchKernelGGL(k_cg_direction, dim3(npart), dim3(256), 0, stream, p, r, n, beta);
+  const CgGrid g = cg_grid(nx, ny, nz, cx, cy, cz);
+  const int64_t n = g.plane * nz;
+  const int blocks = (int)std::min<int64_t>(kCgBlocks, g.items);
+  Cg *cg = static_cast<Cg *>(scratch);
+  double *rr = reinterpret_cast<double *>(cg + 1), *pap = rr + kCgBlocks;
+  float *r = vols, *p = vols + n * (1 + (k & 1)), *p_old = vols + n * (2 - (k & 1));
+  if (k == 0)
+    hipLaunchKernelGGL(k_cg_direction<true>, dim3(blocks), dim3(kCgBlock), 0, stream, g, k, tol2,
+                       r, p_old, p, cg, rr, pap);
+  else
+    hipLaunchKernelGGL(k_cg_direction<false>, dim3(blocks), dim3(kCgBlock), 0, stream, g, k, tol2,
+                       r, p_old, p, cg, rr, pap);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_cg_update, dim3(blocks), dim3(kCgBlock), 0, stream, g, k, tol2, x, r, p, cg,
+                     pap, rr);
   return hipGetLastError();
 }
 
-hipError_t launch_cg_start(const float *g, float *r, float *x, int64_t n, double *part, int npart,
-                           hipStream_t stream) {
-  hipLaunchKernelGGL(k_copy_zero, dim3(npart), dim3(256), 0, stream, g, r, x, n, part);
+hipError_t launch_cg_check(int blocks, void *scratch, double **out, hipStream_t stream) {
+  Cg *cg = static_cast<Cg *>(scratch);
+  double *rr = reinterpret_cast<double *>(cg + 1);
+  *out = rr + 2 * kCgBlocks;
+  hipLaunchKernelGGL(k_cg_check, dim3(1), dim3(kCgBlock), 0, stream, blocks, rr, cg, *out);
   return hipGetLastError();
 }
 

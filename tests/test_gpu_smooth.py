@@ -128,3 +128,21 @@ def test_laplace_tiles(shape):
         assert float(np.abs(out.cpu().numpy() - ref).max()) <= tol
         smooth(x, "laplace", lens, H, out=x)
         assert torch.equal(x, out)
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 1), (1, 2, 300), (70, 3, 2), (9, 33, 31), (3, 16, 16),
+                                   (40, 17, 15)])
+def test_bessel_blocks(shape):
+    """Planes below, at and above a block's 256 points, and ends on every axis.
+    The residual tolerance bounds the error relative to the input (B >= I);
+    every iteration adds a few roundings of 2^-24."""
+    torch = gpu_or_skip()
+    from paper_2502_12350_amd import smooth
+    g = np.random.default_rng(5).standard_normal(shape).astype(np.float32)
+    for lens in ((20.0, 30.0, 12.0), (60.0, 0.0, 40.0)):
+        ref = osm.bessel_filter(g, lens, H)
+        out, it = smooth(torch.from_numpy(g).cuda(), "bessel", lens, H, tol=1e-7)
+        assert it >= 1
+        assert np.linalg.norm(out.cpu().numpy() - ref) <= 1e-5 * np.linalg.norm(g)
+    out, it = smooth(torch.zeros(shape, device="cuda"), "bessel", lens, H)
+    assert it == 0 and float(out.abs().max()) == 0.0
