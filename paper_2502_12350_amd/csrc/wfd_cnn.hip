@@ -29,6 +29,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <initializer_list>
 #include <type_traits>
 
 #include "wfd_internal.h"
@@ -686,11 +687,11 @@ __global__ void __launch_bounds__(CM_THR, COUT == 16 ? 2 : 4)
 // (kz, ky) pair a lane reads 10 elements once and shifts them in registers.
 // Each wavefront owns one output row and accumulates all 27 taps (and the
 // bias, as a product with a ones fragment) over every plane of every tile it
-// visits; the grid is persistent, and each wavefront writes one row of
-// partial sums that two fixed-order passes reduce.
+// visits; the grid is persistent, and each block writes one row of partial
+// sums (its wavefronts added in order), reduced in a fixed order.
 constexpr int WG_TY = 4, WG_ZC = 16, WG_THR = 256, WG_RX = 80, WG_LY = WG_TY + 2;
-constexpr int WG_ROW = 27 * 256 + 16;  // partial sums of a wavefront: [tap][co][ci], then db[co]
-constexpr int WG_MAXB = 512, WG_SEG = 32;
+constexpr int wg_row(int cin, int cout) { return (27 * cin + 1) * cout; }  // a block's dw and db
+constexpr int WG_MAXB = 512;
 
 inline int wg_tiles(int nx, int ny, int nz) {
   return ((nx + 63) / 64) * ((ny + WG_TY - 1) / WG_TY) * ((nz + WG_ZC - 1) / WG_ZC);
@@ -826,6 +827,28 @@ struct WgDz {
   }
 };
 
+// Sums the four wavefronts' accumulators in LDS, in order, and writes the
+// block's row of partials: dw as [tap][ci][co], then db.  each(put) calls
+// put(index, value) for the values of its lane.
+template <int CIN, int COUT, class Each>
+__device__ __forceinline__ void wg_write_row(uint32_t *lds, float *__restrict__ partial,
+                                             Each each) {
+  constexpr int ROW = wg_row(CIN, COUT);
+  float *sum = reinterpret_cast<float *>(lds);
+  const int wave = threadIdx.x >> 6;
+  for (int w = 0; w < 4; ++w) {
+    if (wave == w) {
+      if (w == 0)
+        each([&](int i, float v) { sum[i] = v; });
+      else
+        each([&](int i, float v) { sum[i] += v; });
+    }
+    __syncthreads();
+  }
+  for (int i = threadIdx.x; i < ROW; i += WG_THR)
+    partial[(size_t)blockIdx.x * ROW + i] = sum[i];
+}
+
 template <int CIN, int COUT>
 __global__ void __launch_bounds__(WG_THR)
     k_wgrad(const uint16_t *__restrict__ in, const uint16_t *__restrict__ dz, int nx, int ny,
@@ -922,17 +945,18 @@ __global__ void __launch_bounds__(WG_THR)
       __syncthreads();
     }
   }
-  // lane holds D[co = 4 g + e][ci = j] of every tap: each wavefront writes
-  // its own partial row; the bias sums D_b[co][j] are the same for every j
-  float *row = partial + ((size_t)blockIdx.x * 4 + wave) * WG_ROW;
+  // lane holds D[co = 4 g + e][ci = j] of every tap; the bias sums D_b[co][j]
+  // are the same for every j
+  wg_write_row<CIN, COUT>(lin, partial, [&](auto put) {
 #pragma unroll
-  for (int t = 0; t < 27; ++t)
+    for (int t = 0; t < 27; ++t)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) row[t * 256 + (4 * g + e) * 16 + j] = acc[t][e];
-  if (j == 0) {
+      for (int e = 0; e < 4; ++e) put((t * 16 + j) * 16 + 4 * g + e, acc[t][e]);
+    if (j == 0) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) row[27 * 256 + 4 * g + e] = accb[e];
-  }
+      for (int e = 0; e < 4; ++e) put(27 * 256 + 4 * g + e, accb[e]);
+    }
+  });
 }
 
 // Eight consecutive elements starting s = 0, 1 or 2 elements past an aligned
@@ -1059,55 +1083,57 @@ __global__ void __launch_bounds__(WG_THR)
       __syncthreads();
     }
   }
-  // lane holds D[i = 4 g + e][j] of each product; one partial row per wavefront
-  float *row = partial + ((size_t)blockIdx.x * 4 + wave) * WG_ROW;
+  // lane holds D[i = 4 g + e][j] of each product
+  wg_write_row<MODE == 0 ? 16 : 2, MODE == 0 ? 1 : 16>(lring, partial, [&](auto put) {
 #pragma unroll
-  for (int q = 0; q < NQ; ++q)
+    for (int q = 0; q < NQ; ++q)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int i = 4 * g + e;
-      if (MODE == 0) {  // D[tap = 16 q + i][ci = j]
-        const int t = 16 * q + i;
-        if (t < 27) row[t * 256 + j] = acc[q][e];
-      } else {          // D[co = i][(tap, ci) = j]
-        const int t = 8 * q + (j >> 1);
-        if (t < 27) row[t * 256 + i * 16 + (j & 1)] = acc[q][e];
+      for (int e = 0; e < 4; ++e) {
+        const int i = 4 * g + e;
+        if (MODE == 0) {  // D[tap = 16 q + i][ci = j]
+          const int t = 16 * q + i;
+          if (t < 27) put(t * 16 + j, acc[q][e]);
+        } else {          // D[co = i][(tap, ci) = j]
+          const int t = 8 * q + (j >> 1);
+          if (t < 27) put((t * 2 + (j & 1)) * 16 + i, acc[q][e]);
+        }
       }
-    }
-  if (MODE == 0) {  // db from the centre tap's row (13 = 4 * 3 + 1)
-    if (j == 0 && g == 3) row[27 * 256] = accb[1];
-  } else if (j == 0) {
+    if (MODE == 0) {  // db from the centre tap's row (13 = 4 * 3 + 1)
+      if (j == 0 && g == 3) put(27 * 16, accb[1]);
+    } else if (j == 0) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) row[27 * 256 + 4 * g + e] = accb[e];
-  }
+      for (int e = 0; e < 4; ++e) put(27 * 32 + 4 * g + e, accb[e]);
+    }
+  });
 }
 
-// Fixed-order reduction of the wavefronts' partial rows: pass 1 sums each
-// segment of WG_SEG rows in order, pass 2 sums the segment totals in order
-// and scatters them into dW[tap][ci][co] and db[co].
-__global__ void k_wgrad_seg(const float *__restrict__ partial, int nrows,
-                            float *__restrict__ seg) {
-  const int col = blockIdx.x * blockDim.x + threadIdx.x;
-  if (col >= WG_ROW) return;
-  const int r0 = blockIdx.y * WG_SEG, r1 = min(r0 + WG_SEG, nrows);
+// Fixed-order reduction of the blocks' partial rows into dw and db: a block
+// sums 64 columns, its 16 wavefronts every 16th row each and then one another
+// in order.  (Rows of one wavefront each, laid out for 16 x 16 channels in
+// every layer and reduced in two passes, took 31 us a layer at 128^3, as long
+// as the smaller layers' products.)
+constexpr int WG_RED = 16;  // wavefronts of a reducing block
+__global__ void __launch_bounds__(64 * WG_RED)
+    k_wgrad_reduce(const float *__restrict__ partial, int nrows, int cols, int ndw,
+                   float *__restrict__ dw, float *__restrict__ db) {
+  __shared__ float red[WG_RED][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int col = blockIdx.x * 64 + lane;
   float s = 0.0f;
-  for (int r = r0; r < r1; ++r) s += partial[(size_t)r * WG_ROW + col];
-  seg[(size_t)blockIdx.y * WG_ROW + col] = s;
-}
-
-__global__ void k_wgrad_final(const float *__restrict__ seg, int nseg, int cin, int cout,
-                              float *__restrict__ dw, float *__restrict__ db) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= WG_ROW) return;
-  float s = 0.0f;
-  for (int k = 0; k < nseg; ++k) s += seg[(size_t)k * WG_ROW + i];
-  if (i < 27 * 256) {
-    const int t = i / 256, co = (i / 16) % 16, ci = i % 16;
-    if (co < cout && ci < cin) dw[(t * cin + ci) * cout + co] = s;
-  } else {
-    const int co = i - 27 * 256;
-    if (co < cout && db) db[co] = s;
+  if (col < cols) {
+#pragma unroll 8
+    for (int r = w; r < nrows; r += WG_RED) s += partial[(size_t)r * cols + col];
   }
+  red[w][lane] = s;
+  __syncthreads();
+  if (w > 0 || col >= cols) return;
+  s = red[0][lane];
+#pragma unroll
+  for (int k = 1; k < WG_RED; ++k) s += red[k][lane];
+  if (col < ndw)
+    dw[col] = s;
+  else if (db)
+    db[col - ndw] = s;
 }
 
 // Pack FP32 master weights W[tap][ci][co] into the matrix-core layout.
@@ -1129,35 +1155,95 @@ __global__ void k_pack_weights(const float *__restrict__ w, int cin, int cout, i
   apk[i] = to_bf16(v);
 }
 
-// Residual of the output against the target: loss partials (FP64, fixed
-// order inside a block) and dy = bf16(2 (y - t) / n).
-__global__ void k_mse(const float *__restrict__ y, const float *__restrict__ t, int64_t n,
-                      uint16_t *__restrict__ dy, double *__restrict__ partial) {
-  __shared__ double red[256];
-  double s = 0.0;
-  const double inv = 2.0 / (double)n;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const double d = (double)y[i] - (double)t[i];  // exact
-    s += d * d;
-    dy[i] = to_bf16((float)(inv * d));
-  }
-  red[threadIdx.x] = s;
+// Block reductions of the loss and the input scales: a butterfly of shuffles
+// in each wavefront, then the wavefronts' values in order.
+constexpr int RB_THR = 1024;  // threads: kCnnReduceBlocks blocks then fill the device
+template <class T, class Op>
+__device__ __forceinline__ T rb_reduce(T v, Op op) {
+  __shared__ T red[RB_THR / 64];
+  for (int o = 32; o > 0; o >>= 1) v = op(v, __shfl_xor(v, o, 64));
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  v = red[0];
+  for (int w = 1; w < (int)(blockDim.x >> 6); ++w) v = op(v, red[w]);
+  return v;
+}
+struct RbMax {
+  __device__ float operator()(float a, float b) const { return fmaxf(a, b); }
+};
+struct RbSum {
+  __device__ double operator()(double a, double b) const { return a + b; }
+};
+// Largest of np partials, to every thread.
+__device__ __forceinline__ float rb_max_of(const float *__restrict__ part, int np) {
+  float m = 0.0f;
+  for (int i = threadIdx.x; i < np; i += blockDim.x) m = fmaxf(m, part[i]);
+  return rb_reduce(m, RbMax());
 }
 
-__global__ void k_sum_f64(const double *__restrict__ partial, int n, double scale,
-                          double *__restrict__ out) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    double s = 0.0;
-    for (int i = 0; i < n; ++i) s += partial[i];
-    *out = s * scale;
+// Calls f(i, k) over the elements of a grid-stride loop: groups of four from i
+// (k = 4) with VEC, then the last n % 4 one at a time; VEC only for 16-byte
+// aligned arrays.
+template <bool VEC, class F>
+__device__ __forceinline__ void rb_for(int64_t n, F f) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x,
+                step = (int64_t)gridDim.x * blockDim.x;
+  const int64_t n4 = VEC ? n / 4 : 0;
+  for (int64_t i = t; i < n4; i += step) f(4 * i, std::integral_constant<int, 4>{});
+  for (int64_t i = 4 * n4 + t; i < n; i += step) f(i, std::integral_constant<int, 1>{});
+}
+template <int K>
+__device__ __forceinline__ void rb_load(float *v, const float *__restrict__ p) {
+  if constexpr (K == 4) {
+    const f32x4 q = *reinterpret_cast<const f32x4 *>(p);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = q[e];
+  } else {
+    v[0] = *p;
   }
+}
+inline bool rb_aligned(std::initializer_list<const void *> ps) {
+  for (const void *p : ps)
+    if ((uintptr_t)p % 16) return false;
+  return true;
+}
+
+// Residual of the output against the target: loss partials (FP64, fixed
+// order inside a block) and dy = bf16(2 (y - t) / n).
+template <bool VEC>
+__global__ void __launch_bounds__(RB_THR)
+    k_mse(const float *__restrict__ y, const float *__restrict__ t, int64_t n,
+          uint16_t *__restrict__ dy, double *__restrict__ partial) {
+  double s = 0.0;
+  const double inv = 2.0 / (double)n;
+  rb_for<VEC>(n, [&](int64_t i, auto kc) {
+    constexpr int K = decltype(kc)::value;
+    float a[K], b[K];
+    uint32_t q[K];
+    rb_load<K>(a, y + i);
+    rb_load<K>(b, t + i);
+#pragma unroll
+    for (int e = 0; e < K; ++e) {
+      const double d = (double)a[e] - (double)b[e];  // exact
+      s += d * d;
+      q[e] = to_bf16((float)(inv * d));
+    }
+    if constexpr (K == 4)
+      *reinterpret_cast<u32x2 *>(dy + i) = u32x2{q[0] | q[1] << 16, q[2] | q[3] << 16};
+    else
+      dy[i] = (uint16_t)q[0];
+  });
+  s = rb_reduce(s, RbSum());
+  if (threadIdx.x == 0) partial[blockIdx.x] = s;
+}
+
+__global__ void __launch_bounds__(RB_THR)
+    k_sum_f64(const double *__restrict__ partial, int n, double scale, double *__restrict__ out) {
+  double s = 0.0;
+  for (int i = threadIdx.x; i < n; i += blockDim.x) s += partial[i];
+  s = rb_reduce(s, RbSum());
+  if (threadIdx.x == 0) *out = s * scale;
 }
 
 // Adam (Kingma & Ba, Alg. 1) on FP32 parameters.
@@ -1174,62 +1260,63 @@ __global__ void k_adam(float *__restrict__ w, const float *__restrict__ g, float
   w[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
 }
 
-// Largest |x| per block; with illum set, of x / (illum + eps * max|illum|),
-// the maximum of illum being reduced from the np entries of pmax first.
-__global__ void k_absmax(const float *__restrict__ x, const float *__restrict__ illum,
-                         const float *__restrict__ pmax, int np, float eps, int64_t n,
-                         float *__restrict__ partial) {
-  __shared__ float red[256];
-  __shared__ float shift;
-  if (illum) {
-    if (threadIdx.x == 0) {
-      float m = 0.0f;
-      for (int i = 0; i < np; ++i) m = fmaxf(m, pmax[i]);
-      shift = eps * m;
-    }
-    __syncthreads();
-  }
+// The input scales take three passes of 4, 8 and 8 + 4 bytes per voxel.  Every
+// block reduces the partials of the pass before with all its threads, and
+// 512 blocks of 1024 threads fill the device: at 256^3 15, 24 and 35 us, with
+// one thread per block reducing the 512 partials in turn 41, 104 and 100.
+//
+// Largest |x| per block; with COMP, of x / (illum + eps * max|illum|), the
+// maximum of illum being reduced from the np entries of pmax first.
+template <bool COMP, bool VEC>
+__global__ void __launch_bounds__(RB_THR)
+    k_absmax(const float *__restrict__ x, const float *__restrict__ illum,
+             const float *__restrict__ pmax, int np, float eps, int64_t n,
+             float *__restrict__ partial) {
+  const float shift = COMP ? eps * rb_max_of(pmax, np) : 0.0f;
   float s = 0.0f;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const float v = illum ? (shift > 0.0f ? x[i] / (illum[i] + shift) : x[i]) : x[i];
-    s = fmaxf(s, fabsf(v));
-  }
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + w]);
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
+  rb_for<VEC>(n, [&](int64_t i, auto kc) {
+    constexpr int K = decltype(kc)::value;
+    float a[K], b[K];
+    rb_load<K>(a, x + i);
+    if (COMP) rb_load<K>(b, illum + i);
+#pragma unroll
+    for (int e = 0; e < K; ++e)
+      s = fmaxf(s, fabsf(COMP && shift > 0.0f ? a[e] / (b[e] + shift) : a[e]));
+  });
+  s = rb_reduce(s, RbMax());
+  if (threadIdx.x == 0) partial[blockIdx.x] = s;
 }
 
 // Network input [voxel][2]: c = grad / (illum + eps max|illum|) scaled by
 // max|c|, and illum scaled by max|illum| (a channel with maximum 0 is left
 // unscaled).  pi, pc: per-block maxima of |illum| and |c|.
-__global__ void k_pack_input(const float *__restrict__ grad, const float *__restrict__ illum,
-                             int64_t n, float eps, const float *__restrict__ pi,
-                             const float *__restrict__ pc, int np, uint16_t *__restrict__ out) {
-  __shared__ float mi, mc;
-  if (threadIdx.x == 0) {
-    float a = 0.0f, b = 0.0f;
-    for (int i = 0; i < np; ++i) {
-      a = fmaxf(a, pi[i]);
-      b = fmaxf(b, pc[i]);
-    }
-    mi = a;
-    mc = b;
-  }
-  __syncthreads();
+template <bool VEC>
+__global__ void __launch_bounds__(RB_THR)
+    k_pack_input(const float *__restrict__ grad, const float *__restrict__ illum, int64_t n,
+                 float eps, const float *__restrict__ pi, const float *__restrict__ pc, int np,
+                 uint16_t *__restrict__ out) {
+  const float mi = rb_max_of(pi, np), mc = rb_max_of(pc, np);
   const float shift = eps * mi;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const float c = mi > 0.0f ? grad[i] / (illum[i] + shift) : grad[i];
-    out[2 * i] = to_bf16(mc > 0.0f ? c / mc : c);
-    out[2 * i + 1] = to_bf16(mi > 0.0f ? illum[i] / mi : illum[i]);
-  }
+  rb_for<VEC>(n, [&](int64_t i, auto kc) {
+    constexpr int K = decltype(kc)::value;
+    float a[K], b[K];
+    uint32_t q[K];
+    rb_load<K>(a, grad + i);
+    rb_load<K>(b, illum + i);
+#pragma unroll
+    for (int e = 0; e < K; ++e) {
+      const float c = mi > 0.0f ? a[e] / (b[e] + shift) : a[e];
+      q[e] = (uint32_t)to_bf16(mc > 0.0f ? c / mc : c) |
+             (uint32_t)to_bf16(mi > 0.0f ? b[e] / mi : b[e]) << 16;
+    }
+    if constexpr (K == 4) {
+      *reinterpret_cast<u32x4 *>(out + 2 * i) = u32x4{q[0], q[1], q[2], q[3]};
+    } else {
+      out[2 * i] = (uint16_t)q[0];
+      out[2 * i + 1] = (uint16_t)(q[0] >> 16);
+    }
+  });
 }
-
 
 }  // namespace
 
@@ -1258,18 +1345,16 @@ hipError_t launch_conv(int cin, int cout, const uint16_t *in, int nx, int ny, in
 
 int cnn_wgrad_blocks(int nx, int ny, int nz) { return std::min(wg_tiles(nx, ny, nz), WG_MAXB); }
 
-// partial rows (four per block) followed by the segment totals
+// one row of partials per block, for the layer with the longest row
 size_t cnn_wgrad_workspace_floats(int nx, int ny, int nz) {
-  const int rows = 4 * cnn_wgrad_blocks(nx, ny, nz);
-  return (size_t)(rows + (rows + WG_SEG - 1) / WG_SEG) * WG_ROW;
+  return (size_t)cnn_wgrad_blocks(nx, ny, nz) * wg_row(16, 16);
 }
 
 hipError_t launch_wgrad(int cin, int cout, const uint16_t *in, const uint16_t *dz, int nx, int ny,
                         int nz, float *work, float *dw, float *db, hipStream_t stream) {
   const int ntiles = wg_tiles(nx, ny, nz);
-  const int nb = cnn_wgrad_blocks(nx, ny, nz), rows = 4 * nb;
-  const int nseg = (rows + WG_SEG - 1) / WG_SEG;
-  float *partial = work, *seg = work + (size_t)rows * WG_ROW;
+  const int nb = cnn_wgrad_blocks(nx, ny, nz);
+  float *partial = work;
 #define WFD_WG(CI, CO)                                                                          \
   hipLaunchKernelGGL((k_wgrad<CI, CO>), dim3(nb), dim3(WG_THR), 0, stream, in, dz, nx, ny, nz, \
                      ntiles, partial)
@@ -1284,11 +1369,9 @@ hipError_t launch_wgrad(int cin, int cout, const uint16_t *in, const uint16_t *d
 #undef WFD_WGP
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int cb = (WG_ROW + 255) / 256;
-  hipLaunchKernelGGL(k_wgrad_seg, dim3(cb, nseg), dim3(256), 0, stream, partial, rows, seg);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_wgrad_final, dim3(cb), dim3(256), 0, stream, seg, nseg, cin, cout, dw, db);
+  const int cols = wg_row(cin, cout);
+  hipLaunchKernelGGL(k_wgrad_reduce, dim3((cols + 63) / 64), dim3(64 * WG_RED), 0, stream, partial,
+                     nb, cols, cols - cout, dw, db);
   return hipGetLastError();
 }
 
@@ -1303,11 +1386,14 @@ hipError_t launch_pack_weights(const float *w, int cin, int cout, int flip, uint
 
 hipError_t launch_mse(const float *y, const float *t, int64_t n, uint16_t *dy, double *partial,
                       int npart, double *loss, hipStream_t stream) {
-  hipLaunchKernelGGL(k_mse, dim3(npart), dim3(256), 0, stream, y, t, n, dy, partial);
+  if (rb_aligned({y, t, dy}))
+    hipLaunchKernelGGL(k_mse<true>, dim3(npart), dim3(RB_THR), 0, stream, y, t, n, dy, partial);
+  else
+    hipLaunchKernelGGL(k_mse<false>, dim3(npart), dim3(RB_THR), 0, stream, y, t, n, dy, partial);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_sum_f64, dim3(1), dim3(64), 0, stream, partial, npart, 1.0 / (double)n,
-                     loss);
+  hipLaunchKernelGGL(k_sum_f64, dim3(1), dim3(RB_THR), 0, stream, partial, npart,
+                     1.0 / (double)n, loss);
   return hipGetLastError();
 }
 
@@ -1322,16 +1408,21 @@ hipError_t launch_adam(float *w, const float *g, float *m, float *v, int n, floa
 hipError_t launch_pack_input(const float *grad, const float *illum, int64_t n, float eps,
                              float *partial, int npart, uint16_t *out, hipStream_t stream) {
   float *pi = partial, *pc = partial + npart;
-  hipLaunchKernelGGL(k_absmax, dim3(npart), dim3(256), 0, stream, illum, nullptr, nullptr, 0, 0.0f,
-                     n, pi);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_absmax, dim3(npart), dim3(256), 0, stream, grad, illum, pi, npart, eps, n,
-                     pc);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_pack_input, dim3(npart), dim3(256), 0, stream, grad, illum, n, eps, pi, pc,
-                     npart, out);
+  const dim3 grid(npart), block(RB_THR);
+  const bool vec = rb_aligned({grad, illum, out});
+#define WFD_PACK(V)                                                                              \
+  hipLaunchKernelGGL((k_absmax<false, V>), grid, block, 0, stream, illum, nullptr, nullptr, 0,   \
+                     0.0f, n, pi);                                                               \
+  hipLaunchKernelGGL((k_absmax<true, V>), grid, block, 0, stream, grad, illum, pi, npart, eps, n, \
+                     pc);                                                                        \
+  hipLaunchKernelGGL((k_pack_input<V>), grid, block, 0, stream, grad, illum, n, eps, pi, pc,     \
+                     npart, out)
+  if (vec) {
+    WFD_PACK(true);
+  } else {
+    WFD_PACK(false);
+  }
+#undef WFD_PACK
   return hipGetLastError();
 }
 

@@ -371,3 +371,32 @@ def test_training_lowers_the_loss_and_is_deterministic():
     say(f"  loss {l1[0]:.4e} -> {l1[-1]:.4e}")
     assert l1[-1] < 0.2 * l1[0]
     assert l1 == l2 and torch.equal(w1, w2)
+
+
+@pytest.mark.parametrize("n, offset", [(1, 0), (3, 1), (4, 0), (1023, 0), (4099, 0), (4099, 1),
+                                       (2300000, 0)])
+def test_loss_and_input_packing_any_length_and_alignment(n, offset):
+    """Groups of four and what is left of them, on aligned buffers and on ones
+    that start four bytes later; more elements than the grid has threads."""
+    torch = gpu_or_skip()
+    import ctypes as C
+    from paper_2502_12350_amd import _lib
+    P, _, _ = _net(torch)
+    L = _lib.lib()
+    rng = np.random.default_rng(n + offset)
+    a, b = (rng.standard_normal(n + offset).astype(np.float32)[offset:] for _ in range(2))
+    b = np.abs(b) + np.float32(0.01)
+    dev = [torch.from_numpy(np.concatenate([np.zeros(offset, np.float32), v])).cuda()[offset:]
+           for v in (a, b)]
+    got = _np(P.pack_input(dev[0], dev[1]))
+    frac, worst = _bf16_close(got, cnn.pack_input(a, b))
+    assert frac <= max(1e-3, 1.0 / n) and worst <= 1.0
+    dy = torch.full((n + 1,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    loss = torch.zeros((), dtype=torch.float64, device="cuda")
+    _lib.check(L.wfd_cnn_mse(dev[0].data_ptr(), dev[1].data_ptr(), n, dy.data_ptr(),
+                             loss.data_ptr(), P._reduce.data_ptr(), P._reduce.numel(),
+                             P._stream()))
+    d = a.astype(np.float64) - b.astype(np.float64)
+    assert abs(float(loss) - np.mean(d * d)) <= 1e-12 * np.mean(d * d)
+    assert np.array_equal(_np(dy[:n]), cnn.bf16(((2.0 / n) * d).astype(np.float32)))
+    assert bool(torch.isnan(dy[n]))
