@@ -266,50 +266,36 @@ void cpml_table(int n, int border, double h, double dt, double vmax, double fpea
 // layer, i.e. the grid minus the inner box, as up to 6 boxes.
 wfd::Shell make_shell(const wfd_grid &g, int Nx, int Ny, int Nz) {
   const int N = g.border;
-  auto inner = [&](int n, int total, bool low_layer, int &lo, int &hi) {
-    lo = (N > 0 && low_layer) ? N + wfd::kStencilRadius : 0;
-    hi = N > 0 ? N + n - 1 - wfd::kStencilRadius : total - 1;  // inclusive
-  };
-  int zlo, zhi, ylo, yhi, xlo, xhi;
-  inner(g.nz, Nz, g.free_surface == 0, zlo, zhi);
-  inner(g.ny, Ny, true, ylo, yhi);
-  inner(g.nx, Nx, true, xlo, xhi);
   wfd::Shell sh{};
-  const bool empty_inner = N == 0 || zlo > zhi || ylo > yhi || xlo > xhi;
-  sh.lo[0] = empty_inner ? Nx : xlo, sh.hi[0] = empty_inner ? -1 : xhi;
-  sh.lo[1] = empty_inner ? Ny : ylo, sh.hi[1] = empty_inner ? -1 : yhi;
-  sh.lo[2] = empty_inner ? Nz : zlo, sh.hi[2] = empty_inner ? -1 : zhi;
-  auto add = [&](int z0, int z1, int y0, int y1, int x0, int x1) {
+  auto inner = [&](int d, int n, int total, bool low_layer) {
+    sh.lo[d] = (N > 0 && low_layer) ? N + wfd::kStencilRadius : 0;
+    sh.hi[d] = N > 0 ? N + n - 1 - wfd::kStencilRadius : total - 1;  // inclusive
+  };
+  inner(0, g.nx, Nx, true);
+  inner(1, g.ny, Ny, true);
+  inner(2, g.nz, Nz, g.free_surface == 0);
+  if (N == 0) return sh;  // no layer: empty shell
+  auto add = [&](int kind, int z0, int z1, int y0, int y1, int x0, int x1) {
     if (z1 <= z0 || y1 <= y0 || x1 <= x0) return;
     const int b = sh.nbox++;
-    sh.z0[b] = z0, sh.z1[b] = z1, sh.y0[b] = y0, sh.y1[b] = y1, sh.x0[b] = x0, sh.x1[b] = x1;
-    sh.zfirst[b] = (z1 - z0) < (y1 - y0);
+    sh.id[kind] = b;
+    sh.z0[b] = z0, sh.y0[b] = y0, sh.x0[b] = x0, sh.ny[b] = y1 - y0, sh.nx[b] = x1 - x0;
+    sh.start[b] = sh.points;
+    sh.points += (int64_t)(z1 - z0) * (y1 - y0) * (x1 - x0);
   };
-  if (N == 0) {
-    // no layer: empty shell
-  } else if (zlo > zhi || ylo > yhi || xlo > xhi) {
-    add(0, Nz, 0, Ny, 0, Nx);  // the inner box is empty: every point
-  } else {
-    add(0, zlo, 0, Ny, 0, Nx);
-    add(zhi + 1, Nz, 0, Ny, 0, Nx);
-    add(zlo, zhi + 1, 0, ylo, 0, Nx);
-    add(zlo, zhi + 1, yhi + 1, Ny, 0, Nx);
-    add(zlo, zhi + 1, ylo, yhi + 1, 0, xlo);
-    add(zlo, zhi + 1, ylo, yhi + 1, xhi + 1, Nx);
+  const int *lo = sh.lo, *hi = sh.hi;
+  if (lo[2] > hi[2] || lo[1] > hi[1] || lo[0] > hi[0]) {
+    // the inner box is empty (an axis whose every cell is within reach): every
+    // point, all ids 0
+    add(0, 0, Nz, 0, Ny, 0, Nx);
+    return sh;
   }
-  sh.start[0] = 0;
-  sh.bstart[0] = 0;
-  for (int b = 0; b < sh.nbox; ++b) {
-    const int nxb = sh.x1[b] - sh.x0[b], nyb = sh.y1[b] - sh.y0[b], nzb = sh.z1[b] - sh.z0[b];
-    sh.start[b + 1] = sh.start[b] + (int64_t)nzb * nyb * nxb;
-    // a plane of the box within reach of a z layer
-    sh.zq[b] = sh.z0[b] < sh.lo[2] || sh.z1[b] - 1 > sh.hi[2];
-    sh.cz[b] = sh.zq[b] ? wfd::kShellChunkZ : wfd::kShellChunk;
-    sh.tx[b] = (nxb + wfd::kShellTileX - 1) / wfd::kShellTileX;
-    sh.ty[b] = (nyb + wfd::kShellTileY - 1) / wfd::kShellTileY;
-    sh.nch[b] = (nzb + sh.cz[b] - 1) / sh.cz[b];
-    sh.bstart[b + 1] = sh.bstart[b] + (int64_t)sh.tx[b] * sh.ty[b] * sh.nch[b];
-  }
+  add(0, 0, lo[2], 0, Ny, 0, Nx);
+  add(1, hi[2] + 1, Nz, 0, Ny, 0, Nx);
+  add(2, lo[2], hi[2] + 1, 0, lo[1], 0, Nx);
+  add(3, lo[2], hi[2] + 1, hi[1] + 1, Ny, 0, Nx);
+  add(4, lo[2], hi[2] + 1, lo[1], hi[1] + 1, 0, lo[0]);
+  add(5, lo[2], hi[2] + 1, lo[1], hi[1] + 1, hi[0] + 1, Nx);
   return sh;
 }
 
@@ -447,10 +433,11 @@ Work work_layout(const wfd_ctx *c, int nrec, WorkKind kind, const wfd_ckpt *ck, 
     w.partial = cv.take<double>((size_t)std::max(1, wfd::residual_partial_count(nrec, c->grid.nt)));
   }
   if (c->cpml) {
-    const size_t S = (size_t)c->shell.start[c->shell.nbox];
+    const size_t S = (size_t)c->shell.points;
     for (int i = 0; i < 6; ++i) w.mem[i] = cv.take<float>((size_t)mem_len(c, i));
     if (kind == WorkKind::Gradient && ck && ck->mode == WFD_CKPT_FULL)
       w.cstore = cv.take<float>((size_t)c->grid.nt * S);
+    if (kind != WorkKind::Gradient) w.lastc = cv.take<float>(std::max<size_t>(S, 1));
     if (kind == WorkKind::Gradient && ck && ck->mode == WFD_CKPT_REVOLVE) {
       for (int i = 0; i < 6; ++i) w.amem[i] = cv.take<float>((size_t)mem_len(c, i));
       w.smem = cv.take<float>((size_t)nsnap * (size_t)mem_set_len(c));
@@ -803,7 +790,8 @@ wfd_status wfd_set_model(wfd_ctx *c, const wfd_grid *grid, const float *vel,
           1, wfd::cpml_mem_len(d, c->Nx, c->Ny, c->Nz, grid->border));
     c->shell = make_shell(*grid, c->Nx, c->Ny, c->Nz);
     for (int b = 0; b < c->shell.nbox; ++b)
-      if (c->shell.start[b + 1] - c->shell.start[b] >= (int64_t(1) << 31))
+      if ((b + 1 < c->shell.nbox ? c->shell.start[b + 1] : c->shell.points) -
+              c->shell.start[b] >= (int64_t(1) << 31))
         return fail(WFD_E_ARG, "padded grid too large for the CPML layer's point boxes");
   }
   c->has_model = true;
@@ -852,34 +840,25 @@ wfd_status cpml_forward_terms(wfd_ctx *c, const wfd::StepGrid &g, const Work &w,
                               float *const *mem = nullptr) {
   Timed t(c, WFD_K_OTHER);
   float *const *m = mem ? mem : w.mem;  // out == nullptr: only the memory variables and C
-  HIP_TRY(wfd::launch_cpml_psi(g, c->cpml_tab, c->shell, cur, m[0], m[1], m[2], c->stream));
-  HIP_TRY(wfd::launch_cpml_zeta(g, c->cpml_tab, c->shell, cur, m[0], m[1], m[2], m[3], m[4],
-                                m[5], out, cstore, c->stream));
+  HIP_TRY(wfd::launch_cpml_forward(g, c->cpml_tab, c->shell, cur, m, out,
+                                   cstore ? cstore : w.lastc, cstore != nullptr, c->stream));
   if (nrec > 0 && out)
     HIP_TRY(wfd::launch_record(out, w.rec_idx, w.rec_scale, nrec, n, w.seis_tm, c->stream));
   return WFD_OK;
 }
 
-// The CPML layer's share of adjoint step m: nu and mu from phi^{m+1} (phi1)
-// before the step kernel, then (pre = false) the correction of phi^m and the
-// imaging term phi^{m+1} C^m.
+// The CPML layer's share of adjoint step m (after the step kernel wrote phi^m
+// from phi1 = phi^{m+1}): nu and mu, the correction of phi^m and the imaging
+// term phi^{m+1} C^m.
 wfd_status cpml_adjoint_terms(wfd_ctx *c, const wfd::StepGrid &g, const Work &w,
-                              const float *phi1, float *phi, int m, bool pre,
-                              const float *corr_m = nullptr) {
+                              const float *phi1, float *phi, int m, const float *corr_m) {
   Timed t(c, WFD_K_OTHER);
   float *const *v = w.smem ? w.amem : w.mem;  // mu = v[0..2], nu = v[3..5]
-  if (pre) {
-    HIP_TRY(wfd::launch_cpml_nu(g, c->cpml_tab, c->shell, phi1, v[3], v[4], v[5], c->stream));
-    HIP_TRY(wfd::launch_cpml_mu(g, c->cpml_tab, c->shell, phi1, v[3], v[4], v[5], v[0], v[1],
-                                v[2], c->stream));
-    return WFD_OK;
-  }
   const float *cst = m >= c->grid.nt ? nullptr
                      : corr_m      ? corr_m
-                     : w.cstore    ? w.cstore + (size_t)m * (size_t)c->shell.start[c->shell.nbox]
+                     : w.cstore    ? w.cstore + (size_t)m * (size_t)c->shell.points
                                    : nullptr;
-  HIP_TRY(wfd::launch_cpml_adjoint(g, c->cpml_tab, c->shell, v[3], v[4], v[5], v[0], v[1], v[2],
-                                   phi, phi1, cst, w.g, c->stream));
+  HIP_TRY(wfd::launch_cpml_adjoint(g, c->cpml_tab, c->shell, phi1, v, phi, cst, w.g, c->stream));
   return WFD_OK;
 }
 
@@ -1061,14 +1040,12 @@ wfd_status wfd_gradient_ex(wfd_ctx *c, const float *wavelet, const double src_xy
     return WFD_OK;
   };
   auto adjoint = [&](int m, const float *wm, const float *corr_m = nullptr) -> wfd_status {
-    if (c->cpml && (s = cpml_adjoint_terms(c, g, w, A1, A2, m, true)) != WFD_OK) return s;
     {
       Timed t(c, WFD_K_ADJOINT);
       HIP_TRY(wfd::launch_adjoint_step(c->tuning, g, A1, A2, A2, rt, w.res_tm, m, wm, w.g, il,
                                        c->stream));
     }
-    if (c->cpml && (s = cpml_adjoint_terms(c, g, w, A1, A2, m, false, corr_m)) != WFD_OK)
-      return s;
+    if (c->cpml && (s = cpml_adjoint_terms(c, g, w, A1, A2, m, corr_m)) != WFD_OK) return s;
     if (wavelet_grad) {  // psi^m (in A2) at the source
       Timed t(c, WFD_K_OTHER);
       HIP_TRY(wfd::launch_source_gradient(A2, c->k, src_idx, w.scale, out_exp2, m, wavelet_grad,
@@ -1086,7 +1063,7 @@ wfd_status wfd_gradient_ex(wfd_ctx *c, const float *wavelet, const double src_xy
                                        w.seis_tm, c->tuning, c->stream));
     }
     if (c->cpml) {  // full storage keeps every step's C; checkpointing the latest
-      float *cst = w.cstore ? w.cstore + (size_t)n * (size_t)c->shell.start[c->shell.nbox]
+      float *cst = w.cstore ? w.cstore + (size_t)n * (size_t)c->shell.points
                             : w.lastc;
       if ((s = cpml_forward_terms(c, g, w, cur, out, cst, rec ? nrec : 0, n)) != WFD_OK)
         return s;

@@ -15,11 +15,20 @@
 //
 // D1 is the eighth-order central first difference (4/5, -1/5, 4/105, -1/280)
 // and D2 the second difference of L; cells outside the padded grid are zero,
-// and D2 along z reads the free surface's negated image like L does.  A block
-// of 64 x 4 threads owns an (x, y) tile of one shell box and marches a chunk
-// of planes; where the box is within reach of a z layer each thread keeps
-// nine-plane queues along z, and x and y neighbours come through the caches.
-// The point-wise nu update runs one thread per shell point.
+// and D2 along z reads the free surface's negated image like L does.
+//
+// Everything an axis adds depends on that axis' lines alone, so one kernel per
+// axis and direction does all of it: a block takes a tile of lines over one
+// end's segment (the layer and the 4 cells beyond), loads each array once,
+// keeps w and psi (a nu + phi1, a nu, then a mu) in LDS between the two
+// recursions and writes psi, zeta and the correction: 36 B per point forward,
+// 44 B adjoint with imaging, every load issued before the first barrier.  The
+// axes' kernels follow one another (x, y, z) because their corrections add up
+// where the layers cross.  240 x 240 x 200 with a 20-cell layer (7.4 M line
+// points): 73 us a forward step and 81 us an adjoint step, 3.7-4.1 TB/s, where
+// kernels that walked the shell's points and read every neighbour line through
+// the caches took 141 and 363 us.  What is left is the start and end of three
+// short launches and the x kernels' partial cache lines.
 //
 // A memory variable of axis d is nonzero only on that axis' layer, the B
 // border cells at each end of the padded axis, and is stored as two slabs of
@@ -33,6 +42,9 @@
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
+
+#include <algorithm>
+#include <type_traits>
 
 #include "wfd_internal.h"
 
@@ -50,383 +62,437 @@ __device__ __forceinline__ float d2c(int j) {
                   : (float)(-1.0 / 560.0);
 }
 
-__device__ __forceinline__ int64_t lin(const StepGrid &g, int x, int y, int z) {
-  return (int64_t)z * g.plane + (int64_t)y * g.pitch + x;
-}
-
-// Compact memory variables (above): stored index of cell i on an axis of n
-// cells with slab width `half` and stored length `len`, whether it is stored,
-// and the element of (x, y, z) in the x, y or z variable.
+// Stored index of cell i on an axis of n cells with slab width `half` and
+// stored length `len` (above).
 __device__ __forceinline__ int cidx(int i, int half, int len, int n) {
   return i < half ? i : i - (n - len);
 }
-__device__ __forceinline__ bool stored(int i, int half, int len, int n) {
-  return i < half || i >= n - (len - half);
-}
-__device__ __forceinline__ int64_t mem_x(const StepGrid &g, const CpmlTables &t, int x, int y,
-                                         int z) {
-  return ((int64_t)z * g.ny + y) * t.len[0] + cidx(x, t.half[0], t.len[0], g.nx);
-}
-__device__ __forceinline__ int64_t mem_y(const StepGrid &g, const CpmlTables &t, int x, int y,
-                                         int z) {
-  return ((int64_t)z * t.len[1] + cidx(y, t.half[1], t.len[1], g.ny)) * g.nx + x;
-}
-__device__ __forceinline__ int64_t mem_z(const StepGrid &g, const CpmlTables &t, int x, int y,
-                                         int z) {
-  return ((int64_t)cidx(z, t.half[2], t.len[2], g.nz) * g.ny + y) * g.nx + x;
-}
-__device__ __forceinline__ bool stored_z(const StepGrid &g, const CpmlTables &t, int z) {
-  return z >= 0 && z < g.nz && stored(z, t.half[2], t.len[2], g.nz);
-}
 
-// Shell point q -> (x, y, z).  Offsets inside a box fit 32 bits (the host
-// checks), so the divisions are 32-bit: 64-bit ones are long software
-// sequences and dominated these kernels.
-__device__ __forceinline__ void decode(const Shell &sh, int64_t q, int &x, int &y, int &z) {
-  int b = 0;
-  while (b + 1 < sh.nbox && q >= sh.start[b + 1]) ++b;
-  const uint32_t l = (uint32_t)(q - sh.start[b]);
-  const uint32_t nxb = (uint32_t)(sh.x1[b] - sh.x0[b]);
-  const uint32_t r = l / nxb;
-  x = sh.x0[b] + (int)(l - r * nxb);
-  if (sh.zfirst[b]) {
-    const uint32_t nzb = (uint32_t)(sh.z1[b] - sh.z0[b]);
-    const uint32_t yy = r / nzb;
-    z = sh.z0[b] + (int)(r - yy * nzb);
-    y = sh.y0[b] + (int)yy;
-  } else {
-    const uint32_t nyb = (uint32_t)(sh.y1[b] - sh.y0[b]);
-    const uint32_t zz = r / nyb;
-    y = sh.y0[b] + (int)(r - zz * nyb);
-    z = sh.z0[b] + (int)zz;
-  }
+// A shell point's index in the correction store's layout is the x = 0 index of
+// its row plus x; x matters for the choice of the box between the x layers.
+__device__ __forceinline__ int64_t shell_row(const Shell &sh, int b, int y, int z) {
+  return sh.start[b] + ((int64_t)(z - sh.z0[b]) * sh.ny[b] + (y - sh.y0[b])) * sh.nx[b] -
+         sh.x0[b];
 }
-
-// Within reach (4 cells) of the layer of axis d = 0, 1, 2 (x, y, z).
+// Box of the points of a row within reach of a y or z layer.
+__device__ __forceinline__ int row_box(const Shell &sh, int y, int z) {
+  return z < sh.lo[2] ? sh.id[0] : z > sh.hi[2] ? sh.id[1] : y < sh.lo[1] ? sh.id[2] : sh.id[3];
+}
 __device__ __forceinline__ bool near(const Shell &sh, int d, int i) {
   return i < sh.lo[d] || i > sh.hi[d];
 }
 
-// A field along one axis through (x, y, z), optionally weighted by that axis'
-// a table, zero outside the grid.
-struct Line {
-  const float *p;  // the point
-  const float *a;  // weight per index along the axis, or nullptr
-  int64_t stride;  // elements between neighbours along the axis
-  int i, n;        // index along the axis and the axis length
-  bool inner;      // i - 4 .. i + 4 all inside [0, n): no bounds tests
-  __device__ __forceinline__ Line(const float *u, const float *a_, int64_t base, int64_t stride_,
-                                  int i_, int n_)
-      : p(u + base), a(a_), stride(stride_), i(i_), n(n_),
-        inner(i_ >= kStencilRadius && i_ + kStencilRadius < n_) {}
-  __device__ __forceinline__ float operator()(int j) const {  // value at offset j
-    if (!inner) {
-      const int ii = i + j;
-      if (ii < 0 || ii >= n) return 0.0f;
-    }
-    const float v = p[j * stride];
-    return a ? a[i + j] * v : v;
-  }
+// What one axis' kernel needs besides the grid.
+struct AxisJob {
+  const float *a, *b;  // recursion coefficients per index
+  float ih, c2;        // 1 / h, 1 / h^2
+  int n, half, len;    // axis length, slab width and stored length
+  int L, s0[2];        // segment length, first cell of each end's segment
+  int nseg;            // segments (1: the whole axis, or the far end only)
+  int rows;            // x kernels: rows of a plane per block
+  int tiles;           // tiles of a plane's y range (x kernels) or x range
 };
 
-__device__ __forceinline__ float first_diff(const Line &f) {
+// b u + a t.  The rounding of every forward sum is written out (which product
+// is rounded, which is fused), so that traces keep their bits whatever the
+// kernel's shape.
+template <int AXIS>
+__device__ __forceinline__ float recursion(float b, float u, float a, float t) {
+  return AXIS < 2 ? __builtin_fmaf(b, u, a * t) : __builtin_fmaf(t, a, b * u);
+}
+
+// First and second difference around v[0], neighbours `st` apart.
+__device__ __forceinline__ float first_diff(const float *v, int st) {
   float s = 0.0f;
 #pragma unroll
-  for (int j = 1; j <= 4; ++j) s += d1c(j) * (f(j) - f(-j));
+  for (int j = 1; j <= 4; ++j) s += d1c(j) * (v[j * st] - v[-j * st]);
+  return s;
+}
+__device__ __forceinline__ float second_diff(const float *v, int st) {
+  float s = d2c(0) * v[0];
+#pragma unroll
+  for (int j = 1; j <= 4; ++j) s += d2c(j) * (v[j * st] + v[-j * st]);
+  return s;
+}
+// The second difference at cell i of an axis that a tile holds whole, with a
+// free surface at zs: cells before it are the negated image.
+__device__ __forceinline__ float second_diff_image(const float *v, int st, int i, int n, int zs) {
+  auto cell = [&](int o) {
+    if (i + o >= zs) return v[o * st];
+    const int m = 2 * zs - (i + o);
+    return m < n ? -v[(m - i) * st] : 0.0f;
+  };
+  float s = d2c(0) * cell(0);
+#pragma unroll
+  for (int j = 1; j <= 4; ++j) s += d2c(j) * (cell(j) + cell(-j));
   return s;
 }
 
-// Second difference along the line (x or y: no image planes).
-__device__ __forceinline__ float second_diff(const Line &f) {
-  float s = d2c(0) * f(0);
-#pragma unroll
-  for (int j = 1; j <= 4; ++j) s += d2c(j) * (f(j) + f(-j));
-  return s;
-}
-
-constexpr int kThreads = 256;
-static_assert(kThreads == kShellTileX * kShellTileY, "a column block is one x-y tile");
-
-// The (x, y) column and z chunk of this thread (column marching).  Returns
-// false for lanes past the box's x or y extent.
-struct Column {
-  int b, x, y, z0, z1;
-  uint32_t nxb, nyb, nzb;
-  int64_t pxy;  // offset of (x, y) in a plane
-  __device__ __forceinline__ bool init(const Shell &sh, const StepGrid &g) {
-    const int64_t blk = blockIdx.x;
-    b = 0;
-    while (b + 1 < sh.nbox && blk >= sh.bstart[b + 1]) ++b;
-    uint32_t l = (uint32_t)(blk - sh.bstart[b]);
-    const uint32_t ch = l % (uint32_t)sh.nch[b];
-    l /= (uint32_t)sh.nch[b];
-    const uint32_t ty = l % (uint32_t)sh.ty[b], tx = l / (uint32_t)sh.ty[b];
-    x = sh.x0[b] + (int)tx * kShellTileX + (int)(threadIdx.x % kShellTileX);
-    y = sh.y0[b] + (int)ty * kShellTileY + (int)(threadIdx.x / kShellTileX);
-    z0 = sh.z0[b] + (int)ch * sh.cz[b];
-    z1 = min(z0 + sh.cz[b], sh.z1[b]);
-    nxb = (uint32_t)(sh.x1[b] - sh.x0[b]);
-    nyb = (uint32_t)(sh.y1[b] - sh.y0[b]);
-    nzb = (uint32_t)(sh.z1[b] - sh.z0[b]);
-    pxy = (int64_t)y * g.pitch + x;
-    return x < sh.x1[b] && y < sh.y1[b];
+// ---- y and z: T neighbouring x of a plane (y: of z, z: of y), one segment ----
+// Thread group g of the block's NT / T takes cells g R .. g R + R - 1 of the
+// segment, kept in registers; the four cells on either side come through LDS,
+// whose row 4 + c is cell c (zero past the segment's ends).  T = 64: a group is
+// a wavefront, so cells, coefficients and row addresses are scalars.
+template <int AXIS, int NT, int T, int R>
+struct PlaneTile {
+  static constexpr int G = NT / T, ROWS = G * R + 8;
+  int lane, first, s0, x, other;
+  bool ok;
+  int64_t fb, fs, mb, ms;  // field and memory element of cell 0, step per cell
+  __device__ __forceinline__ PlaneTile(const StepGrid &g, const AxisJob &j) {
+    int b = blockIdx.x;
+    s0 = j.s0[b % j.nseg];
+    b /= j.nseg;
+    other = b / j.tiles;
+    lane = threadIdx.x % T;
+    const int grp = threadIdx.x / T;
+    first = (T == 64 ? __builtin_amdgcn_readfirstlane(grp) : grp) * R;
+    x = (b - other * j.tiles) * T + lane;
+    ok = x < g.nx;
+    fb = AXIS == 1 ? (int64_t)other * g.plane : (int64_t)other * g.pitch;
+    fs = AXIS == 1 ? (int64_t)g.pitch : g.plane;
+    mb = AXIS == 1 ? (int64_t)other * j.len * g.nx : (int64_t)other * g.nx;
+    ms = AXIS == 1 ? (int64_t)g.nx : (int64_t)g.ny * g.nx;
   }
-  // index of (x, y, z) in the shell's point order (the correction store)
-  __device__ __forceinline__ int64_t q(const Shell &sh, int z) const {
-    const uint32_t xo = (uint32_t)(x - sh.x0[b]), yo = (uint32_t)(y - sh.y0[b]),
-                   zo = (uint32_t)(z - sh.z0[b]);
-    const uint32_t l = sh.zfirst[b] ? xo + nxb * (zo + nzb * yo) : xo + nxb * (yo + nyb * zo);
-    return sh.start[b] + (int64_t)l;
+  __device__ __forceinline__ int64_t field(int i) const { return fb + i * fs; }
+  __device__ __forceinline__ int64_t mem(const AxisJob &j, int i) const {
+    return mb + cidx(i, j.half, j.len, j.n) * ms;
+  }
+  __device__ __forceinline__ int y(int i) const { return AXIS == 1 ? i : other; }
+  __device__ __forceinline__ int z(int i) const { return AXIS == 1 ? other : i; }
+  __device__ __forceinline__ float *slot(float *s, int c) const {
+    return s + (first + c + 4) * T + lane;
+  }
+  // the group's cells with four on either side: v[4 + c] is cell first + c
+  __device__ __forceinline__ void with_neighbours(float *s, const float *own, float *v) const {
+#pragma unroll
+    for (int c = 0; c < R + 8; ++c)
+      v[c] = c >= 4 && c < 4 + R ? own[c >= 4 && c < 4 + R ? c - 4 : 0] : *slot(s, c - 4);
+  }
+  __device__ __forceinline__ void zero_ends(float *s) const {
+    for (int e = threadIdx.x; e < 8 * T; e += NT)
+      s[e < 4 * T ? e : e + (ROWS - 8) * T] = 0.0f;
   }
 };
 
-// Nine planes z-4 .. z+4 of a quantity along the thread's column; f(z') gives
-// plane z'.  prime() at the chunk's first plane, then advance() per plane.
-struct ZWin {
-  float v[9];
-  template <class F>
-  __device__ __forceinline__ void prime(F f, int z) {
+// cstore carries the correction from one axis to the next where layers cross
+// (the last of them adds k C to out) and, with `keep`, holds it at every point
+// of the shell afterwards.
+template <int AXIS, int NT, int T, int R, bool IMG>
+__global__ void __launch_bounds__(NT)
+    k_cpml_forward(StepGrid g, AxisJob j, Shell sh, const float *__restrict__ w,
+                   float *__restrict__ psi, float *__restrict__ zeta, float *__restrict__ out,
+                   float *__restrict__ cstore, int keep) {
+  const PlaneTile<AXIS, NT, T, R> t(g, j);
+  __shared__ float sw[t.ROWS * T], sp[t.ROWS * T];
+  t.zero_ends(sw);
+  t.zero_ends(sp);
+  const bool near_x = near(sh, 0, t.x);
+  float wv[R], ps[R], ze[R], ov[R], kv[R], cv[R];
 #pragma unroll
-    for (int i = 0; i < 9; ++i) v[i] = f(z - 4 + i);
+  for (int c = 0; c < R; ++c) {
+    wv[c] = ps[c] = ze[c] = ov[c] = kv[c] = cv[c] = 0.0f;
+    if (t.first + c >= j.L || !t.ok) continue;
+    const int i = t.s0 + t.first + c;
+    wv[c] = w[t.field(i) + t.x];
+    if (j.a[i] != 0.0f) {
+      ps[c] = psi[t.mem(j, i) + t.x];
+      ze[c] = zeta[t.mem(j, i) + t.x];
+    }
+    if (!near(sh, AXIS, i)) continue;
+    if (out && (AXIS == 2 || !near(sh, 2, t.z(i)))) {
+      ov[c] = out[t.field(i) + t.x];
+      kv[c] = g.k[t.field(i) + t.x];
+    }
+    if (near_x || (AXIS == 2 && near(sh, 1, t.y(i))))
+      cv[c] = cstore[shell_row(sh, row_box(sh, t.y(i), t.z(i)), t.y(i), t.z(i)) + t.x];
   }
-  template <class F>
-  __device__ __forceinline__ void advance(F f, int z) {  // to plane z + 1
 #pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = v[i + 1];
-    v[8] = f(z + 5);
+  for (int c = 0; c < R; ++c) *t.slot(sw, c) = wv[c];
+  __syncthreads();
+  float v[R + 8];
+  t.with_neighbours(sw, wv, v);
+#pragma unroll
+  for (int c = 0; c < R; ++c) {
+    const int i = t.s0 + t.first + c;
+    float d2 = 0.0f;
+    if (t.first + c < j.L && t.ok && j.a[i] != 0.0f) {
+      ps[c] = recursion<AXIS>(j.b[i], ps[c], j.a[i], j.ih * first_diff(v + c + 4, 1));
+      psi[t.mem(j, i) + t.x] = ps[c];
+      d2 = IMG ? second_diff_image(t.slot(sw, c), T, i, j.n, g.zs) : second_diff(v + c + 4, 1);
+    }
+    *t.slot(sp, c) = ps[c];
+    wv[c] = d2;
   }
-  __device__ __forceinline__ float d1() const {
-    float s = 0.0f;
+  __syncthreads();
+  t.with_neighbours(sp, ps, v);
 #pragma unroll
-    for (int j = 1; j <= 4; ++j) s += d1c(j) * (v[4 + j] - v[4 - j]);
-    return s;
+  for (int c = 0; c < R; ++c) {
+    const int i = t.s0 + t.first + c;
+    if (t.first + c >= j.L || !t.ok || !near(sh, AXIS, i)) continue;
+    const float d1 = first_diff(v + c + 4, 1), d1p = j.ih * d1;
+    float cc = __builtin_fmaf(j.ih, d1, cv[c]);
+    if (j.a[i] != 0.0f) {
+      const float z = recursion<AXIS>(j.b[i], ze[c], j.a[i], __builtin_fmaf(j.c2, wv[c], d1p));
+      zeta[t.mem(j, i) + t.x] = z;
+      cc += z;
+    }
+    const bool more = AXIS == 1 && near(sh, 2, t.z(i));
+    if (out && !more && t.z(i) > g.zs)
+      out[t.field(i) + t.x] = __builtin_fmaf(cc, kv[c], ov[c]);
+    if (keep || more)
+      cstore[shell_row(sh, row_box(sh, t.y(i), t.z(i)), t.y(i), t.z(i)) + t.x] = cc;
   }
-  __device__ __forceinline__ float d2() const {
-    float s = d2c(0) * v[4];
+}
+
+template <int AXIS, int NT, int T, int R, bool IMG>
+__global__ void __launch_bounds__(NT)
+    k_cpml_adjoint(StepGrid g, AxisJob j, Shell sh, const float *__restrict__ phi1,
+                   float *__restrict__ nu, float *__restrict__ mu, float *__restrict__ phi,
+                   const float *__restrict__ cstore, float *__restrict__ grad) {
+  const PlaneTile<AXIS, NT, T, R> t(g, j);
+  __shared__ float sf[t.ROWS * T], sn[t.ROWS * T];
+  t.zero_ends(sf);
+  t.zero_ends(sn);
+  float fv[R], an[R], mv[R], pv[R], kv[R];
 #pragma unroll
-    for (int j = 1; j <= 4; ++j) s += d2c(j) * (v[4 + j] + v[4 - j]);
-    return s;
+  for (int c = 0; c < R; ++c) {
+    fv[c] = an[c] = mv[c] = pv[c] = kv[c] = 0.0f;
+    if (t.first + c >= j.L || !t.ok) continue;
+    const int i = t.s0 + t.first + c;
+    fv[c] = phi1[t.field(i) + t.x];
+    if (j.a[i] != 0.0f) {
+      an[c] = nu[t.mem(j, i) + t.x];
+      mv[c] = mu[t.mem(j, i) + t.x];
+    }
+    if (!near(sh, AXIS, i)) continue;
+    pv[c] = phi[t.field(i) + t.x];
+    kv[c] = g.k[t.field(i) + t.x];
+    // imaging once per point: by the last axis whose layer it is near
+    if (cstore && (AXIS == 2 || !near(sh, 2, t.z(i))))
+      grad[t.field(i) + t.x] +=
+          fv[c] * cstore[shell_row(sh, row_box(sh, t.y(i), t.z(i)), t.y(i), t.z(i)) + t.x];
+  }
+#pragma unroll
+  for (int c = 0; c < R; ++c) {
+    const int i = t.s0 + t.first + c;
+    if (t.first + c < j.L && t.ok && j.a[i] != 0.0f) {
+      const float v = fv[c] + j.b[i] * an[c];
+      nu[t.mem(j, i) + t.x] = v;
+      an[c] = j.a[i] * v;
+    }
+    fv[c] += an[c];
+    *t.slot(sn, c) = an[c];
+    *t.slot(sf, c) = fv[c];
+  }
+  __syncthreads();
+  float v[R + 8];
+  t.with_neighbours(sf, fv, v);
+#pragma unroll
+  for (int c = 0; c < R; ++c) {
+    const int i = t.s0 + t.first + c;
+    if (t.first + c < j.L && t.ok && j.a[i] != 0.0f) {
+      const float m = j.b[i] * mv[c] - first_diff(v + c + 4, 1) * j.ih;
+      mu[t.mem(j, i) + t.x] = m;
+      mv[c] = j.a[i] * m;
+    }
+  }
+  t.with_neighbours(sn, an, v);
+#pragma unroll
+  for (int c = 0; c < R; ++c) {
+    const int i = t.s0 + t.first + c;
+    fv[c] = j.c2 * (IMG ? second_diff_image(t.slot(sn, c), T, i, j.n, g.zs)
+                        : second_diff(v + c + 4, 1));
+  }
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < R; ++c) *t.slot(sf, c) = mv[c];  // a mu, zero off the layer
+  __syncthreads();
+  t.with_neighbours(sf, mv, v);
+#pragma unroll
+  for (int c = 0; c < R; ++c) {
+    const int i = t.s0 + t.first + c;
+    if (t.first + c >= j.L || !t.ok || !near(sh, AXIS, i) || t.z(i) <= g.zs) continue;
+    phi[t.field(i) + t.x] = pv[c] + kv[c] * (fv[c] - first_diff(v + c + 4, 1) * j.ih);
+  }
+}
+
+// ---- x: rows of a plane, both segments, consecutive elements along x ---------
+// Element e = thread + NT k of the block's rows x segments x cells.
+template <int NT, int N>
+struct RowTile {
+  int y0, z, pitch;   // first row, plane, LDS pitch of a line
+  int P, total;       // positions per row, elements of the block
+  int64_t fb, mb;     // field and memory element of the first row
+  int line[N], pos[N];
+  __device__ __forceinline__ RowTile(const StepGrid &g, const AxisJob &j) {
+    z = blockIdx.x / j.tiles;
+    y0 = (blockIdx.x - z * j.tiles) * j.rows;
+    pitch = j.L + 8;
+    P = j.nseg * j.L;
+    total = min(j.rows, g.ny - y0) * P;
+    fb = (int64_t)z * g.plane + (int64_t)y0 * g.pitch;
+    mb = ((int64_t)z * g.ny + y0) * j.len;
+    const int dl = NT / P, dp = NT - dl * P;
+    int l = threadIdx.x / P, p = threadIdx.x - l * P;
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      line[k] = l, pos[k] = p;
+      l += dl, p += dp;
+      if (p >= P) p -= P, ++l;
+    }
+  }
+  __device__ __forceinline__ bool ok(int k) const {
+    return (int)threadIdx.x + k * NT < total;
+  }
+  __device__ __forceinline__ int x(const AxisJob &j, int k) const {
+    return pos[k] < j.L ? j.s0[0] + pos[k] : j.s0[1] + pos[k] - j.L;
+  }
+  __device__ __forceinline__ int field(const StepGrid &g, int k, int x) const {
+    return line[k] * g.pitch + x;
+  }
+  __device__ __forceinline__ int mem(const AxisJob &j, int k, int x) const {
+    return line[k] * j.len + cidx(x, j.half, j.len, j.n);
+  }
+  __device__ __forceinline__ int slot(const AxisJob &j, int k) const {
+    const int seg = pos[k] < j.L ? 0 : 1;
+    return (line[k] * j.nseg + seg) * pitch + 4 + pos[k] - seg * j.L;
+  }
+  __device__ __forceinline__ int64_t shell(const Shell &sh, int k, int x) const {
+    const int y = y0 + line[k];
+    const int b = near(sh, 2, z) || near(sh, 1, y) ? row_box(sh, y, z)
+                  : x < sh.lo[0]                   ? sh.id[4]
+                                                   : sh.id[5];
+    return shell_row(sh, b, y, z) + x;
+  }
+  __device__ __forceinline__ void zero_ends(float *s, const AxisJob &j) const {
+    for (int e = threadIdx.x; e < j.rows * j.nseg * 8; e += NT) {
+      const int l = e / 8, c = e % 8;
+      s[l * pitch + (c < 4 ? c : j.L + c)] = 0.0f;
+    }
   }
 };
 
-// Plane z' of a column of u (offset pxy): zero outside the grid; with `image`,
-// planes above the free surface read the negated mirror (as L does).
-__device__ __forceinline__ float zval(const float *u, const StepGrid &g, int64_t pxy, int zz,
-                                      bool image) {
-  if (image && zz < g.zs) {
-    const int zm = 2 * g.zs - zz;
-    return zm < g.nz ? -u[(int64_t)zm * g.plane + pxy] : 0.0f;
-  }
-  return (zz >= 0 && zz < g.nz) ? u[(int64_t)zz * g.plane + pxy] : 0.0f;
-}
-
-__global__ void __launch_bounds__(kThreads)
-    k_cpml_psi(StepGrid g, CpmlTables t, Shell sh, const float *__restrict__ w, float *px,
-               float *py, float *pz) {
-  Column c;
-  if (!c.init(sh, g)) return;
-  const bool zq = sh.zq[c.b];
-  const float ax = t.ax[c.x], bx = t.bx[c.x], ay = t.ay[c.y], by = t.by[c.y];
-  auto wz = [&](int zz) { return zval(w, g, c.pxy, zz, false); };
-  ZWin qw;
-  if (zq) qw.prime(wz, c.z0);
-  for (int z = c.z0; z < c.z1; ++z) {
-    const int64_t p = (int64_t)z * g.plane + c.pxy;
-    if (ax != 0.0f) {
-      float &v = px[mem_x(g, t, c.x, c.y, z)];
-      v = bx * v + ax * (first_diff(Line{w, nullptr, p, 1, c.x, g.nx}) * t.ihx);
+template <int NT, int N>
+__global__ void __launch_bounds__(NT)
+    k_cpml_forward_x(StepGrid g, AxisJob j, Shell sh, const float *__restrict__ w,
+                     float *__restrict__ psi, float *__restrict__ zeta, float *__restrict__ out,
+                     float *__restrict__ cstore, int keep) {
+  extern __shared__ float smem[];
+  const RowTile<NT, N> t(g, j);
+  float *sw = smem, *sp = smem + j.rows * j.nseg * t.pitch;
+  t.zero_ends(sw, j);
+  t.zero_ends(sp, j);
+  const bool near_z = near(sh, 2, t.z);
+  w += t.fb, psi += t.mb, zeta += t.mb;
+  const float *kk = g.k + t.fb;
+  float *o = out ? out + t.fb : nullptr;
+  float ps[N], ze[N], ov[N], kv[N];
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    ps[k] = ze[k] = ov[k] = kv[k] = 0.0f;
+    if (!t.ok(k)) continue;
+    const int x = t.x(j, k);
+    sw[t.slot(j, k)] = w[t.field(g, k, x)];
+    if (j.a[x] != 0.0f) {
+      ps[k] = psi[t.mem(j, k, x)];
+      ze[k] = zeta[t.mem(j, k, x)];
     }
-    if (ay != 0.0f) {
-      float &v = py[mem_y(g, t, c.x, c.y, z)];
-      v = by * v + ay * (first_diff(Line{w, nullptr, p, g.pitch, c.y, g.ny}) * t.ihy);
-    }
-    if (zq) {
-      const float az = t.az[z];
-      if (az != 0.0f) {
-        float &v = pz[mem_z(g, t, c.x, c.y, z)];
-        v = t.bz[z] * v + az * (qw.d1() * t.ihz);
-      }
-      qw.advance(wz, z);
+    if (o && near(sh, 0, x) && !near_z && !near(sh, 1, t.y0 + t.line[k])) {
+      ov[k] = o[t.field(g, k, x)];
+      kv[k] = kk[t.field(g, k, x)];
     }
   }
-}
-
-__global__ void __launch_bounds__(kThreads)
-    k_cpml_zeta(StepGrid g, CpmlTables t, Shell sh, const float *__restrict__ w,
-                const float *__restrict__ px, const float *__restrict__ py,
-                const float *__restrict__ pz, float *zx, float *zy, float *zz_, float *out,
-                float *cstore) {
-  Column c;
-  if (!c.init(sh, g)) return;
-  const bool zq = sh.zq[c.b];
-  const bool nx = near(sh, 0, c.x), ny = near(sh, 1, c.y);
-  const float ax = t.ax[c.x], bx = t.bx[c.x], ay = t.ay[c.y], by = t.by[c.y];
-  auto wz = [&](int zz) { return zval(w, g, c.pxy, zz, true); };
-  auto pzz = [&](int zz) { return stored_z(g, t, zz) ? pz[mem_z(g, t, c.x, c.y, zz)] : 0.0f; };
-  ZWin qw, qp;
-  if (zq) {
-    qw.prime(wz, c.z0);
-    qp.prime(pzz, c.z0);
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    if (!t.ok(k)) continue;
+    const int x = t.x(j, k);
+    const float a = j.a[x];
+    if (a != 0.0f) {
+      ps[k] = recursion<0>(j.b[x], ps[k], a, j.ih * first_diff(sw + t.slot(j, k), 1));
+      psi[t.mem(j, k, x)] = ps[k];
+    }
+    sp[t.slot(j, k)] = ps[k];
   }
-  for (int z = c.z0; z < c.z1; ++z) {
-    const int64_t p = (int64_t)z * g.plane + c.pxy;
-    float C = 0.0f;
-    if (nx) {
-      const int64_t q = mem_x(g, t, c.x, c.y, z);
-      const float d1p = first_diff(Line{px, nullptr, q, 1, c.x, g.nx}) * t.ihx;
-      C += d1p;
-      if (ax != 0.0f) {
-        const float v =
-            bx * zx[q] + ax * (second_diff(Line{w, nullptr, p, 1, c.x, g.nx}) * g.cx + d1p);
-        zx[q] = v;
-        C += v;
-      }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    const int x = t.x(j, k);
+    if (!t.ok(k) || !near(sh, 0, x)) continue;
+    const float a = j.a[x], d1 = first_diff(sp + t.slot(j, k), 1), d1p = j.ih * d1;
+    float c = d1p;
+    if (a != 0.0f) {
+      const float d2 = second_diff(sw + t.slot(j, k), 1);
+      const float v = recursion<0>(j.b[x], ze[k], a, __builtin_fmaf(j.c2, d2, d1p));
+      zeta[t.mem(j, k, x)] = v;
+      c += v;
     }
-    if (ny) {
-      const int64_t q = mem_y(g, t, c.x, c.y, z);
-      const float d1p = first_diff(Line{py, nullptr, q, g.nx, c.y, g.ny}) * t.ihy;
-      C += d1p;
-      if (ay != 0.0f) {
-        const float v = by * zy[q] +
-                        ay * (second_diff(Line{w, nullptr, p, g.pitch, c.y, g.ny}) *
-                                  g.cy + d1p);
-        zy[q] = v;
-        C += v;
-      }
-    }
-    if (zq) {
-      if (near(sh, 2, z)) {
-        const float d1p = qp.d1() * t.ihz;
-        C += d1p;
-        const float az = t.az[z];
-        if (az != 0.0f) {
-          float &zv = zz_[mem_z(g, t, c.x, c.y, z)];
-          const float v = t.bz[z] * zv + az * (qw.d2() * g.cz + d1p);
-          zv = v;
-          C += v;
-        }
-      }
-      qw.advance(wz, z);
-      qp.advance(pzz, z);
-    }
-    if (out && z > g.zs) out[p] += g.k[p] * C;
-    if (cstore) cstore[c.q(sh, z)] = C;
+    const bool more = near_z || near(sh, 1, t.y0 + t.line[k]);
+    if (o && !more && t.z > g.zs) o[t.field(g, k, x)] = __builtin_fmaf(c, kv[k], ov[k]);
+    if (keep || more) cstore[t.shell(sh, k, x)] = c;
   }
 }
 
-__global__ void __launch_bounds__(kThreads)
-    k_cpml_nu(StepGrid g, CpmlTables t, Shell sh, const float *__restrict__ phi1, float *nx_,
-              float *ny_, float *nz_) {
-  const int64_t total = sh.start[sh.nbox];
-  for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < total;
-       q += (int64_t)gridDim.x * blockDim.x) {
-    int x, y, z;
-    decode(sh, q, x, y, z);
-    const float f = phi1[lin(g, x, y, z)];
-    if (t.ax[x] != 0.0f) {
-      float &v = nx_[mem_x(g, t, x, y, z)];
-      v = f + t.bx[x] * v;
+template <int NT, int N>
+__global__ void __launch_bounds__(NT)
+    k_cpml_adjoint_x(StepGrid g, AxisJob j, Shell sh, const float *__restrict__ phi1,
+                     float *__restrict__ nu, float *__restrict__ mu, float *__restrict__ phi,
+                     const float *__restrict__ cstore, float *__restrict__ grad) {
+  extern __shared__ float smem[];
+  const RowTile<NT, N> t(g, j);
+  float *sf = smem, *sn = smem + j.rows * j.nseg * t.pitch;
+  t.zero_ends(sf, j);
+  t.zero_ends(sn, j);
+  const bool near_z = near(sh, 2, t.z);
+  phi1 += t.fb, phi += t.fb, grad += t.fb, nu += t.mb, mu += t.mb;
+  const float *kk = g.k + t.fb;
+  float mv[N], pv[N], kv[N];
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    mv[k] = pv[k] = kv[k] = 0.0f;
+    if (!t.ok(k)) continue;
+    const int x = t.x(j, k), f = t.field(g, k, x);
+    const float fv = phi1[f], a = j.a[x];
+    float an = 0.0f;
+    if (a != 0.0f) {
+      mv[k] = mu[t.mem(j, k, x)];
+      const float v = fv + j.b[x] * nu[t.mem(j, k, x)];
+      nu[t.mem(j, k, x)] = v;
+      an = a * v;
     }
-    if (t.ay[y] != 0.0f) {
-      float &v = ny_[mem_y(g, t, x, y, z)];
-      v = f + t.by[y] * v;
-    }
-    if (t.az[z] != 0.0f) {
-      float &v = nz_[mem_z(g, t, x, y, z)];
-      v = f + t.bz[z] * v;
+    sn[t.slot(j, k)] = an;
+    sf[t.slot(j, k)] = an + fv;
+    if (!near(sh, 0, x)) continue;
+    pv[k] = phi[f];
+    kv[k] = kk[f];
+    if (cstore && !near_z && !near(sh, 1, t.y0 + t.line[k]))
+      grad[f] += fv * cstore[t.shell(sh, k, x)];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    if (!t.ok(k)) continue;
+    const int x = t.x(j, k);
+    const float a = j.a[x];
+    if (a != 0.0f) {
+      const float v = j.b[x] * mv[k] - first_diff(sf + t.slot(j, k), 1) * j.ih;
+      mu[t.mem(j, k, x)] = v;
+      mv[k] = a * v;
     }
   }
-}
-
-__global__ void __launch_bounds__(kThreads)
-    k_cpml_mu(StepGrid g, CpmlTables t, Shell sh, const float *__restrict__ phi1,
-              const float *__restrict__ nx_, const float *__restrict__ ny_,
-              const float *__restrict__ nz_, float *mx, float *my, float *mz) {
-  Column c;
-  if (!c.init(sh, g)) return;
-  const bool zq = sh.zq[c.b];
-  const float ax = t.ax[c.x], bx = t.bx[c.x], ay = t.ay[c.y], by = t.by[c.y];
-  // D1 of (a nu + phi1); along z from a queue of a_z nu_z + phi1
-  auto fz = [&](int zz) {
-    if (zz < 0 || zz >= g.nz) return 0.0f;
-    const float f = phi1[(int64_t)zz * g.plane + c.pxy];
-    return stored_z(g, t, zz) ? t.az[zz] * nz_[mem_z(g, t, c.x, c.y, zz)] + f : f;
-  };
-  ZWin qf;
-  if (zq) qf.prime(fz, c.z0);
-  for (int z = c.z0; z < c.z1; ++z) {
-    const int64_t p = (int64_t)z * g.plane + c.pxy;
-    if (ax != 0.0f) {
-      const int64_t q = mem_x(g, t, c.x, c.y, z);
-      const float d = first_diff(Line{nx_, t.ax, q, 1, c.x, g.nx}) +
-                      first_diff(Line{phi1, nullptr, p, 1, c.x, g.nx});
-      mx[q] = bx * mx[q] - d * t.ihx;
-    }
-    if (ay != 0.0f) {
-      const int64_t q = mem_y(g, t, c.x, c.y, z);
-      const float d = first_diff(Line{ny_, t.ay, q, g.nx, c.y, g.ny}) +
-                      first_diff(Line{phi1, nullptr, p, g.pitch, c.y, g.ny});
-      my[q] = by * my[q] - d * t.ihy;
-    }
-    if (zq) {
-      const float az = t.az[z];
-      if (az != 0.0f) {
-        float &v = mz[mem_z(g, t, c.x, c.y, z)];
-        v = t.bz[z] * v - qf.d1() * t.ihz;
-      }
-      qf.advance(fz, z);
-    }
-  }
-}
-
-__global__ void __launch_bounds__(kThreads)
-    k_cpml_adjoint(StepGrid g, CpmlTables t, Shell sh, const float *__restrict__ nx_,
-                   const float *__restrict__ ny_, const float *__restrict__ nz_,
-                   const float *__restrict__ mx, const float *__restrict__ my,
-                   const float *__restrict__ mz, float *phi, const float *__restrict__ phi1,
-                   const float *__restrict__ cstore, float *grad) {
-  Column c;
-  if (!c.init(sh, g)) return;
-  const bool zq = sh.zq[c.b];
-  const bool nx = near(sh, 0, c.x), ny = near(sh, 1, c.y);
-  // along z: a_z nu_z (image planes above a free surface, for D2) and a_z mu_z
-  auto nuz = [&](int zz) {
-    int z2 = zz;
-    float sgn = 1.0f;
-    if (zz < g.zs) {
-      z2 = 2 * g.zs - zz;
-      sgn = -1.0f;
-    }
-    return stored_z(g, t, z2) ? sgn * t.az[z2] * nz_[mem_z(g, t, c.x, c.y, z2)] : 0.0f;
-  };
-  auto muz = [&](int zz) {
-    return stored_z(g, t, zz) ? t.az[zz] * mz[mem_z(g, t, c.x, c.y, zz)] : 0.0f;
-  };
-  ZWin qn, qm;
-  if (zq) {
-    qn.prime(nuz, c.z0);
-    qm.prime(muz, c.z0);
-  }
-  for (int z = c.z0; z < c.z1; ++z) {
-    const int64_t p = (int64_t)z * g.plane + c.pxy;
-    float corr = 0.0f;
-    if (nx) {
-      const int64_t q = mem_x(g, t, c.x, c.y, z);
-      corr += second_diff(Line{nx_, t.ax, q, 1, c.x, g.nx}) * g.cx -
-              first_diff(Line{mx, t.ax, q, 1, c.x, g.nx}) * t.ihx;
-    }
-    if (ny) {
-      const int64_t q = mem_y(g, t, c.x, c.y, z);
-      corr += second_diff(Line{ny_, t.ay, q, g.nx, c.y, g.ny}) * g.cy -
-              first_diff(Line{my, t.ay, q, g.nx, c.y, g.ny}) * t.ihy;
-    }
-    if (zq) {
-      if (near(sh, 2, z)) corr += qn.d2() * g.cz - qm.d1() * t.ihz;
-      qn.advance(nuz, z);
-      qm.advance(muz, z);
-    }
-    if (z > g.zs) phi[p] += g.k[p] * corr;
-    if (cstore) grad[p] += phi1[p] * cstore[c.q(sh, z)];
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < N; ++k)
+    if (t.ok(k)) sf[t.slot(j, k)] = mv[k];  // a mu, zero off the layer
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    const int x = t.x(j, k);
+    if (!t.ok(k) || !near(sh, 0, x) || t.z <= g.zs) continue;
+    const float d2 = second_diff(sn + t.slot(j, k), 1);
+    phi[t.field(g, k, x)] =
+        pv[k] + kv[k] * (d2 * j.c2 - first_diff(sf + t.slot(j, k), 1) * j.ih);
   }
 }
 
@@ -437,63 +503,137 @@ __global__ void k_record(const float *__restrict__ field, const int64_t *__restr
   if (r < nrec) seis_tm[(int64_t)n * nrec + r] = scale[r] * field[idx[r]];
 }
 
-unsigned blocks_for(const Shell &sh) {
-  const int64_t total = sh.start[sh.nbox];
-  const int64_t b = (total + kThreads - 1) / kThreads;
-  return (unsigned)(b < 1 ? 1 : (b > 16384 ? 16384 : b));
+AxisJob axis_job(const StepGrid &g, const CpmlTables &t, const Shell &sh, int d) {
+  AxisJob j{};
+  const int n = d == 0 ? g.nx : d == 1 ? g.ny : g.nz;
+  j.a = d == 0 ? t.ax : d == 1 ? t.ay : t.az;
+  j.b = d == 0 ? t.bx : d == 1 ? t.by : t.bz;
+  j.ih = d == 0 ? t.ihx : d == 1 ? t.ihy : t.ihz;
+  j.c2 = d == 0 ? g.cx : d == 1 ? g.cy : g.cz;
+  j.n = n, j.half = t.half[d], j.len = t.len[d];
+  if (t.len[d] == n) {  // the two ends' slabs meet: the whole axis
+    j.nseg = 1, j.L = n;
+  } else {
+    j.L = n - 1 - sh.hi[d];
+    j.nseg = sh.lo[d] > 0 ? 2 : 1;
+    j.s0[0] = j.nseg == 2 ? 0 : n - j.L;
+    j.s0[1] = n - j.L;
+  }
+  return j;
 }
 
-unsigned columns_for(const Shell &sh) { return (unsigned)sh.bstart[sh.nbox]; }
+// Calls f(threads, tile width T, cells per thread R, image) with the smallest
+// tile that takes a segment of L cells: 64 lines up to 96 cells (borders to 92),
+// fewer lines for longer ones, so that a tile's LDS stays below 64 KB and a
+// thread's cells in registers.  The last covers every border whose volumes fit
+// the device (each axis is longer than twice the border).  Whole axes with
+// image cells are short (under 2 B + 16 cells) and rare: fewer shapes.
+template <class F>
+bool plane_shape(int L, bool img, F f) {
+#define WFD_PLANE(NT, T, R, IMG)                                                      \
+  if (L <= NT / T * R) {                                                              \
+    f(std::integral_constant<int, NT>{}, std::integral_constant<int, T>{},            \
+      std::integral_constant<int, R>{}, std::integral_constant<bool, IMG>{});         \
+    return true;                                                                      \
+  }
+  if (img) {
+    WFD_PLANE(512, 64, 6, true)
+    WFD_PLANE(1024, 64, 6, true)
+    WFD_PLANE(1024, 2, 6, true)
+    return false;
+  }
+  WFD_PLANE(256, 64, 3, false)
+  WFD_PLANE(256, 64, 5, false)
+  WFD_PLANE(256, 64, 6, false)
+  WFD_PLANE(512, 64, 5, false)
+  WFD_PLANE(512, 64, 6, false)
+  WFD_PLANE(1024, 64, 6, false)
+  WFD_PLANE(1024, 16, 6, false)
+  WFD_PLANE(1024, 2, 6, false)
+#undef WFD_PLANE
+  return false;
+}
+
+// Calls f(threads) for an x job, three elements per thread: as many rows of a
+// plane as 256 threads take, or one row by 1024 threads (segments up to 3072
+// cells, as above).
+template <class F>
+bool row_shape(const StepGrid &g, AxisJob &j, F f) {
+  const int P = j.nseg * j.L;
+  j.rows = std::max(1, std::min(g.ny, 3 * 256 / P));
+  j.tiles = (g.ny + j.rows - 1) / j.rows;
+  if (P <= 3 * 256) f(std::integral_constant<int, 256>{});
+  else if (P <= 3 * 1024) f(std::integral_constant<int, 1024>{});
+  else return false;
+  return true;
+}
+
+bool image_axis(const StepGrid &g, const AxisJob &j, int axis) {
+  return axis == 2 && j.nseg == 1 && j.L == j.n && g.zs != kNoSurface;
+}
 
 }  // namespace
 
-hipError_t launch_cpml_psi(const StepGrid &g, const CpmlTables &t, const Shell &sh,
-                           const float *cur, float *psi_x, float *psi_y, float *psi_z,
-                           hipStream_t stream) {
-  if (sh.start[sh.nbox] == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_cpml_psi, dim3(columns_for(sh)), dim3(kThreads), 0, stream, g, t, sh, cur,
-                     psi_x, psi_y, psi_z);
-  return hipGetLastError();
-}
-
-hipError_t launch_cpml_zeta(const StepGrid &g, const CpmlTables &t, const Shell &sh,
-                            const float *cur, const float *psi_x, const float *psi_y,
-                            const float *psi_z, float *zeta_x, float *zeta_y, float *zeta_z,
-                            float *out, float *cstore, hipStream_t stream) {
-  if (sh.start[sh.nbox] == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_cpml_zeta, dim3(columns_for(sh)), dim3(kThreads), 0, stream, g, t, sh, cur,
-                     psi_x, psi_y, psi_z, zeta_x, zeta_y, zeta_z, out, cstore);
-  return hipGetLastError();
-}
-
-hipError_t launch_cpml_nu(const StepGrid &g, const CpmlTables &t, const Shell &sh,
-                          const float *phi1, float *nu_x, float *nu_y, float *nu_z,
-                          hipStream_t stream) {
-  if (sh.start[sh.nbox] == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_cpml_nu, dim3(blocks_for(sh)), dim3(kThreads), 0, stream, g, t, sh, phi1,
-                     nu_x, nu_y, nu_z);
-  return hipGetLastError();
-}
-
-hipError_t launch_cpml_mu(const StepGrid &g, const CpmlTables &t, const Shell &sh,
-                          const float *phi1, const float *nu_x, const float *nu_y,
-                          const float *nu_z, float *mu_x, float *mu_y, float *mu_z,
-                          hipStream_t stream) {
-  if (sh.start[sh.nbox] == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_cpml_mu, dim3(columns_for(sh)), dim3(kThreads), 0, stream, g, t, sh, phi1,
-                     nu_x, nu_y, nu_z, mu_x, mu_y, mu_z);
-  return hipGetLastError();
+hipError_t launch_cpml_forward(const StepGrid &g, const CpmlTables &t, const Shell &sh,
+                               const float *cur, float *const mem[6], float *out, float *cstore,
+                               bool keep, hipStream_t stream) {
+  if (sh.points == 0) return hipSuccess;
+  AxisJob j = axis_job(g, t, sh, 0);
+  bool fits = row_shape(g, j, [&](auto nt) {
+    const size_t lds = 2 * sizeof(float) * (size_t)j.rows * j.nseg * (j.L + 8);
+    constexpr int NT = decltype(nt)::value;
+    hipLaunchKernelGGL((k_cpml_forward_x<NT, 3>), dim3((unsigned)(j.tiles * g.nz)), dim3(NT), lds, stream, g, j, sh, cur, mem[0], mem[3], out, cstore,
+                       keep ? 1 : 0);
+  });
+  auto plane = [&](auto ax) {
+    constexpr int A = decltype(ax)::value;
+    AxisJob p = axis_job(g, t, sh, A);
+    fits = fits && plane_shape(p.L, image_axis(g, p, A), [&](auto nt, auto t_, auto r, auto img) {
+      constexpr int NT = decltype(nt)::value, T = decltype(t_)::value, R = decltype(r)::value;
+      constexpr bool IMG = decltype(img)::value;
+      if constexpr (A == 2 || !IMG) {
+        p.tiles = (g.nx + T - 1) / T;
+        const unsigned blocks = (unsigned)(p.tiles * (A == 1 ? g.nz : g.ny) * p.nseg);
+        hipLaunchKernelGGL(
+            (k_cpml_forward<A, NT, T, R, IMG>), dim3(blocks), dim3(NT), 0, stream, g, p, sh, cur, mem[A], mem[3 + A], out, cstore,
+            keep ? 1 : 0);
+      }
+    });
+  };
+  plane(std::integral_constant<int, 1>{});
+  plane(std::integral_constant<int, 2>{});
+  return fits ? hipGetLastError() : hipErrorInvalidValue;
 }
 
 hipError_t launch_cpml_adjoint(const StepGrid &g, const CpmlTables &t, const Shell &sh,
-                               const float *nu_x, const float *nu_y, const float *nu_z,
-                               const float *mu_x, const float *mu_y, const float *mu_z,
-                               float *phi, const float *phi1, const float *cstore, float *grad,
-                               hipStream_t stream) {
-  if (sh.start[sh.nbox] == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_cpml_adjoint, dim3(columns_for(sh)), dim3(kThreads), 0, stream, g, t, sh,
-                     nu_x, nu_y, nu_z, mu_x, mu_y, mu_z, phi, phi1, cstore, grad);
-  return hipGetLastError();
+                               const float *phi1, float *const mem[6], float *phi,
+                               const float *cstore, float *grad, hipStream_t stream) {
+  if (sh.points == 0) return hipSuccess;
+  AxisJob j = axis_job(g, t, sh, 0);
+  bool fits = row_shape(g, j, [&](auto nt) {
+    const size_t lds = 2 * sizeof(float) * (size_t)j.rows * j.nseg * (j.L + 8);
+    constexpr int NT = decltype(nt)::value;
+    hipLaunchKernelGGL((k_cpml_adjoint_x<NT, 3>), dim3((unsigned)(j.tiles * g.nz)), dim3(NT), lds, stream, g, j, sh, phi1, mem[3], mem[0], phi, cstore,
+                       grad);
+  });
+  auto plane = [&](auto ax) {
+    constexpr int A = decltype(ax)::value;
+    AxisJob p = axis_job(g, t, sh, A);
+    fits = fits && plane_shape(p.L, image_axis(g, p, A), [&](auto nt, auto t_, auto r, auto img) {
+      constexpr int NT = decltype(nt)::value, T = decltype(t_)::value, R = decltype(r)::value;
+      constexpr bool IMG = decltype(img)::value;
+      if constexpr (A == 2 || !IMG) {
+        p.tiles = (g.nx + T - 1) / T;
+        const unsigned blocks = (unsigned)(p.tiles * (A == 1 ? g.nz : g.ny) * p.nseg);
+        hipLaunchKernelGGL(
+            (k_cpml_adjoint<A, NT, T, R, IMG>), dim3(blocks), dim3(NT), 0, stream, g, p, sh, phi1, mem[3 + A], mem[A], phi,
+            cstore, grad);
+      }
+    });
+  };
+  plane(std::integral_constant<int, 1>{});
+  plane(std::integral_constant<int, 2>{});
+  return fits ? hipGetLastError() : hipErrorInvalidValue;
 }
 
 hipError_t launch_record(const float *field, const int64_t *idx, const float *scale, int nrec,

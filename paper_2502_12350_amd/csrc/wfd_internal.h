@@ -283,56 +283,37 @@ inline int64_t cpml_mem_len(int d, int Nx, int Ny, int Nz, int B) {
                   : (int64_t)cpml_slab_len(Nz, B) * Ny * Nx;
 }
 // The points the layer's terms reach: the padded grid minus the inner box
-// more than 4 cells from every layer, as up to 6 boxes [lo, hi) in (z, y, x).
-// Point q of the shell lies in the box b with start[b] <= q < start[b + 1],
-// at offset q - start[b] in x-fastest order, then the box's thinner of z and
-// y (so the z or y neighbours of a row are a few rows away and stay in L2);
-// every box holds fewer than 2^31 points.  lo/hi are the inner box (inclusive) per axis x, y, z: a point
-// outside [lo, hi] along an axis is within reach of that axis' layer.
+// more than 4 cells from every layer, as up to 6 boxes (below z, above z,
+// below y, above y, below x, above x; id maps each to its box), or one box,
+// the whole grid, where the inner box is empty.  The correction C of a step is
+// stored box after box in x-fastest order.  lo/hi are the cells that are not
+// within reach of an axis' layer (inclusive) per axis x, y, z.
 constexpr int kShellBoxes = 6;
 struct Shell {
   int nbox;
-  int z0[kShellBoxes], z1[kShellBoxes], y0[kShellBoxes], y1[kShellBoxes];
-  int x0[kShellBoxes], x1[kShellBoxes];
-  int64_t start[kShellBoxes + 1];
-  int zfirst[kShellBoxes];  // 1: order x, z, y (z before y), for boxes thin in z
+  int z0[kShellBoxes], y0[kShellBoxes], x0[kShellBoxes], ny[kShellBoxes], nx[kShellBoxes];
+  int64_t start[kShellBoxes];
+  int id[kShellBoxes];
+  int64_t points;
   int lo[3], hi[3];
-  // Column marching: a block of 64 x 4 threads owns one (x, y) tile of a box
-  // and marches a chunk of cz planes; tx, ty, nch tile counts per box, bstart
-  // the first block of each box, zq whether the box reaches z-derivative terms
-  // (then each thread keeps nine-plane queues along z and the chunks are long,
-  // kShellChunkZ; other boxes take short chunks, kShellChunk, for parallelism).
-  int tx[kShellBoxes], ty[kShellBoxes], nch[kShellBoxes], zq[kShellBoxes], cz[kShellBoxes];
-  int64_t bstart[kShellBoxes + 1];
 };
-constexpr int kShellTileX = 64, kShellTileY = 4, kShellChunkZ = 16, kShellChunk = 8;
-// Forward: psi_d = b psi_d + a D1_d w (cur) on the layer.
-hipError_t launch_cpml_psi(const StepGrid &g, const CpmlTables &t, const Shell &sh,
-                           const float *cur, float *psi_x, float *psi_y, float *psi_z,
-                           hipStream_t stream);
-// Forward: zeta_d = b zeta_d + a (D2_d w + D1_d psi_d) on the layer; C = sum_d
-// (D1_d psi_d + zeta_d); out += k C below the free surface; C to cstore[q]
-// when cstore is given.
-hipError_t launch_cpml_zeta(const StepGrid &g, const CpmlTables &t, const Shell &sh,
-                            const float *cur, const float *psi_x, const float *psi_y,
-                            const float *psi_z, float *zeta_x, float *zeta_y, float *zeta_z,
-                            float *out, float *cstore, hipStream_t stream);
-// Adjoint: nu_d = phi1 + b nu_d on the layer.
-hipError_t launch_cpml_nu(const StepGrid &g, const CpmlTables &t, const Shell &sh,
-                          const float *phi1, float *nu_x, float *nu_y, float *nu_z,
-                          hipStream_t stream);
-// Adjoint: mu_d = b mu_d - D1_d (a nu_d + phi1) on the layer.
-hipError_t launch_cpml_mu(const StepGrid &g, const CpmlTables &t, const Shell &sh,
-                          const float *phi1, const float *nu_x, const float *nu_y,
-                          const float *nu_z, float *mu_x, float *mu_y, float *mu_z,
-                          hipStream_t stream);
-// Adjoint: phi += k sum_d [D2_d (a nu_d) - D1_d (a mu_d)] below the free
-// surface; g += phi1 C (C from cstore) when cstore is given.
+// The layer's share of a forward step, after the step kernel wrote out from
+// cur.  mem: psi_x, psi_y, psi_z, zeta_x, zeta_y, zeta_z.  psi_d = b psi_d + a
+// D1_d w (w = cur) and zeta_d = b zeta_d + a (D2_d w + D1_d psi_d) on the
+// layer; C = sum_d (D1_d psi_d + zeta_d); out += k C below the free surface
+// (out nullptr: not).  cstore (sh.points floats) holds C afterwards with keep,
+// else it is scratch.
+hipError_t launch_cpml_forward(const StepGrid &g, const CpmlTables &t, const Shell &sh,
+                               const float *cur, float *const mem[6], float *out, float *cstore,
+                               bool keep, hipStream_t stream);
+// The layer's share of an adjoint step, after the step kernel wrote phi from
+// phi1.  mem: mu_x, mu_y, mu_z, nu_x, nu_y, nu_z.  nu_d = phi1 + b nu_d and
+// mu_d = b mu_d - D1_d (a nu_d + phi1) on the layer; phi += k [D2_d (a nu_d) -
+// D1_d (a mu_d)] per axis below the free surface; grad += phi1 C (C from
+// cstore) when cstore is given.
 hipError_t launch_cpml_adjoint(const StepGrid &g, const CpmlTables &t, const Shell &sh,
-                               const float *nu_x, const float *nu_y, const float *nu_z,
-                               const float *mu_x, const float *mu_y, const float *mu_z,
-                               float *phi, const float *phi1, const float *cstore, float *grad,
-                               hipStream_t stream);
+                               const float *phi1, float *const mem[6], float *phi,
+                               const float *cstore, float *grad, hipStream_t stream);
 // seis_tm[n][r] = scale[r] field[idx[r]] (receivers read after the layer's
 // correction).
 hipError_t launch_record(const float *field, const int64_t *idx, const float *scale, int nrec,

@@ -207,3 +207,51 @@ def test_cpml_checkpointed_gradient_equals_full_storage_bitwise(nsnap, fs):
     assert torch.equal(sf, sr)
     assert torch.equal(gf, gr_)
     assert torch.equal(ilf, ilr)
+
+
+@pytest.mark.parametrize("n,N,fs", [
+    ((70, 18, 40), 8, False),    # 12-cell segments: 3 cells per thread, ragged second x tile
+    ((20, 33, 18), 16, False),   # 20 cells: 5 per thread
+    ((33, 20, 17), 20, True),    # 24 cells: 6 per thread, no layer above the surface
+    ((24, 17, 19), 32, False),   # 36 cells: 8 groups of 5
+    ((17, 18, 20), 43, False),   # 47 cells: 8 groups of 6, side rows of 94 elements
+    ((18, 17, 17), 50, False),   # 54 cells: 16 groups of 6
+    ((16, 12, 14), 45, False),   # slabs meet on every axis (whole axes of 102-106 cells)
+    ((16, 12, 14), 45, True),    # the same with the free surface's image cells
+    ((40, 30, 3), 8, True),      # a thin model: whole z axis within the layer's reach
+    ((5, 40, 30), 8, False),     # thin in x: every point within reach of an x layer
+])
+def test_cpml_tile_shapes_match_oracle(n, N, fs):
+    # every tile shape of the layer kernels, forward and adjoint; the source is
+    # next to a corner of the model so that the wave is in the layers within
+    # the 36 steps.  Tolerances are those of the cases above.
+    torch = gpu_or_skip()
+    from paper_2502_12350_amd import GridSpec, Propagator
+    nx, ny, nz = n
+    nt, h = 36, 10.0
+    vel = seisgen.layered_model(7, n, 0.05)
+    rho = seisgen.gardner_density(vel)
+    dt = 0.4 * h / float(vel.max())
+    t = np.arange(nt) * dt
+    a = (np.pi * 40.0 * (t - 0.02)) ** 2
+    wav = ((1 - 2 * a) * np.exp(-a)).astype(np.float32)
+    src = [2 * h, 3 * h, min(3, nz - 1) * h]
+    rec = np.array([[h * i, h * j, h * k] for i in (0, nx // 2, nx - 1)
+                    for j in (0, ny - 1) for k in (1, nz - 1)])
+    g = oracle.Grid(nx, ny, nz, h, h, h, border=N, dt=dt, nt=nt)
+    g.free_surface = fs
+    say(f"[cpml tiles] model {n} border {N} free surface {fs}")
+    dobs = (0.5 * ocpml.forward(g, vel, rho, wav, src, rec, vmax=VMAX, fpeak=FPEAK).seis)
+    dobs = dobs.astype(np.float32)
+    ref = ocpml.gradient(g, vel, rho, wav, src, rec, dobs, vmax=VMAX, fpeak=FPEAK)
+    P = Propagator(0)
+    P.set_model(GridSpec(nx, ny, nz, h, h, h, border=N, dt=dt, nt=nt, cpml=True, fpeak=FPEAK,
+                         cpml_vmax=VMAX, free_surface=fs), torch.from_numpy(vel).cuda(),
+                torch.from_numpy(rho).cuda())
+    J, gr, seis = P.gradient(torch.from_numpy(wav).cuda(), src, rec,
+                             torch.from_numpy(dobs).cuda(), ckpt="full", seis=True)
+    torch.cuda.synchronize()
+    es, eg = rel_l2(seis.cpu().numpy(), ref.seis), rel_l2(gr.cpu().numpy(), ref.grad)
+    say(f"  seismograms rel-L2 {es:.2e}, gradient {eg:.2e}")
+    assert es <= SEIS_TOL and eg <= GRAD_TOL
+    assert abs(float(J.item()) - ref.misfit) <= SEIS_TOL * ref.misfit
