@@ -115,7 +115,8 @@ struct wfd_batch {
   std::vector<int> nrec;
   wfd::WindowStep *d_wins[2] = {nullptr, nullptr};  // device descriptors per step parity
   std::vector<wfd::WindowStep> h_wins[2];
-  int nblocks = 0, variant = 0, nt = 0;
+  int nblocks = 0, nt = 0;
+  wfd::StepPlan plan;
   bool vd = false;
   bool fs = false;  // some shot has a free surface
   hipStream_t stream = nullptr;
@@ -888,12 +889,16 @@ wfd_status forward_core(wfd_ctx *c, const float *wavelet, const double src_xyz[3
     for (int i = 0; i < 6; ++i)
       if ((s = zero(c, w.mem[i], mem_len(c, i))) != WFD_OK) return s;
   float *cur = w.W1, *prev = w.W2;
+  const wfd::StepGrid *const pg = &g;
+  const wfd::Tuning *const pt = &c->tuning;
+  wfd::TileMap map;
+  const wfd::StepPlan plan = wfd::plan_forward(&pg, &pt, 1, false, &map);
   for (int n = 0; n < c->grid.nt; ++n) {
     {
       Timed t(c, WFD_K_FORWARD);
-      HIP_TRY(wfd::launch_forward_step(g, cur, prev, prev, src, n,
+      HIP_TRY(wfd::launch_forward_step(plan, map, g, cur, prev, prev, src, n,
                                        (nrec > 0 && !c->cpml) ? &rt : nullptr, w.rec_scale,
-                                       w.seis_tm, c->tuning, c->stream));
+                                       w.seis_tm, c->stream));
     }
     if (c->cpml && (s = cpml_forward_terms(c, g, w, cur, prev, nullptr, nrec, n)) != WFD_OK)
       return s;
@@ -1016,6 +1021,11 @@ wfd_status wfd_gradient_ex(wfd_ctx *c, const float *wavelet, const double src_xy
   for (float *p : {w.W1, w.W2, w.P1, w.P2, w.g})
     if ((s = zero(c, p, c->vol)) != WFD_OK) return s;
 
+  const wfd::StepGrid *const pg = &g;
+  const wfd::Tuning *const pt = &c->tuning;
+  wfd::TileMap fmap, amap;
+  const wfd::StepPlan fplan = wfd::plan_forward(&pg, &pt, 1, true, &fmap);
+  const wfd::StepPlan aplan = wfd::plan_adjoint(&pg, &pt, 1, illum != nullptr, &amap);
   // adjoint state: psi^{m+1} = A1, psi^{m+2} = A2 (psi^m overwrites A2)
   float *A1 = w.P1, *A2 = w.P2;
   bool residual_done = false;
@@ -1042,7 +1052,7 @@ wfd_status wfd_gradient_ex(wfd_ctx *c, const float *wavelet, const double src_xy
   auto adjoint = [&](int m, const float *wm, const float *corr_m = nullptr) -> wfd_status {
     {
       Timed t(c, WFD_K_ADJOINT);
-      HIP_TRY(wfd::launch_adjoint_step(c->tuning, g, A1, A2, A2, rt, w.res_tm, m, wm, w.g, il,
+      HIP_TRY(wfd::launch_adjoint_step(aplan, amap, g, A1, A2, A2, rt, w.res_tm, m, wm, w.g, il,
                                        c->stream));
     }
     if (c->cpml && (s = cpml_adjoint_terms(c, g, w, A1, A2, m, corr_m)) != WFD_OK) return s;
@@ -1058,9 +1068,9 @@ wfd_status wfd_gradient_ex(wfd_ctx *c, const float *wavelet, const double src_xy
   auto fwd = [&](const float *cur, const float *prev, float *out, int n, bool rec) -> wfd_status {
     {
       Timed t(c, WFD_K_FORWARD);
-      HIP_TRY(wfd::launch_forward_step(g, cur, prev, out, src, n,
+      HIP_TRY(wfd::launch_forward_step(fplan, fmap, g, cur, prev, out, src, n,
                                        (rec && nrec > 0 && !c->cpml) ? &rt : nullptr, w.rec_scale,
-                                       w.seis_tm, c->tuning, c->stream));
+                                       w.seis_tm, c->stream));
     }
     if (c->cpml) {  // full storage keeps every step's C; checkpointing the latest
       float *cst = w.cstore ? w.cstore + (size_t)n * (size_t)c->shell.points
@@ -1337,6 +1347,7 @@ wfd_status wfd_autotune(wfd_ctx *c, int32_t steps, void *work, size_t work_bytes
     return fail(WFD_E_HIP, "hipEventCreate failed");
   }
   const int rounds_opts[] = {0, 2, 3, 4, 6, 8};
+  const wfd::StepGrid *const pg = &g;
   wfd::Tuning bt = c->tuning;
   float best_f = 3.0e38f, best_a = 3.0e38f;
   hipError_t err = hipSuccess;
@@ -1347,9 +1358,12 @@ wfd_status wfd_autotune(wfd_ctx *c, int32_t steps, void *work, size_t work_bytes
       tu.rounds = r;
       float *cur = w.W1, *prev = w.W2;
       float ms = 0.0f;
+      const wfd::Tuning *const pt = &tu;
+      wfd::TileMap map;
+      const wfd::StepPlan plan = wfd::plan_forward(&pg, &pt, 1, false, &map);
       err = time_steps(c, steps, e0, e1, [&] {
-        hipError_t e = wfd::launch_forward_step(g, cur, prev, prev, none_src, 0, nullptr, nullptr,
-                                                nullptr, tu, c->stream);
+        hipError_t e = wfd::launch_forward_step(plan, map, g, cur, prev, prev, none_src, 0, nullptr,
+                                                nullptr, nullptr, c->stream);
         std::swap(cur, prev);
         return e;
       }, &ms);
@@ -1367,8 +1381,11 @@ wfd_status wfd_autotune(wfd_ctx *c, int32_t steps, void *work, size_t work_bytes
       tu.adj_rounds = r;
       float *a1 = w.P1, *a2 = w.P2;
       float ms = 0.0f;
+      const wfd::Tuning *const pt = &tu;
+      wfd::TileMap map;
+      const wfd::StepPlan plan = wfd::plan_adjoint(&pg, &pt, 1, false, &map);
       err = time_steps(c, steps, e0, e1, [&] {
-        hipError_t e = wfd::launch_adjoint_step(tu, g, a1, a2, a2, rt, w.seis_tm, 1, w.W1, w.g,
+        hipError_t e = wfd::launch_adjoint_step(plan, map, g, a1, a2, a2, rt, w.seis_tm, 1, w.W1, w.g,
                                                 wfd::IllumOut{}, c->stream);
         std::swap(a1, a2);
         return e;
@@ -1425,7 +1442,15 @@ wfd_status wfd_batch_create(wfd_batch **out, int32_t nshot, wfd_ctx *const *ctxs
   b->nt = c0->grid.nt;
   b->vd = c0->vd;
   for (int i = 0; i < nshot; ++i) b->fs = b->fs || ctxs[i]->grid.free_surface != 0;
-  b->variant = c0->tuning.variant;
+  std::vector<wfd::StepGrid> grids;
+  std::vector<wfd::TileMap> maps((size_t)nshot);
+  for (int i = 0; i < nshot; ++i) grids.push_back(step_grid(ctxs[i]));
+  {
+    std::vector<const wfd::StepGrid *> pg;
+    std::vector<const wfd::Tuning *> pt;
+    for (int i = 0; i < nshot; ++i) pg.push_back(&grids[(size_t)i]), pt.push_back(&ctxs[i]->tuning);
+    b->plan = wfd::plan_forward(pg.data(), pt.data(), nshot, false, maps.data());
+  }
   b->h_wins[0].resize(nshot);
   b->h_wins[1].resize(nshot);
   int offset = 0;
@@ -1448,18 +1473,10 @@ wfd_status wfd_batch_create(wfd_batch **out, int32_t nshot, wfd_ctx *const *ctxs
       b->d_wins[0] = w.wins;
       b->d_wins[1] = w.wins + kMaxBatch;
     }
-    // Each window keeps the tile map of its own launch (z chunks sized for the
-    // whole device, at least 16 planes deep when several shots share the
-    // launch, 4 for a single shot); one launch then has a single tail instead
-    // of one per shot.  Measured on 24 windows of 173-300 cells: sizing the
-    // chunks for a 1/nshot share of the device instead makes full-depth
-    // columns, whose last round leaves the device idle longer.
-    wfd::Tuning tu = c->tuning;
-    tu.variant = b->variant;  // one tile shape per launch
     wfd::WindowStep d{};
-    d.g = step_grid(c);
-    const int nb = wfd::forward_tile_map(
-        d.g, tu, nshot == 1 ? wfd::kSingleMinZc : wfd::kBatchMinZc, &d.map);
+    d.g = grids[(size_t)i];
+    d.map = maps[(size_t)i];
+    const int nb = d.map.nblocks;
     d.src = wfd::Source{src_idx, &w.scale->sigma, wavelet};
     d.rec = rec_table(w, nrec[i]);
     d.rec_scale = w.rec_scale;
@@ -1509,7 +1526,7 @@ wfd_status batch_enqueue(wfd_batch *b) {
   }
   for (int n = 0; n < b->nt; ++n) {
     Timed t(c0, WFD_K_FORWARD);
-    HIP_TRY(wfd::launch_forward_multi(b->d_wins[n & 1], nwin, b->nblocks, n, b->variant, b->vd,
+    HIP_TRY(wfd::launch_forward_multi(b->plan, b->d_wins[n & 1], nwin, b->nblocks, n, b->vd,
                                       b->fs, b->stream));
   }
   for (int i = 0; i < nwin; ++i)
@@ -1572,7 +1589,8 @@ struct wfd_gbatch {
   std::vector<float *> grad;
   std::vector<int32_t> plan;
   wfd::GradWindow *d_wins = nullptr;  // in shot 0's workspace
-  int fblocks = 0, ablocks = 0, variant = 0, adj_variant = 0, nt = 0, nsnap = 0;
+  int fblocks = 0, ablocks = 0, nt = 0, nsnap = 0;
+  wfd::StepPlan fplan, aplan;
   bool vd = false, fs = false, illum = false;
   hipStream_t stream = nullptr;
   hipGraph_t graph = nullptr;
@@ -1621,8 +1639,16 @@ wfd_status wfd_gbatch_create(wfd_gbatch **out, int32_t nshot, wfd_ctx *const *ct
   b->nsnap = n_snapshots;
   b->vd = c0->vd;
   b->illum = illum;
-  b->variant = c0->tuning.variant;
-  b->adj_variant = c0->tuning.adj_variant;
+  std::vector<wfd::StepGrid> grids;
+  std::vector<wfd::TileMap> fmaps((size_t)nshot), amaps((size_t)nshot);
+  for (int i = 0; i < nshot; ++i) grids.push_back(step_grid(ctxs[i]));
+  {
+    std::vector<const wfd::StepGrid *> pg;
+    std::vector<const wfd::Tuning *> pt;
+    for (int i = 0; i < nshot; ++i) pg.push_back(&grids[(size_t)i]), pt.push_back(&ctxs[i]->tuning);
+    b->fplan = wfd::plan_forward(pg.data(), pt.data(), nshot, true, fmaps.data());
+    b->aplan = wfd::plan_adjoint(pg.data(), pt.data(), nshot, illum, amaps.data());
+  }
   for (int i = 0; i < nshot; ++i) b->fs = b->fs || ctxs[i]->grid.free_surface != 0;
   int64_t nsteps = 0;
   wfd::build_checkpoint_plan(b->nt, n_snapshots, b->plan, nsteps);
@@ -1646,14 +1672,11 @@ wfd_status wfd_gbatch_create(wfd_gbatch **out, int32_t nshot, wfd_ctx *const *ct
       delete b;
       return s;
     }
-    wfd::Tuning tu = c->tuning;
-    tu.variant = b->variant;  // one tile shape per launch
-    tu.adj_variant = b->adj_variant;
     wfd::GradWindow &d = h[(size_t)i];
-    d.g = step_grid(c);
-    const int min_zc = nshot == 1 ? wfd::kSingleMinZc : wfd::kBatchMinZc;
-    const int nf = wfd::forward_tile_map(d.g, tu, min_zc, &d.fmap);
-    const int na = wfd::adjoint_tile_map(d.g, tu, illum, min_zc, &d.amap);
+    d.g = grids[(size_t)i];
+    d.fmap = fmaps[(size_t)i];
+    d.amap = amaps[(size_t)i];
+    const int nf = d.fmap.nblocks, na = d.amap.nblocks;
     d.src = wfd::Source{src_idx, &w.scale->sigma, wavelet};
     d.rec = rec_table(w, nrec[i]);
     d.rec_scale = w.rec_scale;
@@ -1756,8 +1779,8 @@ wfd_status gbatch_enqueue(wfd_gbatch *b) {
         if (o < 0) return fail(WFD_E_STATE, "checkpoint pool exhausted");
         {
           Timed t(c0, WFD_K_FORWARD);
-          HIP_TRY(wfd::launch_forward_pool(b->d_wins, nwin, b->fblocks, n, cur, prev, o,
-                                           n >= reached ? 1 : 0, b->variant, b->vd, b->fs, st));
+          HIP_TRY(wfd::launch_forward_pool(b->fplan, b->d_wins, nwin, b->fblocks, n, cur, prev,
+                                           o, n >= reached ? 1 : 0, b->vd, b->fs, st));
         }
         if (n >= reached) reached = n + 1;
         prev = cur;
@@ -1795,8 +1818,8 @@ wfd_status gbatch_enqueue(wfd_gbatch *b) {
       if (wk < 0) return fail(WFD_E_STATE, "checkpoint plan: state %d unavailable", a);
       {
         Timed t(c0, WFD_K_ADJOINT);
-        HIP_TRY(wfd::launch_adjoint_multi(b->d_wins, nwin, b->ablocks, a, parity, wk,
-                                          b->adj_variant, b->vd, b->illum, b->fs, st));
+        HIP_TRY(wfd::launch_adjoint_multi(b->aplan, b->d_wins, nwin, b->ablocks, a, parity,
+                                          wk, b->vd, b->illum, b->fs, st));
       }
       parity ^= 1;
     } else if (op == wfd::kFree) {

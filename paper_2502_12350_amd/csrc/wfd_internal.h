@@ -64,7 +64,7 @@ struct Source {
   const float *wavelet;
 };
 
-// How a step kernel's blocks cover a grid: 64-wide tiles of `ty` rows,
+// How a step kernel's blocks cover a grid: tiles_x x tiles_y column tiles,
 // z split into nchunks chunks of zc planes.
 struct TileMap {
   int tiles_x, tiles_y, nchunks, zc, nblocks;
@@ -77,7 +77,8 @@ struct TileMap {
 //   adjoint  0: 2x16x1 (64x32)       1: 2x8x1 (64x16, 2-plane halo delay)
 //            2: 2x4x1 (64x8)         3: 2x8x1 (64x16, halo one plane ahead)
 // and the number of rounds of resident blocks the z chunking aims for
-// (0 = chosen by the launch cost model).  Every shape computes bitwise the
+// (0 = chosen by the launch cost model; with variant 0 the planner may then
+// take another shape where that is faster).  Every shape computes bitwise the
 // same values.
 constexpr int kFwdVariants = 5, kAdjVariants = 4;
 struct Tuning {
@@ -129,45 +130,46 @@ struct GradWindow {
   int fblock_begin, fblock_end, ablock_begin, ablock_end;
 };
 
+// The kernel of a step launch: its tile shape and whether its single-use
+// loads and stores carry streaming hints.
+struct StepPlan {
+  int shape = 0;
+  bool stream = true;
+};
+
+// Shape and tile maps of a launch over n grids (one per shot; maps[n]), from
+// the grids and their contexts' tuning (one variant for all: the first's).
+// out_of_place: a forward step may write a third volume.
+StepPlan plan_forward(const StepGrid *const *grids, const Tuning *const *tu, int n,
+                      bool out_of_place, TileMap *maps);
+StepPlan plan_adjoint(const StepGrid *const *grids, const Tuning *const *tu, int n, bool illum,
+                      TileMap *maps);
+
 // Kernel launchers; all enqueue on `stream` and return the launch status.
-hipError_t launch_forward_step(const StepGrid &g, const float *cur, const float *prev, float *out,
-                               const Source &src, int n, const RecTable *rec,
-                               const float *rec_scale, float *seis_tm, const Tuning &tu,
+hipError_t launch_forward_step(const StepPlan &plan, const TileMap &map, const StepGrid &g,
+                               const float *cur, const float *prev, float *out, const Source &src,
+                               int n, const RecTable *rec, const float *rec_scale, float *seis_tm,
                                hipStream_t stream);
-
-// z chunks at least this deep: single launches, and batches of several shots
-// (whose windows fill the device together).
-constexpr int kSingleMinZc = 4, kBatchMinZc = 16;
-
-// Blocks of one window's share of a batched forward launch over g with tuning
-// tu, z chunks at least min_zc planes deep (and its tile map).
-int forward_tile_map(const StepGrid &g, const Tuning &tu, int min_zc, TileMap *map);
+hipError_t launch_adjoint_step(const StepPlan &plan, const TileMap &map, const StepGrid &g,
+                               const float *cur, const float *prev, float *out,
+                               const RecTable &rec, const float *res_tm, int m, const float *wm,
+                               float *grad, const IllumOut &illum, hipStream_t stream);
 
 // One step of every window in wins[0..nwin) (device array), nblocks blocks.
 // fs: some window has a free surface (selects the kernels with image loads).
-hipError_t launch_forward_multi(const WindowStep *wins, int nwin, int nblocks, int n, int variant,
-                                bool vd, bool fs, hipStream_t stream);
-
-hipError_t launch_adjoint_step(const Tuning &tu, const StepGrid &g, const float *cur,
-                               const float *prev, float *out,
-                               const RecTable &rec, const float *res_tm, int m,
-                               const float *wm, float *grad, const IllumOut &illum,
-                               hipStream_t stream);
-
-// Blocks of one window's share of a batched adjoint launch over g with
-// tuning tu, z chunks at least min_zc planes deep (and its tile map).
-int adjoint_tile_map(const StepGrid &g, const Tuning &tu, bool illum, int min_zc, TileMap *map);
+hipError_t launch_forward_multi(const StepPlan &plan, const WindowStep *wins, int nwin,
+                                int nblocks, int n, bool vd, bool fs, hipStream_t stream);
 
 // Batched gradient: one forward step of every window (pool buffers cur_k,
 // prev_k -> out_k; receivers recorded when record != 0), and one adjoint step
 // of every window (psi^{m+1} in P1 for parity 0 else P2; w^m = pool buffer
-// wm_k).  variant / adj_variant: the tile shapes of the windows' maps.
-hipError_t launch_forward_pool(const GradWindow *wins, int nwin, int nblocks, int n, int cur_k,
-                               int prev_k, int out_k, int record, int variant, bool vd, bool fs,
-                               hipStream_t stream);
-hipError_t launch_adjoint_multi(const GradWindow *wins, int nwin, int nblocks, int m, int parity,
-                                int wm_k, int adj_variant, bool vd, bool illum, bool fs,
-                                hipStream_t stream);
+// wm_k).
+hipError_t launch_forward_pool(const StepPlan &plan, const GradWindow *wins, int nwin, int nblocks,
+                               int n, int cur_k, int prev_k, int out_k, int record, bool vd,
+                               bool fs, hipStream_t stream);
+hipError_t launch_adjoint_multi(const StepPlan &plan, const GradWindow *wins, int nwin,
+                                int nblocks, int m, int parity, int wm_k, bool vd, bool illum,
+                                bool fs, hipStream_t stream);
 
 // Model preparation.
 hipError_t launch_precompute_k(const float *vel, int mnx, int mny, int mnz, int border, double dt,

@@ -18,8 +18,8 @@
 #include <algorithm>
 #include <climits>
 #include <cmath>
-#include <cstdlib>
 #include <type_traits>
+#include <vector>
 
 #include "wfd_internal.h"
 
@@ -32,8 +32,6 @@ constexpr float W2 = -1.0f / 5.0f;
 constexpr float W3 = 8.0f / 315.0f;
 constexpr float W4 = -1.0f / 560.0f;
 
-constexpr int WAVE = 64;  // lanes per wavefront = width of one column group
-
 // Calls f(integral_constant<int, 0>), ..., f(integral_constant<int, N - 1>):
 // a compile-time index for register-array access in unrolled loops.
 template <int N, class F>
@@ -44,12 +42,14 @@ __device__ __forceinline__ void static_for(F &&f) {
   }
 }
 
-// A tile is NW wavefronts; each thread owns NI column groups of RY rows.
-template <int RY, int NW, int NI>
+// A tile is NG row groups of XW lanes (64: a row group is a wavefront; 32: half
+// of one); each thread owns NI column groups of RY rows.
+template <int RY_, int NG_, int NI_, int XW_>
 struct Tile {
-  static constexpr int NTHREADS = WAVE * NW;
-  static constexpr int TX = WAVE * NI;
-  static constexpr int TY = NW * RY;
+  static constexpr int RY = RY_, NG = NG_, NI = NI_, XW = XW_;
+  static constexpr int NTHREADS = XW * NG;
+  static constexpr int TX = XW * NI;
+  static constexpr int TY = NG * RY;
   static constexpr int NP = RY * NI;  // points per thread: p = j * NI + i
   static constexpr int LX = TX + 8;
   static constexpr int LY = TY + 8;
@@ -72,11 +72,11 @@ __device__ __forceinline__ void tile_of(const TileMap &m, int b, int &tx, int &t
 }
 
 // Halo element h of a tile plane: global (gx, gy) and its LDS row / column.
-template <int RY, int NW, int NI, int K>
+template <class T, int K>
 __device__ __forceinline__ void halo_slot(int h, int x0, int y0, int &gx, int &gy, int &lrow,
                                           int &lcol) {
-  constexpr int TX = Tile<RY, NW, NI>::TX;
-  constexpr int TY = Tile<RY, NW, NI>::TY;
+  constexpr int TX = T::TX;
+  constexpr int TY = T::TY;
   if (h < 8 * TX) {  // four rows above and four below the tile
     const int r = h / TX, col = h % TX;
     gx = x0 + col;
@@ -105,9 +105,15 @@ __device__ __forceinline__ void halo_slot(int h, int x0, int y0, int &gx, int &g
 
 // Single-use streams (previous state, coefficients, gradient) bypass the
 // cache's normal retention so that L2 keeps the stenciled planes.
+template <bool NT>
+__device__ __forceinline__ float ld_once(const float *p) {
+  if constexpr (NT) return __builtin_nontemporal_load(p);
+  return *p;
+}
+template <bool NT>
 __device__ __forceinline__ float ld_stream(const float *f, const StepGrid &g, int z, uint32_t o,
                                            bool ok) {
-  return ok ? __builtin_nontemporal_load(f + (int64_t)z * g.plane + o) : 0.0f;
+  return ok ? ld_once<NT>(f + (int64_t)z * g.plane + o) : 0.0f;
 }
 // The adjoint's form: a lane outside the grid (or a plane past the chunk)
 // reads the field's first element and drops the value instead of skipping
@@ -115,9 +121,10 @@ __device__ __forceinline__ float ld_stream(const float *f, const StepGrid &g, in
 // read a plane ahead this took the 576^3 adjoint step from 1218 to 1158 us;
 // the same changes made the forward step slower (688 -> 713 us), so it keeps
 // the branches.
+template <bool NT>
 __device__ __forceinline__ float ld_stream_nb(const float *f, const StepGrid &g, int z,
                                               uint32_t o, bool ok) {
-  const float v = __builtin_nontemporal_load(f + (ok ? (int64_t)z * g.plane + o : 0));
+  const float v = ld_once<NT>(f + (ok ? (int64_t)z * g.plane + o : 0));
   return ok ? v : 0.0f;
 }
 // Nontemporal store of one value per lane into plane z of a field through a
@@ -126,11 +133,12 @@ __device__ __forceinline__ float ld_stream_nb(const float *f, const StepGrid &g,
 // every plane, and the hardware drops its store, so the store needs no
 // branch (the adjoint's stores).
 constexpr uint32_t kDropOffset = 0xFFFFFFF0u;
+template <bool NT>
 __device__ __forceinline__ void st_plane(float *f, const StepGrid &g, int z, uint32_t ob,
                                          float v) {
   const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
       f + (int64_t)z * g.plane, (short)0, (int)(uint32_t)(g.plane * 4), 0x00020000);
-  __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, ob, 0, 2 /* nt */);
+  __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, ob, 0, NT ? 2 /* nt */ : 0);
 }
 
 // Per-thread view of one stenciled field: register queue + halo staging.
@@ -147,10 +155,9 @@ __device__ __forceinline__ void st_plane(float *f, const StepGrid &g, int z, uin
 // dropping it from 4 to 3 waves per SIMD.
 // FS: the grid may have a free surface.  Without one, plane loads carry no
 // image branch: a uniform branch in every load cost 7 % of the step time.
-template <int RY, int NW, int NI, int K, bool FS, int DL = 5>
+template <class T, int K, bool FS, int DL = 5>
 struct Marcher {
-  using T = Tile<RY, NW, NI>;
-  static constexpr int NP = T::NP;
+  static constexpr int NP = T::NP, RY = T::RY, NI = T::NI, XW = T::XW;
   float q[NP][9];        // planes z-4 .. z+4 of the thread's points
   float nxt[NP];         // plane z+5 (in flight)
   float hq[DL][T::HPT];  // halo of planes z .. z+DL-1 (hq[0] is staged next)
@@ -185,7 +192,7 @@ struct Marcher {
 #pragma unroll
     for (int j = 0; j < RY; ++j)
 #pragma unroll
-      for (int i = 0; i < NI; ++i) s[4 + wave * RY + j][4 + WAVE * i + lane] = q[j * NI + i][4];
+      for (int i = 0; i < NI; ++i) s[4 + wave * RY + j][4 + XW * i + lane] = q[j * NI + i][4];
 #pragma unroll
     for (int i = 0; i < T::HPT; ++i)
       if (hslot[i] >= 0) (&s[0][0])[hslot[i]] = hq[0][i];
@@ -216,7 +223,7 @@ struct Marcher {
   template <int J, int I>
   __device__ __forceinline__ void diffs(const float (*s)[T::LX], int wave, int lane, float &sx,
                                         float &sy, float &sz) const {
-    const int ly = 4 + wave * RY + J, lx = 4 + WAVE * I + lane;
+    const int ly = 4 + wave * RY + J, lx = 4 + XW * I + lane;
     const float *row = s[ly];
     sx = W1 * (row[lx - 1] + row[lx + 1]) + W2 * (row[lx - 2] + row[lx + 2]) +
          W3 * (row[lx - 3] + row[lx + 3]) + W4 * (row[lx - 4] + row[lx + 4]);
@@ -235,10 +242,9 @@ struct Marcher {
 };
 
 // Common per-thread tile geometry.
-template <int RY, int NW, int NI, int K>
+template <class T, int K>
 struct Geo {
-  using T = Tile<RY, NW, NI>;
-  static constexpr int NP = T::NP;
+  static constexpr int NP = T::NP, RY = T::RY, NI = T::NI, XW = T::XW;
   int lane, wave, x0, y0, z0, z1;
   int xs[NI];     // x of column group i
   int yv[RY];     // y of row j
@@ -253,12 +259,12 @@ struct Geo {
     tile_of(map, b, tx, ty, tz);
     z0 = tz * map.zc;
     z1 = min(z0 + map.zc, g.nz);
-    lane = threadIdx.x % WAVE;
-    wave = threadIdx.x / WAVE;
+    lane = threadIdx.x % XW;
+    wave = threadIdx.x / XW;
     x0 = tx * T::TX;
     y0 = ty * T::TY;
 #pragma unroll
-    for (int i = 0; i < NI; ++i) xs[i] = x0 + WAVE * i + lane;
+    for (int i = 0; i < NI; ++i) xs[i] = x0 + XW * i + lane;
 #pragma unroll
     for (int j = 0; j < RY; ++j) yv[j] = y0 + wave * RY + j;
 #pragma unroll
@@ -274,7 +280,7 @@ struct Geo {
       const int h = threadIdx.x + i * T::NTHREADS;
       if (h < T::NHALO) {
         int gx, gy, lrow, lcol;
-        halo_slot<RY, NW, NI, K>(h, x0, y0, gx, gy, lrow, lcol);
+        halo_slot<T, K>(h, x0, y0, gx, gy, lrow, lcol);
         hin[i] = gx >= 0 && gx < g.nx && gy >= 0 && gy < g.ny;
         hoff[i] = hin[i] ? (uint32_t)gy * (uint32_t)g.pitch + (uint32_t)gx : 0u;
         hslot[i] = lrow * T::LX + lcol;
@@ -307,22 +313,21 @@ struct ColCursor {
 };
 
 // One LDS plane of a tile with its halo.
-template <int RY, int NW, int NI>
-using LdsPlane = float[Tile<RY, NW, NI>::LY][Tile<RY, NW, NI>::LX];
+template <class T>
+using LdsPlane = float[T::LY][T::LX];
 
 // One leapfrog step over tile block b of a grid; records the receivers of
 // step n when seis_tm is set (recomputation sweeps pass none).
-template <int RY, int NW, int NI, bool VD, bool FS>
+template <class T, bool VD, bool FS, bool NT>
 __device__ __forceinline__ void forward_tile(
-    LdsPlane<RY, NW, NI> *sm, const StepGrid &g,
+    LdsPlane<T> *sm, const StepGrid &g,
     const float *__restrict__ cur, const float *prev, float *out, const Source &src, int n,
     const RecTable &rec, const float *__restrict__ rec_scale, float *__restrict__ seis_tm,
     const TileMap &map, int b) {
-  using T = Tile<RY, NW, NI>;
-  constexpr int NP = T::NP;
-  Geo<RY, NW, NI, 0> geo;
+  constexpr int NP = T::NP, RY = T::RY, NI = T::NI;
+  Geo<T, 0> geo;
   if (!geo.init(g, map, b)) return;
-  Marcher<RY, NW, NI, 0, FS> f;
+  Marcher<T, 0, FS> f;
   f.prime(cur, g, geo.z0, geo.off, geo.in, geo.hoff, geo.hin);
   float gxv[NI], gyv[RY];
 #pragma unroll
@@ -340,9 +345,9 @@ __device__ __forceinline__ void forward_tile(
   float pv[NP], kv[NP], mv[NP];  // pointwise streams of the current plane
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
-    pv[p] = ld_stream(prev, g, geo.z0, geo.off[p], geo.in[p]);
-    kv[p] = ld_stream(g.k, g, geo.z0, geo.off[p], geo.in[p]);
-    mv[p] = VD ? ld_stream(g.m2, g, geo.z0, geo.off[p], geo.in[p]) : 0.0f;
+    pv[p] = ld_stream<NT>(prev, g, geo.z0, geo.off[p], geo.in[p]);
+    kv[p] = ld_stream<NT>(g.k, g, geo.z0, geo.off[p], geo.in[p]);
+    mv[p] = VD ? ld_stream<NT>(g.m2, g, geo.z0, geo.off[p], geo.in[p]) : 0.0f;
   }
   for (int z = geo.z0; z < geo.z1; ++z) {
     float(*s)[T::LX] = sm[z & 1];
@@ -352,9 +357,9 @@ __device__ __forceinline__ void forward_tile(
     float pn[NP], kn[NP], mn[NP];  // next plane, in flight during this one
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
-      pn[p] = ld_stream(prev, g, z + 1, geo.off[p], geo.in[p] && more);
-      kn[p] = ld_stream(g.k, g, z + 1, geo.off[p], geo.in[p] && more);
-      mn[p] = VD ? ld_stream(g.m2, g, z + 1, geo.off[p], geo.in[p] && more) : 0.0f;
+      pn[p] = ld_stream<NT>(prev, g, z + 1, geo.off[p], geo.in[p] && more);
+      kn[p] = ld_stream<NT>(g.k, g, z + 1, geo.off[p], geo.in[p] && more);
+      mn[p] = VD ? ld_stream<NT>(g.m2, g, z + 1, geo.off[p], geo.in[p] && more) : 0.0f;
     }
     __syncthreads();
     const float gzv = g.gz[z];
@@ -373,7 +378,10 @@ __device__ __forceinline__ void forward_tile(
         if (geo.in[P] && p == src.idx) acc += src.sigma[0] * src.wavelet[n];
         const float G = gxv[I] * gyv[J] * gzv;
         const float o = (!FS || z > g.zs) ? G * (acc - G * pv[P]) : 0.0f;  // zero at/above a free surface
-        if (geo.in[P]) __builtin_nontemporal_store(o, out + p);
+        if (geo.in[P]) {
+          if constexpr (NT) __builtin_nontemporal_store(o, out + p);
+          else out[p] = o;
+        }
         if (cc[P].ez == z) {
           for (int r = rec.ent_rp[cc[P].e]; r < rec.ent_rp[cc[P].e + 1]; ++r) {
             const int id = rec.perm[r];
@@ -393,31 +401,29 @@ __device__ __forceinline__ void forward_tile(
   }
 }
 
-template <int RY, int NW, int NI, bool VD, bool FS>
-__global__ void __launch_bounds__(WAVE * NW)
+template <class T, bool VD, bool FS, bool NT>
+__global__ void __launch_bounds__(T::NTHREADS)
     k_forward(StepGrid g, const float *__restrict__ cur, const float *prev, float *out,
               Source src, int n, RecTable rec, const float *__restrict__ rec_scale,
               float *__restrict__ seis_tm, TileMap map) {
-  using T = Tile<RY, NW, NI>;
   __shared__ float sm[2][T::LY][T::LX];
-  forward_tile<RY, NW, NI, VD, FS>(sm, g, cur, prev, out, src, n, rec, rec_scale, seis_tm, map,
+  forward_tile<T, VD, FS, NT>(sm, g, cur, prev, out, src, n, rec, rec_scale, seis_tm, map,
                                    blockIdx.x);
 }
 
 // Several grids (one per shot) advanced by one launch: block b belongs to the
 // window whose [block_begin, block_end) contains it.  Window ranges start at
 // multiples of 8 so that each window keeps the XCD-aware tile order.
-template <int RY, int NW, int NI, bool VD, bool FS>
-__global__ void __launch_bounds__(WAVE * NW)
+template <class T, bool VD, bool FS, bool NT>
+__global__ void __launch_bounds__(T::NTHREADS)
     k_forward_multi(const WindowStep *__restrict__ wins, int nwin, int n) {
-  using T = Tile<RY, NW, NI>;
   __shared__ float sm[2][T::LY][T::LX];
   const int b = blockIdx.x;
   int w = 0;
   while (w + 1 < nwin && b >= wins[w + 1].block_begin) ++w;
   const WindowStep &d = wins[w];
   if (b >= d.block_end) return;
-  forward_tile<RY, NW, NI, VD, FS>(sm, d.g, d.cur, d.prev, d.out, d.src, n, d.rec, d.rec_scale,
+  forward_tile<T, VD, FS, NT>(sm, d.g, d.cur, d.prev, d.out, d.src, n, d.rec, d.rec_scale,
                                    d.seis_tm, d.map, b - d.block_begin);
 }
 
@@ -428,19 +434,18 @@ __global__ void __launch_bounds__(WAVE * NW)
 // residuals of sample m-1 injected at the receivers, and
 // g += psi^{m+1} (L w^m - m2 w^m) (+ the illumination).  sm[0] stages psi,
 // sm[1] w.
-template <int RY, int NW, int NI, int DL, bool VD, bool ILLUM, bool FS>
+template <class T, int DL, bool VD, bool ILLUM, bool FS, bool NT>
 __device__ __forceinline__ void adjoint_tile(
     const StepGrid g, const float *__restrict__ cur, const float *prev,
     float *out, const RecTable rec, const float *__restrict__ res_tm, int m,
     const float *__restrict__ wm, float *__restrict__ grad, const IllumOut il,
     const TileMap map, int b) {
-  using T = Tile<RY, NW, NI>;
-  constexpr int NP = T::NP;
+  constexpr int NP = T::NP, RY = T::RY, NI = T::NI;
   __shared__ float sm[2][2][T::LY][T::LX];  // [field][buffer]
-  Geo<RY, NW, NI, 1> geo;
+  Geo<T, 1> geo;
   if (!geo.init(g, map, b)) return;
-  Marcher<RY, NW, NI, 1, FS, DL> fa;  // adjoint state psi^{m+1}
-  Marcher<RY, NW, NI, 1, FS, DL> fw;  // forward state w^m
+  Marcher<T, 1, FS, DL> fa;  // adjoint state psi^{m+1}
+  Marcher<T, 1, FS, DL> fw;  // forward state w^m
   fa.prime(cur, g, geo.z0, geo.off, geo.in, geo.hoff, geo.hin);
   fw.prime(wm, g, geo.z0, geo.off, geo.in, geo.hoff, geo.hin);
   float gxv[NI], gyv[RY];
@@ -461,10 +466,10 @@ __device__ __forceinline__ void adjoint_tile(
   float pv[NP], kv[NP], mv[NP], gv[NP];
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
-    pv[p] = ld_stream_nb(prev, g, geo.z0, geo.off[p], geo.in[p]);
-    kv[p] = ld_stream_nb(g.k, g, geo.z0, geo.off[p], geo.in[p]);
-    mv[p] = VD ? ld_stream_nb(g.m2, g, geo.z0, geo.off[p], geo.in[p]) : 0.0f;
-    gv[p] = ld_stream_nb(grad, g, geo.z0, geo.off[p], geo.in[p]);
+    pv[p] = ld_stream_nb<NT>(prev, g, geo.z0, geo.off[p], geo.in[p]);
+    kv[p] = ld_stream_nb<NT>(g.k, g, geo.z0, geo.off[p], geo.in[p]);
+    mv[p] = VD ? ld_stream_nb<NT>(g.m2, g, geo.z0, geo.off[p], geo.in[p]) : 0.0f;
+    gv[p] = ld_stream_nb<NT>(grad, g, geo.z0, geo.off[p], geo.in[p]);
   }
   for (int z = geo.z0; z < geo.z1; ++z) {
     float(*sa)[T::LX] = sm[0][z & 1];
@@ -478,10 +483,10 @@ __device__ __forceinline__ void adjoint_tile(
     float pn[NP], kn[NP], mn[NP], gn[NP];
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
-      pn[p] = ld_stream_nb(prev, g, z + 1, geo.off[p], geo.in[p] && more);
-      kn[p] = ld_stream_nb(g.k, g, z + 1, geo.off[p], geo.in[p] && more);
-      mn[p] = VD ? ld_stream_nb(g.m2, g, z + 1, geo.off[p], geo.in[p] && more) : 0.0f;
-      gn[p] = ld_stream_nb(grad, g, z + 1, geo.off[p], geo.in[p] && more);
+      pn[p] = ld_stream_nb<NT>(prev, g, z + 1, geo.off[p], geo.in[p] && more);
+      kn[p] = ld_stream_nb<NT>(g.k, g, z + 1, geo.off[p], geo.in[p] && more);
+      mn[p] = VD ? ld_stream_nb<NT>(g.m2, g, z + 1, geo.off[p], geo.in[p] && more) : 0.0f;
+      gn[p] = ld_stream_nb<NT>(grad, g, z + 1, geo.off[p], geo.in[p] && more);
     }
     __syncthreads();
     static_for<RY>([&](auto Jc) {
@@ -506,8 +511,8 @@ __device__ __forceinline__ void adjoint_tile(
         const float G = gxv[I] * gyv[J] * gzv;
         const bool live = !FS || z > g.zs;  // at and above a free surface psi and w stay zero
         const uint32_t ob = geo.in[P] ? 4u * geo.off[P] : kDropOffset;
-        st_plane(out, g, z, ob, live ? G * (acc - G * pv[P]) : 0.0f);
-        st_plane(grad, g, z, ob, live ? gv[P] + ca * (VD ? lap_w - mv[P] * cw : lap_w) : gv[P]);
+        st_plane<NT>(out, g, z, ob, live ? G * (acc - G * pv[P]) : 0.0f);
+        st_plane<NT>(grad, g, z, ob, live ? gv[P] + ca * (VD ? lap_w - mv[P] * cw : lap_w) : gv[P]);
         if (ILLUM && geo.in[P]) {
           const int ix = geo.xs[I] - il.border, iy = geo.yv[J] - il.border, iz = z - il.border;
           if (ix >= 0 && ix < il.mnx && iy >= 0 && iy < il.mny && iz >= 0 && iz < il.mnz)
@@ -531,19 +536,18 @@ __device__ __forceinline__ void adjoint_tile(
 // The single-shot kernel keeps its own copy of the tile body: sharing the
 // device function with the batched kernel cost two VGPR spills in the plane
 // loop (1238 against 1220 us per step at 576^3).
-template <int RY, int NW, int NI, int DL, bool VD, bool ILLUM, bool FS>
-__global__ void __launch_bounds__(WAVE * NW)
+template <class T, int DL, bool VD, bool ILLUM, bool FS, bool NT>
+__global__ void __launch_bounds__(T::NTHREADS)
     k_adjoint(StepGrid g, const float *__restrict__ cur, const float *prev, float *out,
               RecTable rec, const float *__restrict__ res_tm, int m,
               const float *__restrict__ wm, float *__restrict__ grad, IllumOut il,
               TileMap map) {
-  using T = Tile<RY, NW, NI>;
-  constexpr int NP = T::NP;
+  constexpr int NP = T::NP, RY = T::RY, NI = T::NI;
   __shared__ float sm[2][2][T::LY][T::LX];  // [field][buffer]
-  Geo<RY, NW, NI, 1> geo;
+  Geo<T, 1> geo;
   if (!geo.init(g, map, blockIdx.x)) return;
-  Marcher<RY, NW, NI, 1, FS, DL> fa;  // adjoint state psi^{m+1}
-  Marcher<RY, NW, NI, 1, FS, DL> fw;  // forward state w^m
+  Marcher<T, 1, FS, DL> fa;  // adjoint state psi^{m+1}
+  Marcher<T, 1, FS, DL> fw;  // forward state w^m
   fa.prime(cur, g, geo.z0, geo.off, geo.in, geo.hoff, geo.hin);
   fw.prime(wm, g, geo.z0, geo.off, geo.in, geo.hoff, geo.hin);
   float gxv[NI], gyv[RY];
@@ -564,10 +568,10 @@ __global__ void __launch_bounds__(WAVE * NW)
   float pv[NP], kv[NP], mv[NP], gv[NP];
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
-    pv[p] = ld_stream_nb(prev, g, geo.z0, geo.off[p], geo.in[p]);
-    kv[p] = ld_stream_nb(g.k, g, geo.z0, geo.off[p], geo.in[p]);
-    mv[p] = VD ? ld_stream_nb(g.m2, g, geo.z0, geo.off[p], geo.in[p]) : 0.0f;
-    gv[p] = ld_stream_nb(grad, g, geo.z0, geo.off[p], geo.in[p]);
+    pv[p] = ld_stream_nb<NT>(prev, g, geo.z0, geo.off[p], geo.in[p]);
+    kv[p] = ld_stream_nb<NT>(g.k, g, geo.z0, geo.off[p], geo.in[p]);
+    mv[p] = VD ? ld_stream_nb<NT>(g.m2, g, geo.z0, geo.off[p], geo.in[p]) : 0.0f;
+    gv[p] = ld_stream_nb<NT>(grad, g, geo.z0, geo.off[p], geo.in[p]);
   }
   for (int z = geo.z0; z < geo.z1; ++z) {
     float(*sa)[T::LX] = sm[0][z & 1];
@@ -581,10 +585,10 @@ __global__ void __launch_bounds__(WAVE * NW)
     float pn[NP], kn[NP], mn[NP], gn[NP];
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
-      pn[p] = ld_stream_nb(prev, g, z + 1, geo.off[p], geo.in[p] && more);
-      kn[p] = ld_stream_nb(g.k, g, z + 1, geo.off[p], geo.in[p] && more);
-      mn[p] = VD ? ld_stream_nb(g.m2, g, z + 1, geo.off[p], geo.in[p] && more) : 0.0f;
-      gn[p] = ld_stream_nb(grad, g, z + 1, geo.off[p], geo.in[p] && more);
+      pn[p] = ld_stream_nb<NT>(prev, g, z + 1, geo.off[p], geo.in[p] && more);
+      kn[p] = ld_stream_nb<NT>(g.k, g, z + 1, geo.off[p], geo.in[p] && more);
+      mn[p] = VD ? ld_stream_nb<NT>(g.m2, g, z + 1, geo.off[p], geo.in[p] && more) : 0.0f;
+      gn[p] = ld_stream_nb<NT>(grad, g, z + 1, geo.off[p], geo.in[p] && more);
     }
     __syncthreads();
     static_for<RY>([&](auto Jc) {
@@ -609,8 +613,8 @@ __global__ void __launch_bounds__(WAVE * NW)
         const float G = gxv[I] * gyv[J] * gzv;
         const bool live = !FS || z > g.zs;  // at and above a free surface psi and w stay zero
         const uint32_t ob = geo.in[P] ? 4u * geo.off[P] : kDropOffset;
-        st_plane(out, g, z, ob, live ? G * (acc - G * pv[P]) : 0.0f);
-        st_plane(grad, g, z, ob, live ? gv[P] + ca * (VD ? lap_w - mv[P] * cw : lap_w) : gv[P]);
+        st_plane<NT>(out, g, z, ob, live ? G * (acc - G * pv[P]) : 0.0f);
+        st_plane<NT>(grad, g, z, ob, live ? gv[P] + ca * (VD ? lap_w - mv[P] * cw : lap_w) : gv[P]);
         if (ILLUM && geo.in[P]) {
           const int ix = geo.xs[I] - il.border, iy = geo.yv[J] - il.border, iz = z - il.border;
           if (ix >= 0 && ix < il.mnx && iy >= 0 && iy < il.mny && iz >= 0 && iz < il.mnz)
@@ -641,11 +645,10 @@ __device__ __forceinline__ float *pool_buffer(const GradWindow &d, int k) {
 // the window whose [fblock_begin, fblock_end) contains it; the step reads pool
 // buffers cur_k (w^n) and prev_k (w^{n-1}) and writes out_k, recording the
 // receivers when `record` is set.
-template <int RY, int NW, int NI, bool VD, bool FS>
-__global__ void __launch_bounds__(WAVE * NW)
+template <class T, bool VD, bool FS, bool NT>
+__global__ void __launch_bounds__(T::NTHREADS)
     k_forward_pool(const GradWindow *__restrict__ wins, int nwin, int n, int cur_k, int prev_k,
                    int out_k, int record) {
-  using T = Tile<RY, NW, NI>;
   __shared__ float sm[2][T::LY][T::LX];
   const int b = blockIdx.x;
   int w = 0;
@@ -653,7 +656,7 @@ __global__ void __launch_bounds__(WAVE * NW)
   const GradWindow &d = wins[w];
   if (b >= d.fblock_end) return;
   const RecTable none{};
-  forward_tile<RY, NW, NI, VD, FS>(sm, d.g, pool_buffer(d, cur_k), pool_buffer(d, prev_k),
+  forward_tile<T, VD, FS, NT>(sm, d.g, pool_buffer(d, cur_k), pool_buffer(d, prev_k),
                                    pool_buffer(d, out_k), d.src, n, record ? d.rec : none,
                                    d.rec_scale, record ? d.seis_tm : nullptr, d.fmap,
                                    b - d.fblock_begin);
@@ -661,8 +664,8 @@ __global__ void __launch_bounds__(WAVE * NW)
 
 // One adjoint step (with imaging) of every window: psi^{m+1} is P1 (parity 0)
 // or P2 (parity 1) and psi^m overwrites the other; w^m is pool buffer wm_k.
-template <int RY, int NW, int NI, int DL, bool VD, bool ILLUM, bool FS>
-__global__ void __launch_bounds__(WAVE * NW)
+template <class T, int DL, bool VD, bool ILLUM, bool FS, bool NT>
+__global__ void __launch_bounds__(T::NTHREADS)
     k_adjoint_multi(const GradWindow *__restrict__ wins, int nwin, int m, int parity, int wm_k) {
   const int b = blockIdx.x;
   int w = 0;
@@ -670,15 +673,9 @@ __global__ void __launch_bounds__(WAVE * NW)
   const GradWindow &d = wins[w];
   if (b >= d.ablock_end) return;
   float *a1 = parity ? d.P2 : d.P1, *a2 = parity ? d.P1 : d.P2;
-  adjoint_tile<RY, NW, NI, DL, VD, ILLUM, FS>(d.g, a1, a2, a2, d.rec, d.res_tm, m,
+  adjoint_tile<T, DL, VD, ILLUM, FS, NT>(d.g, a1, a2, a2, d.rec, d.res_tm, m,
                                               pool_buffer(d, wm_k), d.gimg, d.il, d.amap,
                                               b - d.ablock_begin);
-}
-
-int env_int(const char *name, int dflt) {
-  const char *v = std::getenv(name);
-  if (!v || !*v) return dflt;
-  return std::atoi(v);
 }
 
 int device_cus() {
@@ -702,355 +699,358 @@ int blocks_per_cu(K kernel, int threads) {
   return per_cu;
 }
 
-// Tile map: the grid's (x, y) tiles times nch z chunks.  With `rounds` > 0 the
-// chunk count aims at that many rounds of resident blocks.  Otherwise it
-// minimises a cost model of the launch with R = blocks / resident slots:
-//   R <= 1:  one round, as long as one block (an under-filled device runs no
-//            faster per block);
-//   R > 1:   floor(R) full rounds plus a last round that costs its fill
-//            fraction but at least kTailFloor of a round,
-// each round lasting zc planes plus `halo` plane-equivalents for re-reading
-// the 8-plane z halo of the stencil fields.  Fitted to step times measured at
-// 576^3 (forward 64x16 and adjoint 64x8 tiles, 2 to 19 chunks): time / cost
-// was constant to within 3 per cent, with a last round of few blocks taking
-// about half a full one.  Chunks are at least min_zc planes deep.  A single
-// launch takes min_zc = 4: a grid too small to fill the device even then
-// (R <= 1) gets the shortest marches, since its step time is the latency of
-// one block's march (80^3 forward: 21 us per step with 16-plane chunks, 11 us
-// with 4-plane ones; 2 planes gave 11.2).  The windows of a batch of several
-// shots take 16: together they fill the device, and 4-plane chunks of small
-// windows only added halo re-reads (24 windows of 50-69 cells: gradients
-// 0.182 s against 0.162 s).
-constexpr double kTailFloor = 0.47;
-
-double launch_cost(double R, int zc, double halo) {
-  if (R <= 1.0) return zc + halo;
-  const double full = std::floor(R), f = R - full;
-  return (full + (f > 0.0 ? std::max(f, kTailFloor) : 0.0)) * (zc + halo);
-}
-
-TileMap make_map(const StepGrid &g, int tx, int ty, int per_cu, int nch_override, int rounds,
-                 double halo, int min_zc) {
-  TileMap m;
-  m.tiles_x = (g.nx + tx - 1) / tx;
-  m.tiles_y = (g.ny + ty - 1) / ty;
-  const int64_t tiles = (int64_t)m.tiles_x * m.tiles_y;
-  const int64_t slots = (int64_t)per_cu * device_cus();
-  const int max_nch = std::max(1, (g.nz + min_zc - 1) / min_zc);
-  int nch = nch_override;
-  if (nch <= 0 && rounds > 0) nch = (int)((rounds * slots + tiles / 2) / tiles);
-  if (nch <= 0) {
-    double best = 1e300;
-    for (int c = 1; c <= max_nch; ++c) {
-      const int zc = (g.nz + c - 1) / c;
-      if ((g.nz + zc - 1) / zc != c) continue;  // same chunks as a smaller count
-      const double cost = launch_cost((double)(c * tiles) / (double)slots, zc, halo);
-      if (cost < best) {
-        best = cost;
-        nch = c;
-      }
-    }
-  }
-  nch = std::max(1, std::min(nch, max_nch));
-  m.zc = (g.nz + nch - 1) / nch;
-  m.nchunks = (g.nz + m.zc - 1) / m.zc;
-  m.nblocks = (int)(tiles * m.nchunks);
-  return m;
-}
-
-// Halo cost of the step kernels in plane-equivalents: 8 planes times the
-// stencil fields' share of the bytes per point (forward: 4 of 20 B with
-// variable density; adjoint: 8 of 32 B).
-constexpr double kFwdHalo = 8.0 * 4.0 / 20.0, kAdjHalo = 8.0 * 8.0 / 32.0;
-
-// Forward tile shapes selectable at run time: (rows per thread, wavefronts,
-// column groups per thread).  Variant 0 was the fastest of the 64-wide tiles
-// at 576^3 (694 us per step against 793 us for 64 x 32 tiles and 745 us for
-// 4 x 4 with the same chunking rule).
+// Forward tile shapes (rows per thread, row groups, column groups per thread,
+// lanes per row): 0 to 4 by tuning, 5 by the planner only.  Of the 64-wide tiles
+// 0 was the fastest at 576^3 (694 us per step against 793 us for 64 x 32 tiles
+// and 745 us for 4 x 4 with the same chunking rule).
 template <int V>
 struct FwdShape;
 template <>
-struct FwdShape<0> {
-  static constexpr int RY = 2, NW = 8, NI = 1;  // 64 x 16
-};
+struct FwdShape<0> : Tile<2, 8, 1, 64> {};  // 64 x 16
 template <>
-struct FwdShape<1> {
-  static constexpr int RY = 2, NW = 16, NI = 1;  // 64 x 32
-};
+struct FwdShape<1> : Tile<2, 16, 1, 64> {};  // 64 x 32
 template <>
-struct FwdShape<2> {
-  static constexpr int RY = 2, NW = 4, NI = 1;  // 64 x 8
-};
+struct FwdShape<2> : Tile<2, 4, 1, 64> {};  // 64 x 8
 template <>
-struct FwdShape<3> {
-  static constexpr int RY = 4, NW = 4, NI = 1;  // 64 x 16
-};
+struct FwdShape<3> : Tile<4, 4, 1, 64> {};  // 64 x 16
 template <>
-struct FwdShape<4> {
-  static constexpr int RY = 1, NW = 16, NI = 3;  // 192 x 16
-};
+struct FwdShape<4> : Tile<1, 16, 3, 64> {};  // 192 x 16
+template <>
+struct FwdShape<5> : Tile<2, 16, 1, 32> {};  // 32 x 32
 
-// Adjoint tile shapes selectable at run time, with their halo delay-line
-// depth.  With two stenciled fields, the 64 x 32 tile (one halo value per
-// thread per plane, five-plane delay) stays within 128 VGPRs (4 waves per
+// Adjoint tile shapes, with their halo delay-line depth: 0 to 3 by tuning, 4 by
+// the planner only.  With two stenciled fields, the 64 x 32 tile (one halo value
+// per thread per plane, five-plane delay) stays within 128 VGPRs (4 waves per
 // SIMD): 1213 us per step at 576^3 against 1432 us (64 x 8) and 1654 us
 // (64 x 16, five-plane delay: 137 VGPRs, 3 waves per SIMD).  A two-plane delay
 // keeps the 64 x 16 tile at 125 VGPRs: two blocks per CU.
 template <int V>
 struct AdjShape;
 template <>
-struct AdjShape<0> {
-  static constexpr int RY = 2, NW = 16, NI = 1, DL = 5;  // 64 x 32
+struct AdjShape<0> : Tile<2, 16, 1, 64> {  // 64 x 32
+  static constexpr int DL = 5;
 };
 template <>
-struct AdjShape<1> {
-  static constexpr int RY = 2, NW = 8, NI = 1, DL = 2;  // 64 x 16
+struct AdjShape<1> : Tile<2, 8, 1, 64> {  // 64 x 16
+  static constexpr int DL = 2;
 };
 template <>
-struct AdjShape<2> {
-  static constexpr int RY = 2, NW = 4, NI = 1, DL = 5;  // 64 x 8
+struct AdjShape<2> : Tile<2, 4, 1, 64> {  // 64 x 8
+  static constexpr int DL = 5;
 };
 template <>
-struct AdjShape<3> {
-  static constexpr int RY = 2, NW = 8, NI = 1, DL = 1;  // 64 x 16, halo one plane ahead
+struct AdjShape<3> : Tile<2, 8, 1, 64> {  // 64 x 16, halo one plane ahead
+  static constexpr int DL = 1;
+};
+template <>
+struct AdjShape<4> : Tile<2, 16, 1, 32> {  // 32 x 32
+  static constexpr int DL = 5;
 };
 
-template <int V, bool VD, bool FS>
-int fwd_per_cu() {
-  using S = FwdShape<V>;
-  static const int per_cu =
-      blocks_per_cu(k_forward<S::RY, S::NW, S::NI, VD, FS>, Tile<S::RY, S::NW, S::NI>::NTHREADS);
-  return per_cu;
+template <class S>
+using TileOf = Tile<S::RY, S::NG, S::NI, S::XW>;
+
+template <bool B>
+using Bool = std::integral_constant<bool, B>;
+template <class F>
+auto with_bool(bool b, F f) {
+  return b ? f(Bool<true>{}) : f(Bool<false>{});
 }
 
-template <int V>
-using FwdTile = Tile<FwdShape<V>::RY, FwdShape<V>::NW, FwdShape<V>::NI>;
-
-template <int V, bool VD, bool FS>
-hipError_t fwd_launch(const StepGrid &g, const float *cur, const float *prev, float *out,
-                      const Source &src, int n, const RecTable &rec, const float *rec_scale,
-                      float *seis_tm, const Tuning &tu, hipStream_t stream) {
-  using S = FwdShape<V>;
-  static const int nch_env = env_int("WFD_ZCHUNKS_FWD", 0);  // 0 = automatic
-  const TileMap map = make_map(g, FwdTile<V>::TX, FwdTile<V>::TY, fwd_per_cu<V, VD, FS>(),
-                               nch_env, tu.rounds, kFwdHalo, kSingleMinZc);
-  hipLaunchKernelGGL((k_forward<S::RY, S::NW, S::NI, VD, FS>), dim3(map.nblocks),
-                     dim3(FwdTile<V>::NTHREADS), 0, stream, g, cur, prev, out, src, n, rec,
-                     rec_scale, seis_tm, map);
-  return hipGetLastError();
+// Calls f(shape, variable density, free surface, streaming hints).  Only the
+// shapes that the planner chooses come without the hints.
+template <class F>
+auto with_forward(int shape, bool vd, bool fs, bool stream, F f) {
+  return with_bool(vd, [&](auto VD) {
+    return with_bool(fs, [&](auto FS) {
+      auto both = [&](auto S) {
+        return with_bool(stream, [&](auto NT) { return f(S, VD, FS, NT); });
+      };
+      switch (shape) {
+        case 1: return f(FwdShape<1>{}, VD, FS, Bool<true>{});
+        case 2: return f(FwdShape<2>{}, VD, FS, Bool<true>{});
+        case 3: return f(FwdShape<3>{}, VD, FS, Bool<true>{});
+        case 4: return f(FwdShape<4>{}, VD, FS, Bool<true>{});
+        case 5: return both(FwdShape<5>{});
+        default: return both(FwdShape<0>{});
+      }
+    });
+  });
+}
+template <class F>
+auto with_adjoint(int shape, bool vd, bool illum, bool fs, bool stream, F f) {
+  return with_bool(vd, [&](auto VD) {
+    return with_bool(illum, [&](auto IL) {
+      return with_bool(fs, [&](auto FS) {
+        auto both = [&](auto S) {
+          return with_bool(stream, [&](auto NT) { return f(S, VD, IL, FS, NT); });
+        };
+        switch (shape) {
+          case 1: return f(AdjShape<1>{}, VD, IL, FS, Bool<true>{});
+          case 2: return f(AdjShape<2>{}, VD, IL, FS, Bool<true>{});
+          case 3: return both(AdjShape<3>{});
+          case 4: return both(AdjShape<4>{});
+          default: return both(AdjShape<0>{});
+        }
+      });
+    });
+  });
 }
 
-template <int V, bool VD, bool FS>
-hipError_t fwd_multi_launch(const WindowStep *wins, int nwin, int nblocks, int n,
-                            hipStream_t stream) {
-  using S = FwdShape<V>;
-  hipLaunchKernelGGL((k_forward_multi<S::RY, S::NW, S::NI, VD, FS>), dim3(nblocks),
-                     dim3(FwdTile<V>::NTHREADS), 0, stream, wins, nwin, n);
-  return hipGetLastError();
+// A tile shape as the planner sees it: tile, resident blocks per CU, and its time
+// for a full round against shape 0's (below).
+struct Candidate {
+  int shape, tx, ty, per_cu;
+  double weight;
+};
+
+template <class K, class S>
+Candidate candidate(int shape, K kernel, S, double weight) {
+  return Candidate{shape, S::TX, S::TY, blocks_per_cu(kernel, S::NTHREADS), weight};
 }
 
-template <int V, bool VD, bool ILLUM, bool FS>
-hipError_t adj_launch(const Tuning &tu, const StepGrid &g, const float *cur, const float *prev,
-                      float *out, const RecTable &rec, const float *res_tm, int m,
-                      const float *wm, float *grad, const IllumOut &illum, hipStream_t stream) {
-  using S = AdjShape<V>;
-  using T = Tile<S::RY, S::NW, S::NI>;
-  static const int per_cu =
-      blocks_per_cu(k_adjoint<S::RY, S::NW, S::NI, S::DL, VD, ILLUM, FS>, T::NTHREADS);
-  static const int nch = env_int("WFD_ZCHUNKS_ADJ", 0);  // 0 = automatic
-  const TileMap map =
-      make_map(g, T::TX, T::TY, per_cu, nch, tu.adj_rounds, kAdjHalo, kSingleMinZc);
-  hipLaunchKernelGGL((k_adjoint<S::RY, S::NW, S::NI, S::DL, VD, ILLUM, FS>), dim3(map.nblocks),
-                     dim3(T::NTHREADS), 0, stream, g, cur, prev, out, rec, res_tm, m, wm, grad,
-                     illum, map);
-  return hipGetLastError();
+// Weights: 32-wide forward tiles against 64 x 16 where both waste no lanes,
+// 240 x 240 x 200 and 144^3 without streaming hints 39.8 / 41.1 and 19.8 / 20.3
+// us, 250 x 250 x 240 and 576^3 with them 67.5 / 61.2 and 730 / 704 (128-byte
+// rows); adjoint, 240 x 240 x 200: 64 x 16 tiles 91 / 87 us, 32 x 32 99 / 87 with
+// hints and 75 / 72 without.  They pay where a grid's last 64-wide tile is mostly
+// empty: 390 x 340 x 320 forward 166 us against 176.
+Candidate forward_candidate(int shape, bool vd, bool fs, bool stream) {
+  return with_forward(shape, vd, fs, stream, [&](auto S, auto VD, auto FS, auto NT) {
+    using Sh = decltype(S);
+    static const Candidate c = candidate(
+        shape, k_forward<TileOf<Sh>, decltype(VD)::value, decltype(FS)::value, decltype(NT)::value>,
+        S, shape == 5 ? (NT.value ? 1.08 : 0.98) : 1.0);
+    return c;
+  });
+}
+Candidate adjoint_candidate(int shape, bool vd, bool illum, bool fs, bool stream) {
+  return with_adjoint(shape, vd, illum, fs, stream, [&](auto S, auto VD, auto IL, auto FS, auto NT) {
+    using Sh = decltype(S);
+    static const Candidate c =
+        candidate(shape,
+                  k_adjoint<TileOf<Sh>, Sh::DL, decltype(VD)::value, decltype(IL)::value,
+                            decltype(FS)::value, decltype(NT)::value>,
+                  S, shape == 3 ? 1.04 : shape == 4 ? (NT.value ? 1.12 : 1.05) : 1.0);
+    return c;
+  });
 }
 
-template <int V>
-hipError_t adj_dispatch(const Tuning &tu, const StepGrid &g, const float *cur, const float *prev,
-                        float *out, const RecTable &rec, const float *res_tm, int m,
-                        const float *wm, float *grad, const IllumOut &illum, hipStream_t stream) {
-  const bool vd = g.m2 != nullptr, fs = g.zs != kNoSurface;
-#define WFD_ADJ(VD_, IL_)                                                                       \
-  return fs ? adj_launch<V, VD_, IL_, true>(tu, g, cur, prev, out, rec, res_tm, m, wm, grad,    \
-                                            illum, stream)                                      \
-            : adj_launch<V, VD_, IL_, false>(tu, g, cur, prev, out, rec, res_tm, m, wm, grad,   \
-                                             illum, stream)
-  if (vd) {
-    if (illum.p) WFD_ADJ(true, true);
-    WFD_ADJ(true, false);
+// z chunks at least this deep (shallower ones gave nothing: 80^3 11.0 us at 4
+// planes, 11.2 at 2).
+constexpr int kMinZc = 4;
+
+// Time of a launch of `blocks` blocks that march zc planes each, in planes of a
+// full device, from the rounds R = blocks / resident slots:
+//   R <= 1:  one round.  A plane takes less where fewer points share a CU: 1.30
+//            us with one 64 x 16 tile per CU, 1.65 with two (240 x 240 x 200 and
+//            296^3, 190 to 480 blocks).
+//   R > 1:   floor(R) full rounds and a last one that costs its fill, but at
+//            least kTailFloor of a round (a block alone takes as long as a full
+//            device's).
+// Each round lasts zc planes plus kHalo for the queue's first planes and the
+// 8-plane z halo.  Step times over 1 to 50 chunks at 144^3, 233 x 247 x 201,
+// 240 x 240 x 200, 296^3, 390 x 340 x 320 and 576^3 keep a ratio to this within
+// 10 per cent, and its best chunk count (the smallest within 2 per cent) is the
+// measured best or within 2 per cent of it.  (With a floor of 0.47, fitted to 576^3 alone, 296^3 ran 1.48
+// rounds of 37 planes: 125 us instead of 105 us for 0.93 of 60; the adjoint 278
+// instead of 240 us.)
+constexpr double kTailFloor = 0.9, kHalo = 4.0;
+
+double launch_cost(const Candidate &c, int64_t blocks, int zc) {
+  const int64_t cus = device_cus();
+  const double R = (double)blocks / (double)(c.per_cu * cus), full = std::floor(R), f = R - full;
+  double rounds;
+  if (R <= 1.0) {
+    const double share = (double)((blocks + cus - 1) / cus) * c.tx * c.ty / 2048.0;
+    rounds = std::min(1.0, 0.58 + 0.42 * share);
+  } else {
+    rounds = full + (f > 0.0 ? std::max(f, kTailFloor) : 0.0);
   }
-  if (illum.p) WFD_ADJ(false, true);
-  WFD_ADJ(false, false);
-#undef WFD_ADJ
+  return c.weight * rounds * (zc + kHalo);
 }
 
-template <int V, bool VD, bool FS>
-hipError_t fwd_pool_launch(const GradWindow *wins, int nwin, int nblocks, int n, int ck, int pk,
-                           int ok, int record, hipStream_t stream) {
-  using S = FwdShape<V>;
-  hipLaunchKernelGGL((k_forward_pool<S::RY, S::NW, S::NI, VD, FS>), dim3(nblocks),
-                     dim3(FwdTile<V>::NTHREADS), 0, stream, wins, nwin, n, ck, pk, ok, record);
-  return hipGetLastError();
+int64_t tiles_of(const StepGrid &g, const Candidate &c) {
+  return (int64_t)((g.nx + c.tx - 1) / c.tx) * ((g.ny + c.ty - 1) / c.ty);
 }
 
-template <int V, bool VD, bool ILLUM, bool FS>
-hipError_t adj_multi_launch(const GradWindow *wins, int nwin, int nblocks, int m, int parity,
-                            int wk, hipStream_t stream) {
-  using S = AdjShape<V>;
-  hipLaunchKernelGGL((k_adjoint_multi<S::RY, S::NW, S::NI, S::DL, VD, ILLUM, FS>), dim3(nblocks),
-                     dim3(WAVE * S::NW), 0, stream, wins, nwin, m, parity, wk);
-  return hipGetLastError();
+TileMap map_of(const StepGrid &g, const Candidate &c, int nch) {
+  TileMap m;
+  m.tiles_x = (g.nx + c.tx - 1) / c.tx;
+  m.tiles_y = (g.ny + c.ty - 1) / c.ty;
+  nch = std::max(1, std::min(nch, (g.nz + kMinZc - 1) / kMinZc));
+  m.zc = (g.nz + nch - 1) / nch;
+  m.nchunks = (g.nz + m.zc - 1) / m.zc;
+  m.nblocks = (int)((int64_t)m.tiles_x * m.tiles_y * m.nchunks);
+  return m;
 }
 
-template <int V>
-hipError_t adj_multi_dispatch(const GradWindow *wins, int nwin, int nblocks, int m, int parity,
-                              int wk, bool vd, bool illum, bool fs, hipStream_t stream) {
-#define WFD_AM(VD_, IL_)                                                                     \
-  return fs ? adj_multi_launch<V, VD_, IL_, true>(wins, nwin, nblocks, m, parity, wk, stream) \
-            : adj_multi_launch<V, VD_, IL_, false>(wins, nwin, nblocks, m, parity, wk, stream)
-  if (vd) {
-    if (illum) WFD_AM(true, true);
-    WFD_AM(true, false);
+// Tile maps of a launch over n grids: one shape for all, chosen with the chunk
+// depth by the cost above from ncand candidates; `rounds` > 0 sets each grid's
+// chunk count to that many rounds of the device instead.  Returns the shape.
+int plan_maps(const StepGrid *const *grids, const int *rounds, int n, const Candidate *cand,
+              int ncand, TileMap *maps) {
+  bool fixed = false;
+  int deepest = 1;
+  for (int i = 0; i < n; ++i) {
+    fixed = fixed || rounds[i] > 0;
+    deepest = std::max(deepest, grids[i]->nz);
   }
-  if (illum) WFD_AM(false, true);
-  WFD_AM(false, false);
-#undef WFD_AM
+  const Candidate *best = &cand[0];
+  int best_zc = deepest;
+  double best_cost = 1e300;
+  for (int k = 0; k < ncand; ++k)
+    for (int nch = 1; nch <= (deepest + kMinZc - 1) / kMinZc; ++nch) {
+      const int zc = (deepest + nch - 1) / nch;
+      if ((deepest + zc - 1) / zc != nch) continue;  // same chunks as a smaller count
+      int64_t blocks = 0;
+      for (int i = 0; i < n; ++i) blocks += tiles_of(*grids[i], cand[k]) * ((grids[i]->nz + zc - 1) / zc);
+      const double cost = launch_cost(cand[k], blocks, zc);
+      if (cost < 0.98 * best_cost) {
+        best_cost = cost;
+        best = &cand[k];
+        best_zc = zc;
+      }
+    }
+  const int64_t slots = (int64_t)best->per_cu * device_cus();
+  for (int i = 0; i < n; ++i) {
+    const int64_t tiles = tiles_of(*grids[i], *best);
+    const int nch = rounds[i] > 0 ? (int)((rounds[i] * slots + tiles / 2) / tiles)
+                                  : (grids[i]->nz + best_zc - 1) / best_zc;
+    maps[i] = map_of(*grids[i], *best, nch);
+  }
+  return best->shape;
 }
 
-template <int V>
-int adj_map(const StepGrid &g, const Tuning &tu, bool illum, int min_zc, TileMap *map) {
-  using S = AdjShape<V>;
-  using T = Tile<S::RY, S::NW, S::NI>;
-  const bool vd = g.m2 != nullptr, fs = g.zs != kNoSurface;
-  int per_cu;
-#define WFD_PC(VD_, IL_, FS_) \
-  blocks_per_cu(k_adjoint<S::RY, S::NW, S::NI, S::DL, VD_, IL_, FS_>, T::NTHREADS)
-  if (vd)
-    per_cu = illum ? (fs ? WFD_PC(true, true, true) : WFD_PC(true, true, false))
-                   : (fs ? WFD_PC(true, false, true) : WFD_PC(true, false, false));
-  else
-    per_cu = illum ? (fs ? WFD_PC(false, true, true) : WFD_PC(false, true, false))
-                   : (fs ? WFD_PC(false, false, true) : WFD_PC(false, false, false));
-#undef WFD_PC
-  *map = make_map(g, T::TX, T::TY, per_cu, 0, tu.adj_rounds, kAdjHalo, min_zc);
-  return map->nblocks;
+// Streaming hints keep single-use data out of the 256 MB last-level cache; a
+// step whose volumes all fit it runs faster without them, since the next step
+// finds its operands there: 144^3 VD 23.7 -> 20.5 us, 233 x 247 x 201 VD (185
+// MB) 53.7 -> 46.2, 250 x 250 x 240 VD (240 MB) 61.2 -> 52.2; 270 x 260 x 250
+// (281 MB) is even and 296^3 (415 MB) loses, 105 -> 118.  An adjoint step's stored
+// state w^m comes from memory all the same: 24 windows (175 MB) 99 -> 92 us, 240 x
+// 240 x 200 with illumination (276 MB) 85 -> 88.
+constexpr double kCachedBytes = 256e6;
+
+bool step_streams(const StepGrid *const *grids, int n, int volumes) {
+  double bytes = 0.0;
+  for (int i = 0; i < n; ++i)
+    bytes += 4.0 * volumes * (double)grids[i]->nx * grids[i]->ny * grids[i]->nz;
+  return bytes > kCachedBytes;
 }
 
 }  // namespace
 
-int adjoint_tile_map(const StepGrid &g, const Tuning &tu, bool illum, int min_zc, TileMap *map) {
-  switch (tu.adj_variant) {
-    case 1: return adj_map<1>(g, tu, illum, min_zc, map);
-    case 2: return adj_map<2>(g, tu, illum, min_zc, map);
-    case 3: return adj_map<3>(g, tu, illum, min_zc, map);
-    default: return adj_map<0>(g, tu, illum, min_zc, map);
+StepPlan plan_forward(const StepGrid *const *grids, const Tuning *const *tu, int n,
+                      bool out_of_place, TileMap *maps) {
+  bool vd = false, fs = false, tuned = false;
+  std::vector<int> rounds(n);
+  for (int i = 0; i < n; ++i) {
+    vd = vd || grids[i]->m2;
+    fs = fs || grids[i]->zs != kNoSurface;
+    rounds[i] = tu[i]->rounds;
+    tuned = tuned || rounds[i] > 0;
   }
+  StepPlan p;
+  p.stream = step_streams(grids, n, 3 + (vd ? 1 : 0) + (out_of_place ? 1 : 0));
+  Candidate c[2] = {forward_candidate(tu[0]->variant, vd, fs, p.stream), {}};
+  int nc = 1;
+  if (tu[0]->variant == 0 && !tuned) c[nc++] = forward_candidate(5, vd, fs, p.stream);
+  p.shape = plan_maps(grids, rounds.data(), n, c, nc, maps);
+  return p;
 }
 
-hipError_t launch_forward_pool(const GradWindow *wins, int nwin, int nblocks, int n, int cur_k,
-                               int prev_k, int out_k, int record, int variant, bool vd, bool fs,
+StepPlan plan_adjoint(const StepGrid *const *grids, const Tuning *const *tu, int n, bool illum,
+                      TileMap *maps) {
+  bool vd = false, fs = false, tuned = false;
+  std::vector<int> rounds(n);
+  for (int i = 0; i < n; ++i) {
+    vd = vd || grids[i]->m2;
+    fs = fs || grids[i]->zs != kNoSurface;
+    rounds[i] = tu[i]->adj_rounds;
+    tuned = tuned || rounds[i] > 0;
+  }
+  StepPlan p;
+  // psi^{m+1}, psi^m, w^m, g, k (m2, illumination)
+  p.stream = step_streams(grids, n, 5 + (vd ? 1 : 0) + (illum ? 1 : 0));
+  Candidate c[3] = {adjoint_candidate(tu[0]->adj_variant, vd, illum, fs, p.stream), {}, {}};
+  int nc = 1;
+  if (tu[0]->adj_variant == 0 && !tuned) {
+    c[nc++] = adjoint_candidate(3, vd, illum, fs, p.stream);
+    c[nc++] = adjoint_candidate(4, vd, illum, fs, p.stream);
+  }
+  p.shape = plan_maps(grids, rounds.data(), n, c, nc, maps);
+  return p;
+}
+
+hipError_t launch_forward_step(const StepPlan &plan, const TileMap &map, const StepGrid &g,
+                               const float *cur, const float *prev, float *out, const Source &src,
+                               int n, const RecTable *rec, const float *rec_scale, float *seis_tm,
                                hipStream_t stream) {
-#define WFD_FP(V)                                                                              \
-  return vd ? (fs ? fwd_pool_launch<V, true, true>(wins, nwin, nblocks, n, cur_k, prev_k, out_k, \
-                                                   record, stream)                             \
-                  : fwd_pool_launch<V, true, false>(wins, nwin, nblocks, n, cur_k, prev_k,     \
-                                                    out_k, record, stream))                    \
-            : (fs ? fwd_pool_launch<V, false, true>(wins, nwin, nblocks, n, cur_k, prev_k,     \
-                                                    out_k, record, stream)                     \
-                  : fwd_pool_launch<V, false, false>(wins, nwin, nblocks, n, cur_k, prev_k,    \
-                                                     out_k, record, stream))
-  switch (variant) {
-    case 1: WFD_FP(1);
-    case 2: WFD_FP(2);
-    case 3: WFD_FP(3);
-    case 4: WFD_FP(4);
-    default: WFD_FP(0);
-  }
-#undef WFD_FP
-}
-
-hipError_t launch_adjoint_multi(const GradWindow *wins, int nwin, int nblocks, int m, int parity,
-                                int wm_k, int adj_variant, bool vd, bool illum, bool fs,
-                                hipStream_t stream) {
-  switch (adj_variant) {
-    case 1: return adj_multi_dispatch<1>(wins, nwin, nblocks, m, parity, wm_k, vd, illum, fs, stream);
-    case 2: return adj_multi_dispatch<2>(wins, nwin, nblocks, m, parity, wm_k, vd, illum, fs, stream);
-    case 3: return adj_multi_dispatch<3>(wins, nwin, nblocks, m, parity, wm_k, vd, illum, fs, stream);
-    default: return adj_multi_dispatch<0>(wins, nwin, nblocks, m, parity, wm_k, vd, illum, fs, stream);
-  }
-}
-
-hipError_t launch_forward_step(const StepGrid &g, const float *cur, const float *prev, float *out,
-                               const Source &src, int n, const RecTable *rec,
-                               const float *rec_scale, float *seis_tm, const Tuning &tu,
-                               hipStream_t stream) {
-  const bool vd = g.m2 != nullptr, fs = g.zs != kNoSurface;
   const RecTable none{};
   const RecTable &r = rec ? *rec : none;
   float *rec_out = rec ? seis_tm : nullptr;
-#define WFD_FWD1(V, VD_)                                                                     \
-  (fs ? fwd_launch<V, VD_, true>(g, cur, prev, out, src, n, r, rec_scale, rec_out, tu, stream) \
-      : fwd_launch<V, VD_, false>(g, cur, prev, out, src, n, r, rec_scale, rec_out, tu, stream))
-#define WFD_FWD(V) return vd ? WFD_FWD1(V, true) : WFD_FWD1(V, false)
-  switch (tu.variant) {
-    case 1: WFD_FWD(1);
-    case 2: WFD_FWD(2);
-    case 3: WFD_FWD(3);
-    case 4: WFD_FWD(4);
-    default: WFD_FWD(0);
-  }
-#undef WFD_FWD
-#undef WFD_FWD1
+  return with_forward(plan.shape, g.m2 != nullptr, g.zs != kNoSurface, plan.stream,
+                      [&](auto S, auto VD, auto FS, auto NT) {
+    using Sh = decltype(S);
+    hipLaunchKernelGGL((k_forward<TileOf<Sh>, decltype(VD)::value, decltype(FS)::value,
+                                  decltype(NT)::value>),
+                       dim3(map.nblocks), dim3(Sh::NTHREADS), 0, stream, g, cur, prev, out, src, n,
+                       r, rec_scale, rec_out, map);
+    return hipGetLastError();
+  });
 }
 
-int forward_tile_map(const StepGrid &g, const Tuning &tu, int min_zc, TileMap *map) {
-  const bool vd = g.m2 != nullptr, fs = g.zs != kNoSurface;
-  int tx = 64, ty = 16, per_cu = 4;
-#define WFD_PCU(V)                                                                 \
-  tx = FwdTile<V>::TX;                                                              \
-  ty = FwdTile<V>::TY;                                                              \
-  per_cu = (vd ? (fs ? fwd_per_cu<V, true, true>() : fwd_per_cu<V, true, false>())  \
-               : (fs ? fwd_per_cu<V, false, true>() : fwd_per_cu<V, false, false>()))
-  switch (tu.variant) {
-    case 1: WFD_PCU(1); break;
-    case 2: WFD_PCU(2); break;
-    case 3: WFD_PCU(3); break;
-    case 4: WFD_PCU(4); break;
-    default: WFD_PCU(0); break;
-  }
-#undef WFD_PCU
-  *map = make_map(g, tx, ty, per_cu, 0, tu.rounds, kFwdHalo, min_zc);
-  return map->nblocks;
+hipError_t launch_forward_multi(const StepPlan &plan, const WindowStep *wins, int nwin,
+                                int nblocks, int n, bool vd, bool fs, hipStream_t stream) {
+  return with_forward(plan.shape, vd, fs, plan.stream, [&](auto S, auto VD, auto FS, auto NT) {
+    using Sh = decltype(S);
+    hipLaunchKernelGGL((k_forward_multi<TileOf<Sh>, decltype(VD)::value, decltype(FS)::value,
+                                        decltype(NT)::value>),
+                       dim3(nblocks), dim3(Sh::NTHREADS), 0, stream, wins, nwin, n);
+    return hipGetLastError();
+  });
 }
 
-hipError_t launch_forward_multi(const WindowStep *wins, int nwin, int nblocks, int n, int variant,
-                                bool vd, bool fs, hipStream_t stream) {
-#define WFD_MULTI(V)                                                                       \
-  return vd ? (fs ? fwd_multi_launch<V, true, true>(wins, nwin, nblocks, n, stream)         \
-                  : fwd_multi_launch<V, true, false>(wins, nwin, nblocks, n, stream))       \
-            : (fs ? fwd_multi_launch<V, false, true>(wins, nwin, nblocks, n, stream)        \
-                  : fwd_multi_launch<V, false, false>(wins, nwin, nblocks, n, stream))
-  switch (variant) {
-    case 1: WFD_MULTI(1);
-    case 2: WFD_MULTI(2);
-    case 3: WFD_MULTI(3);
-    case 4: WFD_MULTI(4);
-    default: WFD_MULTI(0);
-  }
-#undef WFD_MULTI
+hipError_t launch_forward_pool(const StepPlan &plan, const GradWindow *wins, int nwin, int nblocks,
+                               int n, int cur_k, int prev_k, int out_k, int record, bool vd,
+                               bool fs, hipStream_t stream) {
+  return with_forward(plan.shape, vd, fs, plan.stream, [&](auto S, auto VD, auto FS, auto NT) {
+    using Sh = decltype(S);
+    hipLaunchKernelGGL((k_forward_pool<TileOf<Sh>, decltype(VD)::value, decltype(FS)::value,
+                                       decltype(NT)::value>),
+                       dim3(nblocks), dim3(Sh::NTHREADS), 0, stream, wins, nwin, n, cur_k, prev_k,
+                       out_k, record);
+    return hipGetLastError();
+  });
 }
 
-hipError_t launch_adjoint_step(const Tuning &tu, const StepGrid &g, const float *cur,
-                               const float *prev, float *out, const RecTable &rec,
-                               const float *res_tm, int m, const float *wm, float *grad,
-                               const IllumOut &illum, hipStream_t stream) {
-  switch (tu.adj_variant) {
-    case 1: return adj_dispatch<1>(tu, g, cur, prev, out, rec, res_tm, m, wm, grad, illum, stream);
-    case 2: return adj_dispatch<2>(tu, g, cur, prev, out, rec, res_tm, m, wm, grad, illum, stream);
-    case 3: return adj_dispatch<3>(tu, g, cur, prev, out, rec, res_tm, m, wm, grad, illum, stream);
-    default: return adj_dispatch<0>(tu, g, cur, prev, out, rec, res_tm, m, wm, grad, illum, stream);
-  }
+hipError_t launch_adjoint_step(const StepPlan &plan, const TileMap &map, const StepGrid &g,
+                               const float *cur, const float *prev, float *out,
+                               const RecTable &rec, const float *res_tm, int m, const float *wm,
+                               float *grad, const IllumOut &illum, hipStream_t stream) {
+  return with_adjoint(plan.shape, g.m2 != nullptr, illum.p != nullptr, g.zs != kNoSurface,
+                      plan.stream, [&](auto S, auto VD, auto IL, auto FS, auto NT) {
+    using Sh = decltype(S);
+    hipLaunchKernelGGL((k_adjoint<TileOf<Sh>, Sh::DL, decltype(VD)::value, decltype(IL)::value,
+                                  decltype(FS)::value, decltype(NT)::value>),
+                       dim3(map.nblocks), dim3(Sh::NTHREADS), 0, stream, g, cur, prev, out, rec,
+                       res_tm, m, wm, grad, illum, map);
+    return hipGetLastError();
+  });
+}
+
+hipError_t launch_adjoint_multi(const StepPlan &plan, const GradWindow *wins, int nwin,
+                                int nblocks, int m, int parity, int wm_k, bool vd, bool illum,
+                                bool fs, hipStream_t stream) {
+  return with_adjoint(plan.shape, vd, illum, fs, plan.stream,
+                      [&](auto S, auto VD, auto IL, auto FS, auto NT) {
+    using Sh = decltype(S);
+    hipLaunchKernelGGL((k_adjoint_multi<TileOf<Sh>, Sh::DL, decltype(VD)::value,
+                                        decltype(IL)::value, decltype(FS)::value,
+                                        decltype(NT)::value>),
+                       dim3(nblocks), dim3(Sh::NTHREADS), 0, stream, wins, nwin, m, parity, wm_k);
+    return hipGetLastError();
+  });
 }
 
 }  // namespace wfd
