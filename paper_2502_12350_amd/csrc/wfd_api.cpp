@@ -1483,7 +1483,7 @@ wfd_status wfd_batch_create(wfd_batch **out, int32_t nshot, wfd_ctx *const *ctxs
     d.seis_tm = nrec[i] > 0 ? w.seis_tm : nullptr;
     d.block_begin = offset;
     d.block_end = offset + nb;
-    offset += (nb + 7) / 8 * 8;
+    offset += nb;
     for (int p = 0; p < 2; ++p) {
       wfd::WindowStep e = d;
       e.cur = p == 0 ? w.W1 : w.W2;
@@ -1695,8 +1695,8 @@ wfd_status wfd_gbatch_create(wfd_gbatch **out, int32_t nshot, wfd_ctx *const *ct
     d.fblock_end = foff + nf;
     d.ablock_begin = aoff;
     d.ablock_end = aoff + na;
-    foff += (nf + 7) / 8 * 8;  // ranges start at multiples of 8: XCD-aware order
-    aoff += (na + 7) / 8 * 8;
+    foff += nf;
+    aoff += na;
     b->ctxs.push_back(c);
     b->model_gen.push_back(c->model_gen);
     b->work.push_back(w);

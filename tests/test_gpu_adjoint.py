@@ -363,3 +363,42 @@ def test_gradient_workload_grid_large_residual_matches_stored_oracle():
     assert e["dobs"] <= SEIS_TOL and e["seis"] <= SEIS_TOL and e["J"] <= SEIS_TOL
     assert e["illum"] <= SEIS_TOL
     assert max(e["norm"], e["sketch"], e["z60"], e["y100"]) <= GRAD_TOL
+
+
+@pytest.mark.parametrize("n,N,fs", [((1, 6, 5), 7, False), ((5, 1, 9), 6, False),
+                                    ((2, 2, 3), 5, True), ((70, 3, 2), 4, False),
+                                    ((64, 18, 20), 70, False)])
+def test_gradient_fold_edges_match_oracle(n, N, fs):
+    # the fold of the padded gradient onto models one to three cells thick (a
+    # cell both first and last of its axis), with a border longer than a
+    # wavefront, and several inner rows per block
+    torch = gpu_or_skip()
+    from paper_2502_12350_amd import GridSpec, Propagator
+    nx, ny, nz = n
+    nt, h = 24, 10.0
+    rng = np.random.default_rng(3)
+    vel = (2000.0 + 1000.0 * rng.random((nz, ny, nx))).astype(np.float32)
+    dt = 0.4 * h / 3000.0
+    t = np.arange(nt) * dt
+    a = (np.pi * 40.0 * (t - 0.02)) ** 2
+    wav = ((1 - 2 * a) * np.exp(-a)).astype(np.float32)
+    # near the low x end, or the high one for the long border, so that the wave is
+    # at the receivers and in the border within the 24 steps
+    end, out = (nx - 1, -1) if N > 64 else (0, 1)
+    src = [(end + out * min(2, nx - 1)) * h, ny // 2 * h, min(2, nz - 1) * h]
+    rec = np.array([[h * end, h * (ny // 2), h * min(3, nz - 1)],
+                    [h * (end + out * min(5, nx - 1)), h * min(ny // 2 + 3, ny - 1), 0]])
+    g = oracle.Grid(nx, ny, nz, h, h, h, border=N, dt=dt, nt=nt)
+    g.free_surface = fs
+    dobs = (0.5 * oracle.forward(g, vel, None, wav, src, rec).seis).astype(np.float32)
+    ref = oracle.gradient(g, vel, None, wav, src, rec, dobs)
+    P = Propagator(0)
+    P.set_model(GridSpec(nx, ny, nz, h, h, h, border=N, dt=dt, nt=nt, free_surface=fs),
+                torch.from_numpy(vel).cuda())
+    J, gr = P.gradient(torch.from_numpy(wav).cuda(), src, rec, torch.from_numpy(dobs).cuda(),
+                       ckpt="full")
+    torch.cuda.synchronize()
+    e = rel_l2(gr.cpu().numpy(), ref.grad)
+    say(f"[fold] model {n} border {N}: gradient rel-L2 {e:.2e}")
+    assert e <= 1e-3
+    assert abs(float(J.item()) - ref.misfit) <= 1e-4 * ref.misfit

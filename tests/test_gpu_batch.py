@@ -386,3 +386,40 @@ def test_gradient_batch_graph_replays_match_eager():
         torch.cuda.synchronize()
         assert bool(torch.isfinite(x).all())
     b.close()
+
+
+@pytest.mark.parametrize("n,N", [((24, 40, 30), 4), ((25, 17, 50), 8), ((86, 30, 20), 5),
+                                 ((118, 70, 40), 5), ((61, 125, 25), 9)])
+def test_planned_launches_equal_fixed_tiles_bitwise(n, N):
+    # the planner's shapes (32-wide tiles where a 64-wide one would be mostly
+    # empty, chunks in whole rounds, no streaming hints at these sizes), shot by
+    # shot and batched, against 64 x 8 tiles with a fixed number of rounds
+    torch = gpu_or_skip()
+    from paper_2502_12350_amd import GradientBatch, GridSpec, Propagator
+    nx, ny, nz = n
+    nt, h = 40, 10.0
+    vel = seisgen.layered_model(5, n, 0.05)
+    rho = seisgen.gardner_density(vel)
+    dt = 0.4 * h / float(vel.max())
+    t = np.arange(nt) * dt
+    a = (np.pi * 30.0 * (t - 0.03)) ** 2
+    wav = torch.from_numpy(((1 - 2 * a) * np.exp(-a)).astype(np.float32)).cuda()
+    src = np.array([[nx // 2 * h, ny // 2 * h, 5 * h]])
+    rec = np.array([[h * i, h * j, 3 * h] for i in range(0, nx, 5) for j in range(0, ny, 4)])
+    dobs = torch.randn((len(rec), nt), generator=torch.Generator().manual_seed(1)).cuda() * 1e-12
+    gs = GridSpec(nx, ny, nz, h, h, h, border=N, dt=dt, nt=nt)
+
+    def prop():
+        P = Propagator(0)
+        P.set_model(gs, torch.from_numpy(vel).cuda(), torch.from_numpy(rho).cuda())
+        return P
+
+    say(f"[plan] model {n} border {N}")
+    ref = prop()
+    ref.set_tuning(2, 3, 2, 2)
+    Jr, gr, sr = ref.gradient(wav, src, rec, dobs, ckpt=("revolve", 4), seis=True)
+    J, g, s = prop().gradient(wav, src, rec, dobs, ckpt=("revolve", 4), seis=True)
+    assert torch.equal(s, sr) and torch.equal(g, gr) and float(J) == float(Jr)
+    m, gb = GradientBatch([prop() for _ in range(3)], wav, [src] * 3, [rec] * 3, [dobs] * 3, 4).run()
+    for i in range(3):
+        assert torch.equal(gb[i], gr) and float(m[i]) == float(Jr)
