@@ -317,7 +317,7 @@ std::vector<float> sponge_table(int n, int border, bool free_top = false) {
 // Workspace layout for one shot.
 struct Work {
   // receiver tables (uploaded)
-  int *col_start, *ent_z, *ent_rp, *perm, *rec_model_idx;
+  int *col_start, *ent_z, *ent_rp, *slot, *rec_model_idx;
   int64_t *rec_idx;
   // device-computed scalars / scales
   wfd::ShotScale *scale;  // sigma 2^e and the field exponent e
@@ -418,7 +418,7 @@ Work work_layout(const wfd_ctx *c, int nrec, WorkKind kind, const wfd_ckpt *ck, 
   w.col_start = cv.take<int>((size_t)ncol + 1);
   w.ent_z = cv.take<int>((size_t)std::max(nrec, 1));
   w.ent_rp = cv.take<int>((size_t)nrec + 1);
-  w.perm = cv.take<int>((size_t)std::max(nrec, 1));
+  w.slot = cv.take<int>((size_t)std::max(nrec, 1));
   w.rec_model_idx = cv.take<int>((size_t)std::max(nrec, 1));
   w.rec_idx = cv.take<int64_t>((size_t)std::max(nrec, 1));
   w.scale = cv.take<wfd::ShotScale>(1);
@@ -513,7 +513,7 @@ wfd_status prepare_shot(wfd_ctx *c, const float *wavelet, const double src_xyz[3
     return a.col != b.col ? a.col < b.col : a.z < b.z;
   });
   const int ncol = c->Nx * c->Ny;
-  std::vector<int> col_start((size_t)ncol + 1, 0), ent_z, ent_rp, perm;
+  std::vector<int> col_start((size_t)ncol + 1, 0), ent_z, ent_rp, slot((size_t)nrec);
   ent_rp.push_back(0);
   std::vector<int> ent_col;
   for (size_t i = 0; i < sorted.size(); ++i) {
@@ -522,7 +522,7 @@ wfd_status prepare_shot(wfd_ctx *c, const float *wavelet, const double src_xyz[3
       ent_z.push_back(sorted[i].z);
       ent_col.push_back(sorted[i].col);
     }
-    perm.push_back(sorted[i].id);
+    slot[(size_t)sorted[i].id] = (int)i;
   }
   if (!sorted.empty()) ent_rp.push_back((int)sorted.size());
   // col_start: first entry of each column
@@ -562,7 +562,7 @@ wfd_status prepare_shot(wfd_ctx *c, const float *wavelet, const double src_xyz[3
   }
   HIP_TRY(up(w.ent_z, ent_z.data(), n_ent * sizeof(int)));
   HIP_TRY(up(w.ent_rp, ent_rp.data(), ent_rp.size() * sizeof(int)));
-  HIP_TRY(up(w.perm, perm.data(), perm.size() * sizeof(int)));
+  HIP_TRY(up(w.slot, slot.data(), slot.size() * sizeof(int)));
   HIP_TRY(up(w.rec_model_idx, rmodel.data(), rmodel.size() * sizeof(int)));
   HIP_TRY(up(w.rec_idx, ridx.data(), ridx.size() * sizeof(int64_t)));
   HIP_TRY(hipEventRecord(c->upload_done, c->stream));
@@ -583,9 +583,31 @@ wfd::RecTable rec_table(const Work &w, int nrec) {
   t.col_start = w.col_start;
   t.ent_z = w.ent_z;
   t.ent_rp = w.ent_rp;
-  t.perm = w.perm;
   t.nrec = nrec;
   return t;
+}
+
+wfd::Source source_of(const wfd_ctx *c, int64_t idx, const Work &w, const float *wavelet) {
+  return wfd::Source{(int)(idx / c->plane), (uint32_t)(idx % c->plane * 4), &w.scale->sigma,
+                     wavelet};
+}
+
+wfd::Record record_of(const Work &w, int nrec) {
+  return wfd::Record{w.rec_idx, w.rec_scale, nrec};
+}
+
+// Row of sample n in the recorded traces (nullptr: nothing to record).
+float *sample_row(const Work &w, int nrec, int n) {
+  return nrec > 0 && n >= 0 ? w.seis_tm + (size_t)n * (size_t)nrec : nullptr;
+}
+
+// The last sample of a forward sweep, from its final state.
+wfd_status record_last(wfd_ctx *c, const Work &w, int nrec, const float *field) {
+  if (nrec == 0) return WFD_OK;
+  Timed t(c, WFD_K_OTHER);
+  HIP_TRY(wfd::launch_record(field, w.rec_idx, w.rec_scale, nrec, c->grid.nt - 1, w.seis_tm,
+                             c->stream));
+  return WFD_OK;
 }
 
 wfd_status zero(wfd_ctx *c, float *p, int64_t n) {
@@ -835,16 +857,14 @@ namespace {
 
 // The CPML layer's share of forward step n (after the step kernel wrote out
 // from cur): memory variables, the correction k C added to out, C kept in
-// cstore when given, and the receivers read from out afterwards.
+// cstore when given.
 wfd_status cpml_forward_terms(wfd_ctx *c, const wfd::StepGrid &g, const Work &w,
-                              const float *cur, float *out, float *cstore, int nrec, int n,
+                              const float *cur, float *out, float *cstore,
                               float *const *mem = nullptr) {
   Timed t(c, WFD_K_OTHER);
   float *const *m = mem ? mem : w.mem;  // out == nullptr: only the memory variables and C
   HIP_TRY(wfd::launch_cpml_forward(g, c->cpml_tab, c->shell, cur, m, out,
                                    cstore ? cstore : w.lastc, cstore != nullptr, c->stream));
-  if (nrec > 0 && out)
-    HIP_TRY(wfd::launch_record(out, w.rec_idx, w.rec_scale, nrec, n, w.seis_tm, c->stream));
   return WFD_OK;
 }
 
@@ -883,8 +903,8 @@ wfd_status forward_core(wfd_ctx *c, const float *wavelet, const double src_xyz[3
   if ((s = zero(c, w.W1, c->vol)) != WFD_OK) return s;
   if ((s = zero(c, w.W2, c->vol)) != WFD_OK) return s;
   const wfd::StepGrid g = step_grid(c);
-  const wfd::RecTable rt = rec_table(w, nrec);
-  const wfd::Source src{src_idx, &w.scale->sigma, wavelet};
+  const wfd::Record rec = record_of(w, nrec);
+  const wfd::Source src = source_of(c, src_idx, w, wavelet);
   if (c->cpml)
     for (int i = 0; i < 6; ++i)
       if ((s = zero(c, w.mem[i], mem_len(c, i))) != WFD_OK) return s;
@@ -896,14 +916,14 @@ wfd_status forward_core(wfd_ctx *c, const float *wavelet, const double src_xyz[3
   for (int n = 0; n < c->grid.nt; ++n) {
     {
       Timed t(c, WFD_K_FORWARD);
-      HIP_TRY(wfd::launch_forward_step(plan, map, g, cur, prev, prev, src, n,
-                                       (nrec > 0 && !c->cpml) ? &rt : nullptr, w.rec_scale,
-                                       w.seis_tm, c->stream));
+      HIP_TRY(wfd::launch_forward_step(plan, map, g, cur, prev, prev, src, n, rec,
+                                       sample_row(w, nrec, n - 1), c->stream));
     }
-    if (c->cpml && (s = cpml_forward_terms(c, g, w, cur, prev, nullptr, nrec, n)) != WFD_OK)
+    if (c->cpml && (s = cpml_forward_terms(c, g, w, cur, prev, nullptr)) != WFD_OK)
       return s;
     std::swap(cur, prev);
   }
+  if ((s = record_last(c, w, nrec, cur)) != WFD_OK) return s;
   if (nrec > 0 && seis) {
     Timed t(c, WFD_K_OTHER);
     HIP_TRY(wfd::launch_transpose(w.seis_tm, seis, nrec, c->grid.nt, c->stream));
@@ -912,7 +932,7 @@ wfd_status forward_core(wfd_ctx *c, const float *wavelet, const double src_xyz[3
     int np = 0;
     {
       Timed t(c, WFD_K_OTHER);
-      HIP_TRY(wfd::launch_residual(w.seis_tm, dobs, w.rec_adj, w.scale, nrec, c->grid.nt,
+      HIP_TRY(wfd::launch_residual(w.seis_tm, dobs, w.rec_adj, w.slot, w.scale, nrec, c->grid.nt,
                                    w.res_tm, w.partial, &np, c->stream));
     }
     Timed t(c, WFD_K_OTHER);
@@ -1010,7 +1030,7 @@ wfd_status wfd_gradient_ex(wfd_ctx *c, const float *wavelet, const double src_xy
   const int nt = c->grid.nt;
   const wfd::StepGrid g = step_grid(c);
   const wfd::RecTable rt = rec_table(w, nrec);
-  const wfd::Source src{src_idx, &w.scale->sigma, wavelet};
+  const wfd::Source src = source_of(c, src_idx, w, wavelet);
   const wfd::IllumOut il{illum, c->grid.border, c->grid.nx, c->grid.ny, c->grid.nz, w.scale,
                          out_exp2};
   if (field_exp2) {
@@ -1036,7 +1056,7 @@ wfd_status wfd_gradient_ex(wfd_ctx *c, const float *wavelet, const double src_xy
     int np = 0;
     {
       Timed t(c, WFD_K_OTHER);
-      HIP_TRY(wfd::launch_residual(w.seis_tm, dobs, w.rec_adj, w.scale, nrec, nt, w.res_tm,
+      HIP_TRY(wfd::launch_residual(w.seis_tm, dobs, w.rec_adj, w.slot, w.scale, nrec, nt, w.res_tm,
                                    w.partial, &np, c->stream));
     }
     {
@@ -1068,18 +1088,16 @@ wfd_status wfd_gradient_ex(wfd_ctx *c, const float *wavelet, const double src_xy
   auto fwd = [&](const float *cur, const float *prev, float *out, int n, bool rec) -> wfd_status {
     {
       Timed t(c, WFD_K_FORWARD);
-      HIP_TRY(wfd::launch_forward_step(fplan, fmap, g, cur, prev, out, src, n,
-                                       (rec && nrec > 0 && !c->cpml) ? &rt : nullptr, w.rec_scale,
-                                       w.seis_tm, c->stream));
+      HIP_TRY(wfd::launch_forward_step(fplan, fmap, g, cur, prev, out, src, n, record_of(w, nrec),
+                                       rec ? sample_row(w, nrec, n - 1) : nullptr, c->stream));
     }
     if (c->cpml) {  // full storage keeps every step's C; checkpointing the latest
       float *cst = w.cstore ? w.cstore + (size_t)n * (size_t)c->shell.points
                             : w.lastc;
-      if ((s = cpml_forward_terms(c, g, w, cur, out, cst, rec ? nrec : 0, n)) != WFD_OK)
-        return s;
+      if ((s = cpml_forward_terms(c, g, w, cur, out, cst)) != WFD_OK) return s;
       last_c_step = n;
     }
-    return WFD_OK;
+    return rec && n == nt - 1 ? record_last(c, w, nrec, out) : WFD_OK;
   };
 
   if (ck->mode == WFD_CKPT_FULL) {
@@ -1252,13 +1270,13 @@ wfd_status wfd_gradient_ex(wfd_ctx *c, const float *wavelet, const double src_xy
           if (last_c_step == a) {
             corr = w.lastc;
           } else if (cur_state == a) {
-            if ((s = cpml_forward_terms(c, g, w, buf[cur], nullptr, w.visitc, 0, a)) != WFD_OK)
+            if ((s = cpml_forward_terms(c, g, w, buf[cur], nullptr, w.visitc)) != WFD_OK)
               return s;
             corr = w.visitc;
           } else if (Slot *sl = slot_of(a)) {
             const auto m = slot_mem((size_t)(sl - slots.data()));
-            if ((s = cpml_forward_terms(c, g, w, buf[sl->a], nullptr, w.visitc, 0, a,
-                                        m.data())) != WFD_OK)
+            if ((s = cpml_forward_terms(c, g, w, buf[sl->a], nullptr, w.visitc, m.data())) !=
+                WFD_OK)
               return s;
             corr = w.visitc;
           } else {
@@ -1338,8 +1356,8 @@ wfd_status wfd_autotune(wfd_ctx *c, int32_t steps, void *work, size_t work_bytes
     return s;
   const wfd::StepGrid g = step_grid(c);
   const wfd::RecTable rt = rec_table(w, 0);
-  // index -1 matches no point: nothing is injected (the pointers stay valid)
-  const wfd::Source none_src{-1, &w.scale->sigma, &w.scale->sigma};
+  // plane -1 matches no point: nothing is injected (the pointers stay valid)
+  const wfd::Source none_src{-1, 0, &w.scale->sigma, &w.scale->sigma};
   hipEvent_t e0, e1;
   HIP_TRY(hipEventCreate(&e0));
   if (hipEventCreate(&e1) != hipSuccess) {
@@ -1362,8 +1380,8 @@ wfd_status wfd_autotune(wfd_ctx *c, int32_t steps, void *work, size_t work_bytes
       wfd::TileMap map;
       const wfd::StepPlan plan = wfd::plan_forward(&pg, &pt, 1, false, &map);
       err = time_steps(c, steps, e0, e1, [&] {
-        hipError_t e = wfd::launch_forward_step(plan, map, g, cur, prev, prev, none_src, 0, nullptr,
-                                                nullptr, nullptr, c->stream);
+        hipError_t e = wfd::launch_forward_step(plan, map, g, cur, prev, prev, none_src, 0,
+                                                wfd::Record{}, nullptr, c->stream);
         std::swap(cur, prev);
         return e;
       }, &ms);
@@ -1476,11 +1494,10 @@ wfd_status wfd_batch_create(wfd_batch **out, int32_t nshot, wfd_ctx *const *ctxs
     wfd::WindowStep d{};
     d.g = grids[(size_t)i];
     d.map = maps[(size_t)i];
-    const int nb = d.map.nblocks;
-    d.src = wfd::Source{src_idx, &w.scale->sigma, wavelet};
-    d.rec = rec_table(w, nrec[i]);
-    d.rec_scale = w.rec_scale;
-    d.seis_tm = nrec[i] > 0 ? w.seis_tm : nullptr;
+    const int nb = wfd::window_blocks(d.map, nrec[i]);
+    d.src = source_of(c, src_idx, w, wavelet);
+    d.rec = record_of(w, nrec[i]);
+    d.seis_tm = w.seis_tm;
     d.block_begin = offset;
     d.block_end = offset + nb;
     offset += nb;
@@ -1529,6 +1546,9 @@ wfd_status batch_enqueue(wfd_batch *b) {
     HIP_TRY(wfd::launch_forward_multi(b->plan, b->d_wins[n & 1], nwin, b->nblocks, n, b->vd,
                                       b->fs, b->stream));
   }
+  HIP_TRY(wfd::launch_record_windows(b->d_wins[b->nt & 1], nwin,
+                                     *std::max_element(b->nrec.begin(), b->nrec.end()), b->nt - 1,
+                                     b->stream));
   for (int i = 0; i < nwin; ++i)
     if (b->nrec[i] > 0)
       HIP_TRY(wfd::launch_transpose(b->seis_tm[i], b->seis_out[i], b->nrec[i], b->nt, b->stream));
@@ -1676,10 +1696,10 @@ wfd_status wfd_gbatch_create(wfd_gbatch **out, int32_t nshot, wfd_ctx *const *ct
     d.g = grids[(size_t)i];
     d.fmap = fmaps[(size_t)i];
     d.amap = amaps[(size_t)i];
-    const int nf = d.fmap.nblocks, na = d.amap.nblocks;
-    d.src = wfd::Source{src_idx, &w.scale->sigma, wavelet};
+    const int nf = wfd::window_blocks(d.fmap, nrec[i]), na = d.amap.nblocks;
+    d.src = source_of(c, src_idx, w, wavelet);
     d.rec = rec_table(w, nrec[i]);
-    d.rec_scale = w.rec_scale;
+    d.out = record_of(w, nrec[i]);
     d.seis_tm = w.seis_tm;
     d.res_tm = w.res_tm;
     d.W1 = w.W1;
@@ -1782,6 +1802,9 @@ wfd_status gbatch_enqueue(wfd_gbatch *b) {
           HIP_TRY(wfd::launch_forward_pool(b->fplan, b->d_wins, nwin, b->fblocks, n, cur, prev,
                                            o, n >= reached ? 1 : 0, b->vd, b->fs, st));
         }
+        if (n == nt - 1 && n >= reached)
+          HIP_TRY(wfd::launch_record_pool(
+              b->d_wins, nwin, *std::max_element(b->nrec.begin(), b->nrec.end()), n, o, st));
         if (n >= reached) reached = n + 1;
         prev = cur;
         cur = o;
@@ -1803,7 +1826,7 @@ wfd_status gbatch_enqueue(wfd_gbatch *b) {
           const Work &w = b->work[(size_t)s];
           int np = 0;
           Timed t(c0, WFD_K_OTHER);
-          HIP_TRY(wfd::launch_residual(w.seis_tm, b->dobs[(size_t)s], w.rec_adj, w.scale,
+          HIP_TRY(wfd::launch_residual(w.seis_tm, b->dobs[(size_t)s], w.rec_adj, w.slot, w.scale,
                                        b->nrec[(size_t)s], nt, w.res_tm, w.partial, &np, st));
           HIP_TRY(wfd::launch_sum_partials(w.partial, np, b->misfit[(size_t)s], st));
         }

@@ -31,13 +31,20 @@ struct StepGrid {
 constexpr int kNoSurface = -(1 << 24);
 
 // Receivers grouped by (y, x) column of the padded grid.  Entry e is one
-// distinct receiver node at depth ent_z[e]; the receivers sharing it are
-// perm[ent_rp[e] .. ent_rp[e+1]).  col_start has Ny*Nx + 1 entries.
+// distinct receiver node at depth ent_z[e]; in the order of columns and depths,
+// the receivers sharing it are numbers ent_rp[e] .. ent_rp[e+1] - 1.  col_start
+// has Ny*Nx + 1 entries.
 struct RecTable {
   const int *col_start;
   const int *ent_z;
   const int *ent_rp;
-  const int *perm;
+  int nrec;
+};
+
+// Receivers as the recording gathers them: sample[r] = scale[r] w[idx[r]].
+struct Record {
+  const int64_t *idx;
+  const float *scale;
   int nrec;
 };
 
@@ -56,10 +63,11 @@ struct ShotScale {
 };
 constexpr int kMaxFieldExp = 120;  // |e| bound: 2^-120 sqrt(rho) stays a normal FP32
 
-// Source: padded node (linear index into a pitched volume), device scalar
-// sigma 2^e (the first member of the shot's ShotScale) and the wavelet.
+// Source: padded node (plane z and byte offset in it), device scalar sigma 2^e
+// (the first member of the shot's ShotScale) and the wavelet.
 struct Source {
-  int64_t idx;
+  int z;
+  uint32_t offset;
   const float *sigma;
   const float *wavelet;
 };
@@ -68,6 +76,7 @@ struct Source {
 // z split into nchunks chunks of zc planes.
 struct TileMap {
   int tiles_x, tiles_y, nchunks, zc, nblocks;
+  int spread;  // blocks in tile order, not a range of tiles per XCD
 };
 
 // Step-kernel tuning.  Tile shapes (rows per thread x wavefronts per block
@@ -96,8 +105,7 @@ struct WindowStep {
   const float *prev;
   float *out;
   Source src;
-  RecTable rec;
-  const float *rec_scale;
+  Record rec;
   float *seis_tm;
   int block_begin, block_end;
 };
@@ -120,9 +128,9 @@ struct GradWindow {
   TileMap fmap, amap;
   Source src;
   RecTable rec;
-  const float *rec_scale;
+  Record out;
   float *seis_tm;        // [nt][nrec] recorded traces
-  const float *res_tm;   // [nt][nrec] scaled residuals
+  const float *res_tm;   // [nt][nrec] scaled residuals, node by node
   float *W1, *W2, *store;
   int64_t vol;           // floats per pitched volume
   float *P1, *P2, *gimg;  // adjoint pair and imaging sum
@@ -145,15 +153,26 @@ StepPlan plan_forward(const StepGrid *const *grids, const Tuning *const *tu, int
 StepPlan plan_adjoint(const StepGrid *const *grids, const Tuning *const *tu, int n, bool illum,
                       TileMap *maps);
 
-// Kernel launchers; all enqueue on `stream` and return the launch status.
+// Kernel launchers; all enqueue on `stream` and return the launch status.  A
+// forward step n also records the receivers from cur = w^n, sample n - 1, into
+// row (nullptr: not); the sweep's last sample is recorded by launch_record.
 hipError_t launch_forward_step(const StepPlan &plan, const TileMap &map, const StepGrid &g,
                                const float *cur, const float *prev, float *out, const Source &src,
-                               int n, const RecTable *rec, const float *rec_scale, float *seis_tm,
-                               hipStream_t stream);
+                               int n, const Record &rec, float *row, hipStream_t stream);
 hipError_t launch_adjoint_step(const StepPlan &plan, const TileMap &map, const StepGrid &g,
                                const float *cur, const float *prev, float *out,
                                const RecTable &rec, const float *res_tm, int m, const float *wm,
                                float *grad, const IllumOut &illum, hipStream_t stream);
+
+// Blocks of a window's share of a batched forward launch: its tiles, then the
+// recording's.
+int window_blocks(const TileMap &map, int nrec);
+// The last sample n = nt - 1 of every window: from the current state of wins
+// (the descriptors of step nt), or from pool buffer cur_k.
+hipError_t launch_record_windows(const WindowStep *wins, int nwin, int nrec_max, int n,
+                                 hipStream_t stream);
+hipError_t launch_record_pool(const GradWindow *wins, int nwin, int nrec_max, int n, int cur_k,
+                              hipStream_t stream);
 
 // One step of every window in wins[0..nwin) (device array), nblocks blocks.
 // fs: some window has a free surface (selects the kernels with image loads).
@@ -161,7 +180,7 @@ hipError_t launch_forward_multi(const StepPlan &plan, const WindowStep *wins, in
                                 int nblocks, int n, bool vd, bool fs, hipStream_t stream);
 
 // Batched gradient: one forward step of every window (pool buffers cur_k,
-// prev_k -> out_k; receivers recorded when record != 0), and one adjoint step
+// prev_k -> out_k; sample n - 1 recorded when record != 0), and one adjoint step
 // of every window (psi^{m+1} in P1 for parity 0 else P2; w^m = pool buffer
 // wm_k).
 hipError_t launch_forward_pool(const StepPlan &plan, const GradWindow *wins, int nwin, int nblocks,
@@ -201,10 +220,11 @@ hipError_t launch_source_gradient(const float *psi, const float *k, int64_t src_
                                   const ShotScale *sc, int out_exp2, int m, float *wg,
                                   hipStream_t stream);
 
-// Residual + misfit: res_tm[n][r] = 2^e adj[r] (seis_tm[n][r] - dobs[r][n]),
+// Residual + misfit: res_tm[n][slot[r]] = 2^e adj[r] (seis_tm[n][r] - dobs[r][n])
+// (slot: the receivers' numbers node by node, as RecTable has them),
 // partial[b] = 1/2 sum (seis - dobs)^2 (FP64) per block; then misfit += sum partial.
 hipError_t launch_residual(const float *seis_tm, const float *dobs, const float *rec_adj,
-                           const ShotScale *sc, int nrec, int nt, float *res_tm, double *partial,
+                           const int *slot, const ShotScale *sc, int nrec, int nt, float *res_tm, double *partial,
                            int *n_partial, hipStream_t stream);
 int residual_partial_count(int nrec, int nt);
 hipError_t launch_sum_partials(const double *partial, int n, double *misfit, hipStream_t stream);

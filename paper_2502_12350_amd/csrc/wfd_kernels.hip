@@ -176,12 +176,13 @@ __global__ void k_source_gradient(const float *__restrict__ psi, const float *__
 
 constexpr int TT = 32;  // transpose tile
 
-// res_tm[n][r] = 2^e adj[r] (seis_tm[n][r] - dobs[r][n]) (the adjoint field
+// res_tm[n][slot[r]] = 2^e adj[r] (seis_tm[n][r] - dobs[r][n]) (the adjoint field
 // carries 2^e like the forward one); per-block 1/2 sum res^2 (physical).
 __global__ void __launch_bounds__(256)
     k_residual(const float *__restrict__ seis_tm, const float *__restrict__ dobs,
-               const float *__restrict__ adj, const ShotScale *__restrict__ sc, int nrec, int nt,
-               float *__restrict__ res_tm, double *__restrict__ partial) {
+               const float *__restrict__ adj, const int *__restrict__ slot,
+               const ShotScale *__restrict__ sc, int nrec, int nt, float *__restrict__ res_tm,
+               double *__restrict__ partial) {
   const int e = sc->e;
   __shared__ float tile[TT][TT + 1];
   const int r0 = blockIdx.y * TT, n0 = blockIdx.x * TT;
@@ -196,7 +197,7 @@ __global__ void __launch_bounds__(256)
     const int n = n0 + j, r = r0 + tx;
     if (r < nrec && n < nt) {
       const float res = seis_tm[(int64_t)n * nrec + r] - tile[tx][j];
-      res_tm[(int64_t)n * nrec + r] = ldexpf(adj[r] * res, e);
+      res_tm[(int64_t)n * nrec + slot[r]] = ldexpf(adj[r] * res, e);
       acc += 0.5 * (double)res * (double)res;
     }
   }
@@ -371,12 +372,12 @@ int residual_partial_count(int nrec, int nt) {
 }
 
 hipError_t launch_residual(const float *seis_tm, const float *dobs, const float *rec_adj,
-                           const ShotScale *sc, int nrec, int nt, float *res_tm, double *partial,
-                           int *n_partial, hipStream_t stream) {
+                           const int *slot, const ShotScale *sc, int nrec, int nt, float *res_tm,
+                           double *partial, int *n_partial, hipStream_t stream) {
   dim3 grid((nt + TT - 1) / TT, (nrec + TT - 1) / TT);
   *n_partial = (int)(grid.x * grid.y);
-  hipLaunchKernelGGL(k_residual, grid, dim3(TT, 8), 0, stream, seis_tm, dobs, rec_adj, sc, nrec,
-                     nt, res_tm, partial);
+  hipLaunchKernelGGL(k_residual, grid, dim3(TT, 8), 0, stream, seis_tm, dobs, rec_adj, slot, sc,
+                     nrec, nt, res_tm, partial);
   return hipGetLastError();
 }
 

@@ -1,17 +1,16 @@
 // Leapfrog step kernels for gfx950 (MI355X): the eighth-order 25-point star
 // (arXiv 2502.12350, §2.1) in a z-marching, LDS-tiled form.
 //
-// A block of NW wavefronts owns a TX x TY column tile of the padded grid
-// (TX = 64 NI, TY = NW RY) and a chunk of z planes: each thread holds NI
-// column groups (x = x0 + lane + 64 i) of RY consecutive rows, so every
-// global access is a 256-byte row segment per wavefront instruction.  Each
-// thread keeps, for each of its points, the nine z-neighbours in a register
-// queue; the current plane with a 4-cell x/y halo is staged in LDS
-// (double-buffered: one barrier per plane).  The next plane's queue entries
-// and pointwise streams are fetched one iteration ahead, the halo five planes
-// ahead through a register delay line (below).  Blocks are mapped XCD-aware:
-// the dispatcher places block b on XCD b mod 8, so each XCD receives a
-// contiguous range of tiles and neighbouring tiles share halos in one L2.
+// A block owns a TX x TY column tile of the padded grid (TX = XW NI, TY = NG RY)
+// and a chunk of z planes: each thread holds NI column groups (x = x0 + lane +
+// XW i) of RY consecutive rows, so every global access is a 256-byte row
+// segment (128 bytes for XW = 32).  Each thread keeps, for each of its points,
+// the nine z-neighbours in a register queue; the current plane with a 4-cell
+// x/y halo is staged in LDS (double-buffered: one barrier per plane).  Queue
+// entries and pointwise streams are fetched ahead (forward two iterations,
+// adjoint one), the halo with the interior of its plane through a register
+// delay line.  Small grids' forward blocks take four planes at once instead of
+// marching.  A planner chooses tile, chunks and cache hints for each launch.
 //
 // HBM traffic per point: forward 16 B (constant density) / 20 B (variable
 // density); adjoint + imaging 28 B / 32 B (+ 8 B with illumination).
@@ -58,13 +57,20 @@ struct Tile {
 };
 
 // Block -> (tile x, tile y, z chunk).  Logical tiles are numbered x fastest,
-// then y, then z chunk; XCD k (= blockIdx mod 8) gets one contiguous range.
+// then y, then z chunk; XCD k (= blockIdx mod 8) gets one contiguous range, so
+// that neighbouring tiles share their halos in one L2, or, where m.spread is
+// set, the blocks run in tile order over all XCDs: the device then reads each
+// plane as a few contiguous stretches, which memory far beyond the last-level
+// cache prefers (576^3 VD forward, 64 x 32 tiles: 688 against 728 us; 448^3 322 /
+// 331; 390 x 340 x 320, under 1 GB a step, 158 / 154; 296^3 97 / 95).
 __device__ __forceinline__ void tile_of(const TileMap &m, int b, int &tx, int &ty, int &tz) {
   const int nb = m.nblocks;
   const int per = nb / 8, rem = nb % 8;
   const int xcd = b % 8, slot = b / 8;
   const int logical =
-      xcd < rem ? xcd * (per + 1) + slot : rem * (per + 1) + (xcd - rem) * per + slot;
+      m.spread ? b
+               : (xcd < rem ? xcd * (per + 1) + slot
+                            : rem * (per + 1) + (xcd - rem) * per + slot);
   tx = logical % m.tiles_x;
   const int r = logical / m.tiles_x;
   ty = r % m.tiles_y;
@@ -110,17 +116,10 @@ __device__ __forceinline__ float ld_once(const float *p) {
   if constexpr (NT) return __builtin_nontemporal_load(p);
   return *p;
 }
-template <bool NT>
-__device__ __forceinline__ float ld_stream(const float *f, const StepGrid &g, int z, uint32_t o,
-                                           bool ok) {
-  return ok ? ld_once<NT>(f + (int64_t)z * g.plane + o) : 0.0f;
-}
 // The adjoint's form: a lane outside the grid (or a plane past the chunk)
 // reads the field's first element and drops the value instead of skipping
 // the load.  Together with the branch-free stores below and the sponge factor
-// read a plane ahead this took the 576^3 adjoint step from 1218 to 1158 us;
-// the same changes made the forward step slower (688 -> 713 us), so it keeps
-// the branches.
+// read a plane ahead this took the 576^3 adjoint step from 1218 to 1158 us.
 template <bool NT>
 __device__ __forceinline__ float ld_stream_nb(const float *f, const StepGrid &g, int z,
                                               uint32_t o, bool ok) {
@@ -141,7 +140,31 @@ __device__ __forceinline__ void st_plane(float *f, const StepGrid &g, int z, uin
   __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, ob, 0, NT ? 2 /* nt */ : 0);
 }
 
-// Per-thread view of one stenciled field: register queue + halo staging.
+// Sums of the x, y and z second differences (before 1/h^2 weights) of the point
+// in row J, column group I of the thread, on the plane whose z neighbours are
+// q[point][Z .. Z + 8] and whose tile with halo is staged in s.
+template <class T, int J, int I, int Z, int NQ>
+__device__ __forceinline__ void point_diffs(const float (&q)[T::NP][NQ],
+                                            const float (*s)[T::LX], int wave, int lane,
+                                            float &sx, float &sy, float &sz) {
+  constexpr int RY = T::RY, NI = T::NI, P = J * NI + I;
+  const int ly = 4 + wave * RY + J, lx = 4 + T::XW * I + lane;
+  const float *row = s[ly];
+  sx = W1 * (row[lx - 1] + row[lx + 1]) + W2 * (row[lx - 2] + row[lx + 2]) +
+       W3 * (row[lx - 3] + row[lx + 3]) + W4 * (row[lx - 4] + row[lx + 4]);
+  float up[4], dn[4];
+#pragma unroll
+  for (int k = 1; k <= 4; ++k) {
+    up[k - 1] = (J - k >= 0) ? q[((J - k >= 0) ? J - k : 0) * NI + I][Z + 4] : s[ly - k][lx];
+    dn[k - 1] = (J + k < RY) ? q[((J + k < RY) ? J + k : 0) * NI + I][Z + 4] : s[ly + k][lx];
+  }
+  sy = W1 * (up[0] + dn[0]) + W2 * (up[1] + dn[1]) + W3 * (up[2] + dn[2]) + W4 * (up[3] + dn[3]);
+  sz = W1 * (q[P][Z + 3] + q[P][Z + 5]) + W2 * (q[P][Z + 2] + q[P][Z + 6]) +
+       W3 * (q[P][Z + 1] + q[P][Z + 7]) + W4 * (q[P][Z] + q[P][Z + 8]);
+}
+
+// The adjoint's per-thread view of one stenciled field: register queue + halo
+// staging.
 // The halo of a plane is loaded together with the plane's interior (five
 // planes ahead of its use), when the neighbouring tiles load the same lines
 // as their interior, and waits in a register delay line; loading it one plane
@@ -149,10 +172,9 @@ __device__ __forceinline__ void st_plane(float *f, const StepGrid &g, int z, uin
 // adjoint (two stenciled fields) then re-read its halo from HBM.
 // DL is the delay-line depth: the halo of plane z is loaded DL planes before
 // it is staged (5: with the interior of that plane; 1: one plane ahead).
-// K tags the kernel family (0 forward, 1 adjoint): each family gets its own
-// instantiations of the tile helpers.  With shared ones, hipcc allocated the
-// adjoint 137 VGPRs instead of 123 once a forward shape used the same tile,
-// dropping it from 4 to 3 waves per SIMD.
+// K tags the kernel family (0 forward, 1 adjoint) of the tile helpers: with
+// shared ones, hipcc allocated the adjoint 137 VGPRs instead of 123 once a
+// forward shape used the same tile, dropping it from 4 to 3 waves per SIMD.
 // FS: the grid may have a free surface.  Without one, plane loads carry no
 // image branch: a uniform branch in every load cost 7 % of the step time.
 template <class T, int K, bool FS, int DL = 5>
@@ -171,8 +193,7 @@ struct Marcher {
       return (ok && zm < g.nz) ? -f[(int64_t)zm * g.plane + o] : 0.0f;
     }
     const bool in = ok && z >= 0 && z < g.nz;
-    if (K == 0) return in ? f[(int64_t)z * g.plane + o] : 0.0f;
-    const float v = f[in ? (int64_t)z * g.plane + o : 0];  // adjoint: as ld_stream_nb
+    const float v = f[in ? (int64_t)z * g.plane + o : 0];  // as ld_stream_nb
     return in ? v : 0.0f;
   }
   __device__ __forceinline__ void prime(const float *f, const StepGrid &g, int z0,
@@ -223,21 +244,7 @@ struct Marcher {
   template <int J, int I>
   __device__ __forceinline__ void diffs(const float (*s)[T::LX], int wave, int lane, float &sx,
                                         float &sy, float &sz) const {
-    const int ly = 4 + wave * RY + J, lx = 4 + XW * I + lane;
-    const float *row = s[ly];
-    sx = W1 * (row[lx - 1] + row[lx + 1]) + W2 * (row[lx - 2] + row[lx + 2]) +
-         W3 * (row[lx - 3] + row[lx + 3]) + W4 * (row[lx - 4] + row[lx + 4]);
-    float up[4], dn[4];
-#pragma unroll
-    for (int k = 1; k <= 4; ++k) {
-      up[k - 1] = (J - k >= 0) ? q[((J - k >= 0) ? J - k : 0) * NI + I][4] : s[ly - k][lx];
-      dn[k - 1] = (J + k < RY) ? q[((J + k < RY) ? J + k : 0) * NI + I][4] : s[ly + k][lx];
-    }
-    sy = W1 * (up[0] + dn[0]) + W2 * (up[1] + dn[1]) + W3 * (up[2] + dn[2]) +
-         W4 * (up[3] + dn[3]);
-    constexpr int P = J * NI + I;
-    sz = W1 * (q[P][3] + q[P][5]) + W2 * (q[P][2] + q[P][6]) + W3 * (q[P][1] + q[P][7]) +
-         W4 * (q[P][0] + q[P][8]);
+    point_diffs<T, J, I, 0>(q, s, wave, lane, sx, sy, sz);
   }
 };
 
@@ -294,137 +301,337 @@ struct Geo {
   }
 };
 
-// Receiver entries of one column, walked in z order.
+// Receiver nodes of one column, walked in z order: the next one's plane and the
+// sum of the residuals injected there (res_row holds them node by node).  Both
+// are read when the cursor gets there, at the latest with the block's first
+// loads: read at the node's own plane, the chain column -> node -> residuals
+// held every wavefront of the plane for three memory latencies.
 struct ColCursor {
   int e, ee, ez;
-  __device__ __forceinline__ void init(const RecTable &rec, int col, int z0, bool ok) {
-    e = ee = 0;
+  float sum;
+  __device__ __forceinline__ void load(const RecTable &rec, const float *__restrict__ res_row,
+                                       int z0) {
     ez = INT_MAX;
-    if (!ok) return;
-    e = rec.col_start[col];
-    ee = rec.col_start[col + 1];
-    while (e < ee && rec.ent_z[e] < z0) ++e;
-    ez = e < ee ? rec.ent_z[e] : INT_MAX;
+    for (; e < ee; ++e) {
+      const int z = rec.ent_z[e], r0 = rec.ent_rp[e], r1 = rec.ent_rp[e + 1];
+      if (z < z0) continue;
+      sum = 0.0f;
+      for (int r = r0; r < r1; ++r) sum += res_row[r];
+      ez = z;
+      break;
+    }
   }
-  __device__ __forceinline__ void advance(const RecTable &rec) {
+  __device__ __forceinline__ void init(const RecTable &rec, const float *__restrict__ res_row,
+                                       int col, int z0, bool ok) {
+    e = ok ? rec.col_start[col] : 0;
+    ee = ok ? rec.col_start[col + 1] : 0;
+    load(rec, res_row, z0);
+  }
+  __device__ __forceinline__ void advance(const RecTable &rec, const float *__restrict__ res_row) {
     ++e;
-    ez = e < ee ? rec.ent_z[e] : INT_MAX;
+    load(rec, res_row, 0);
   }
 };
+
+// Recording.  Sample n - 1 is read from w^n, the current state of step n, by
+// blocks of their own beside the step's: a recording in the blocks that write
+// w^{n+1} held the plane of the receivers for four dependent memory latencies
+// (80^3, a receiver every 8 cells: 9.0 us a step, 7.5 without).
+constexpr int kRecordBlock = 256;
+__device__ __forceinline__ void record_block(const Record &rec, const float *__restrict__ field,
+                                             float *__restrict__ row, int b) {
+  const int r = b * kRecordBlock + threadIdx.x;
+  if (threadIdx.x < kRecordBlock && r < rec.nrec) row[r] = rec.scale[r] * field[rec.idx[r]];
+}
+int record_blocks(int nrec) { return (nrec + kRecordBlock - 1) / kRecordBlock; }
 
 // One LDS plane of a tile with its halo.
 template <class T>
 using LdsPlane = float[T::LY][T::LX];
 
-// One leapfrog step over tile block b of a grid; records the receivers of
-// step n when seis_tm is set (recomputation sweeps pass none).
+// Plane z of a field as a buffer: reads at a lane's offset in bytes, zero past
+// the plane (a lane outside the grid passes kDropOffset) and on planes outside
+// the grid (an empty buffer), without branches or address arithmetic per lane.
+// Above a free surface the mirror plane; its sign is image_sign's.
+template <bool FS>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_of(const float *f, const StepGrid &g,
+                                                           int z, bool more = true) {
+  if (FS && z < g.zs) z = 2 * g.zs - z;
+  const bool in = more && z >= 0 && z < g.nz;
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(f) + (in ? (int64_t)z * g.plane : 0),
+                                           (short)0, in ? (int)(uint32_t)(g.plane * 4) : 0,
+                                           0x00020000);
+}
+template <bool NT>
+__device__ __forceinline__ float ld_plane(__amdgpu_buffer_rsrc_t r, uint32_t ob) {
+  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, ob, 0, NT ? 2 : 0));
+}
+template <bool FS>
+__device__ __forceinline__ float image(const StepGrid &g, int z, float v) {
+  return FS && z < g.zs ? -v : v;
+}
+
+// What the plane loop of a forward tile loads two planes ahead.
+template <class T>
+struct InFlight {
+  float q[T::NP], h[T::HPT];                // w: interior and halo of plane z + 6
+  float p[T::NP], k[T::NP], m[T::NP], gz;  // streams of plane z + 2
+};
+
+// One leapfrog step over tile block b of a grid.  The loads of an iteration are
+// used at the end of the next one: two sets of registers take turns, since
+// moving a register waits for its load.  Loads carry no branch, so that the
+// compiler's wait counts are exact.  (One plane ahead, and with the sponge
+// factor loaded in the plane that used it, every plane waited for all of its
+// own loads: 296^3 VD 102 us instead of 92, 240 x 240 x 200 CD 38 instead of 33.)
 template <class T, bool VD, bool FS, bool NT>
 __device__ __forceinline__ void forward_tile(
     LdsPlane<T> *sm, const StepGrid &g,
     const float *__restrict__ cur, const float *prev, float *out, const Source &src, int n,
-    const RecTable &rec, const float *__restrict__ rec_scale, float *__restrict__ seis_tm,
     const TileMap &map, int b) {
-  constexpr int NP = T::NP, RY = T::RY, NI = T::NI;
+  constexpr int NP = T::NP, RY = T::RY, NI = T::NI, HPT = T::HPT, DL = 5;
   Geo<T, 0> geo;
   if (!geo.init(g, map, b)) return;
-  Marcher<T, 0, FS> f;
-  f.prime(cur, g, geo.z0, geo.off, geo.in, geo.hoff, geo.hin);
+  uint32_t ob[NP], hb[HPT];
+#pragma unroll
+  for (int p = 0; p < NP; ++p) ob[p] = geo.in[p] ? 4u * geo.off[p] : kDropOffset;
+#pragma unroll
+  for (int i = 0; i < HPT; ++i) hb[i] = geo.hin[i] ? 4u * geo.hoff[i] : kDropOffset;
+  float q[NP][9], hq[DL][HPT], pv[NP], kv[NP], mv[NP], gz;
+  auto fetch = [&](InFlight<T> &f, int z) {  // for the plane loop's iteration z - 1
+    const auto rw = plane_of<FS>(cur, g, z + 5);
+    const bool more = z + 1 < geo.z1;
+    const auto rp = plane_of<false>(prev, g, z + 1, more), rk = plane_of<false>(g.k, g, z + 1, more);
+#pragma unroll
+    for (int p = 0; p < NP; ++p) f.q[p] = ld_plane<false>(rw, ob[p]);
+#pragma unroll
+    for (int i = 0; i < HPT; ++i) f.h[i] = ld_plane<false>(rw, hb[i]);
+#pragma unroll
+    for (int p = 0; p < NP; ++p) f.p[p] = ld_plane<NT>(rp, ob[p]);
+#pragma unroll
+    for (int p = 0; p < NP; ++p) f.k[p] = ld_plane<NT>(rk, ob[p]);
+    if constexpr (VD) {
+      const auto rm = plane_of<false>(g.m2, g, z + 1, more);
+#pragma unroll
+      for (int p = 0; p < NP; ++p) f.m[p] = ld_plane<NT>(rm, ob[p]);
+    }
+    f.gz = g.gz[z + 1 < g.nz ? z + 1 : z];
+  };
+#pragma unroll
+  for (int i = 0; i < 9; ++i) {
+    const int z = geo.z0 - 4 + i;
+    const auto r = plane_of<FS>(cur, g, z);
+#pragma unroll
+    for (int p = 0; p < NP; ++p) q[p][i] = image<FS>(g, z, ld_plane<false>(r, ob[p]));
+    if (i >= 4) {
+#pragma unroll
+      for (int k = 0; k < HPT; ++k) hq[i - 4][k] = image<FS>(g, z, ld_plane<false>(r, hb[k]));
+    }
+  }
+  {
+    const auto rp = plane_of<false>(prev, g, geo.z0), rk = plane_of<false>(g.k, g, geo.z0);
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      pv[p] = ld_plane<NT>(rp, ob[p]);
+      kv[p] = ld_plane<NT>(rk, ob[p]);
+      mv[p] = VD ? ld_plane<NT>(plane_of<false>(g.m2, g, geo.z0), ob[p]) : 0.0f;
+    }
+    gz = g.gz[geo.z0];
+  }
+  InFlight<T> f0, f1;
+  fetch(f1, geo.z0);
   float gxv[NI], gyv[RY];
 #pragma unroll
   for (int i = 0; i < NI; ++i) gxv[i] = geo.xs[i] < g.nx ? g.gx[geo.xs[i]] : 0.0f;
 #pragma unroll
   for (int j = 0; j < RY; ++j) gyv[j] = geo.yv[j] < g.ny ? g.gy[geo.yv[j]] : 0.0f;
-  ColCursor cc[NP];
-#pragma unroll
-  for (int j = 0; j < RY; ++j)
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-      cc[j * NI + i].init(rec, geo.yv[j] * g.nx + geo.xs[i], geo.z0,
-                          geo.in[j * NI + i] && seis_tm != nullptr);
+  const float sigma = src.sigma[0], wavelet = src.wavelet[n];
   const float c0 = W0 * (g.cx + g.cy + g.cz);
-  float pv[NP], kv[NP], mv[NP];  // pointwise streams of the current plane
-#pragma unroll
-  for (int p = 0; p < NP; ++p) {
-    pv[p] = ld_stream<NT>(prev, g, geo.z0, geo.off[p], geo.in[p]);
-    kv[p] = ld_stream<NT>(g.k, g, geo.z0, geo.off[p], geo.in[p]);
-    mv[p] = VD ? ld_stream<NT>(g.m2, g, geo.z0, geo.off[p], geo.in[p]) : 0.0f;
-  }
-  for (int z = geo.z0; z < geo.z1; ++z) {
+
+  auto plane = [&](int z, InFlight<T> &next, const InFlight<T> &ready) {
     float(*s)[T::LX] = sm[z & 1];
-    f.stage(s, geo.wave, geo.lane, geo.hslot);
-    f.fetch(cur, g, z, geo.off, geo.in, geo.hoff, geo.hin);
-    const bool more = z + 1 < geo.z1;
-    float pn[NP], kn[NP], mn[NP];  // next plane, in flight during this one
 #pragma unroll
-    for (int p = 0; p < NP; ++p) {
-      pn[p] = ld_stream<NT>(prev, g, z + 1, geo.off[p], geo.in[p] && more);
-      kn[p] = ld_stream<NT>(g.k, g, z + 1, geo.off[p], geo.in[p] && more);
-      mn[p] = VD ? ld_stream<NT>(g.m2, g, z + 1, geo.off[p], geo.in[p] && more) : 0.0f;
-    }
+    for (int j = 0; j < RY; ++j)
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+        s[4 + geo.wave * RY + j][4 + T::XW * i + geo.lane] = q[j * NI + i][4];
+#pragma unroll
+    for (int i = 0; i < HPT; ++i)
+      if (geo.hslot[i] >= 0) (&s[0][0])[geo.hslot[i]] = hq[0][i];
+    fetch(next, z + 1);
     __syncthreads();
-    const float gzv = g.gz[z];
-    const int64_t zoff = (int64_t)z * g.plane;
+    const auto ro = __builtin_amdgcn_make_buffer_rsrc(
+        out + (int64_t)z * g.plane, (short)0, (int)(uint32_t)(g.plane * 4), 0x00020000);
     static_for<RY>([&](auto Jc) {
       constexpr int J = decltype(Jc)::value;
       static_for<NI>([&](auto Ic) {
         constexpr int I = decltype(Ic)::value;
         constexpr int P = J * NI + I;
         float sx, sy, sz;
-        f.template diffs<J, I>(s, geo.wave, geo.lane, sx, sy, sz);
-        const float c = f.q[P][4];
+        point_diffs<T, J, I, 0>(q, s, geo.wave, geo.lane, sx, sy, sz);
+        const float c = q[P][4];
         const float lap = c0 * c + g.cx * sx + g.cy * sy + g.cz * sz;
         float acc = VD ? 2.0f * c + kv[P] * (lap - mv[P] * c) : 2.0f * c + kv[P] * lap;
-        const int64_t p = zoff + geo.off[P];
-        if (geo.in[P] && p == src.idx) acc += src.sigma[0] * src.wavelet[n];
-        const float G = gxv[I] * gyv[J] * gzv;
+        if (z == src.z && ob[P] == src.offset) acc = __builtin_fmaf(sigma, wavelet, acc);
+        const float G = gxv[I] * gyv[J] * gz;
         const float o = (!FS || z > g.zs) ? G * (acc - G * pv[P]) : 0.0f;  // zero at/above a free surface
-        if (geo.in[P]) {
-          if constexpr (NT) __builtin_nontemporal_store(o, out + p);
-          else out[p] = o;
-        }
-        if (cc[P].ez == z) {
-          for (int r = rec.ent_rp[cc[P].e]; r < rec.ent_rp[cc[P].e + 1]; ++r) {
-            const int id = rec.perm[r];
-            seis_tm[(int64_t)n * rec.nrec + id] = rec_scale[id] * o;
-          }
-          cc[P].advance(rec);
-        }
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(o), ro, ob[P], 0, NT ? 2 : 0);
       });
     });
-    f.shift();
+    // to plane z + 1
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
-      pv[p] = pn[p];
-      kv[p] = kn[p];
-      mv[p] = mn[p];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) q[p][i] = q[p][i + 1];
+      q[p][8] = image<FS>(g, z + 5, ready.q[p]);
+      pv[p] = ready.p[p];
+      kv[p] = ready.k[p];
+      if (VD) mv[p] = ready.m[p];
     }
+#pragma unroll
+    for (int d = 0; d < DL - 1; ++d)
+#pragma unroll
+      for (int i = 0; i < HPT; ++i) hq[d][i] = hq[d + 1][i];
+#pragma unroll
+    for (int i = 0; i < HPT; ++i) hq[DL - 1][i] = image<FS>(g, z + 5, ready.h[i]);
+    gz = ready.gz;
+  };
+  for (int z = geo.z0; z < geo.z1; z += 2) {
+    plane(z, f0, f1);
+    if (z + 1 >= geo.z1) break;
+    plane(z + 1, f1, f0);
   }
 }
 
-template <class T, bool VD, bool FS, bool NT>
-__global__ void __launch_bounds__(T::NTHREADS)
+// The same step over a block of a tile times ZC planes that does not march: every
+// load of the block is issued before its one barrier, so that the block takes
+// about one memory latency instead of one per plane.
+template <class T, int ZC, bool VD, bool FS, bool NT>
+__device__ __forceinline__ void forward_slab(
+    LdsPlane<T> *sm, const StepGrid &g, const float *__restrict__ cur, const float *prev,
+    float *out, const Source &src, int n, const TileMap &map, int b) {
+  constexpr int NP = T::NP, RY = T::RY, NI = T::NI;
+  Geo<T, 0> geo;
+  if (!geo.init(g, map, b)) return;
+  float q[NP][ZC + 8], h[ZC][T::HPT], pv[ZC][NP], kv[ZC][NP], mv[ZC][NP];
+  uint32_t ob[NP], hb[T::HPT];
+#pragma unroll
+  for (int p = 0; p < NP; ++p) ob[p] = geo.in[p] ? 4u * geo.off[p] : kDropOffset;
+#pragma unroll
+  for (int i = 0; i < T::HPT; ++i) hb[i] = geo.hin[i] ? 4u * geo.hoff[i] : kDropOffset;
+#pragma unroll
+  for (int i = 0; i < ZC + 8; ++i) {
+    const int z = geo.z0 - 4 + i;
+    const auto r = plane_of<FS>(cur, g, z);
+#pragma unroll
+    for (int p = 0; p < NP; ++p) q[p][i] = image<FS>(g, z, ld_plane<false>(r, ob[p]));
+    if (i >= 4 && i < ZC + 4) {
+#pragma unroll
+      for (int k = 0; k < T::HPT; ++k)
+        h[i >= 4 && i < ZC + 4 ? i - 4 : 0][k] = image<FS>(g, z, ld_plane<false>(r, hb[k]));
+    }
+  }
+#pragma unroll
+  for (int z = 0; z < ZC; ++z) {
+    const bool more = geo.z0 + z < geo.z1;
+    const auto rp = plane_of<false>(prev, g, geo.z0 + z, more),
+               rk = plane_of<false>(g.k, g, geo.z0 + z, more);
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      pv[z][p] = ld_plane<NT>(rp, ob[p]);
+      kv[z][p] = ld_plane<NT>(rk, ob[p]);
+      mv[z][p] = VD ? ld_plane<NT>(plane_of<false>(g.m2, g, geo.z0 + z, more), ob[p]) : 0.0f;
+    }
+  }
+  const float sigma = src.sigma[0], wavelet = src.wavelet[n];
+  float gzv[ZC];
+#pragma unroll
+  for (int z = 0; z < ZC; ++z) gzv[z] = g.gz[min(geo.z0 + z, g.nz - 1)];
+  float gxv[NI], gyv[RY];
+#pragma unroll
+  for (int i = 0; i < NI; ++i) gxv[i] = geo.xs[i] < g.nx ? g.gx[geo.xs[i]] : 0.0f;
+#pragma unroll
+  for (int j = 0; j < RY; ++j) gyv[j] = geo.yv[j] < g.ny ? g.gy[geo.yv[j]] : 0.0f;
+#pragma unroll
+  for (int z = 0; z < ZC; ++z) {
+#pragma unroll
+    for (int j = 0; j < RY; ++j)
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+        sm[z][4 + geo.wave * RY + j][4 + T::XW * i + geo.lane] = q[j * NI + i][z + 4];
+#pragma unroll
+    for (int i = 0; i < T::HPT; ++i)
+      if (geo.hslot[i] >= 0) (&sm[z][0][0])[geo.hslot[i]] = h[z][i];
+  }
+  __syncthreads();
+  const float c0 = W0 * (g.cx + g.cy + g.cz);
+  static_for<ZC>([&](auto Zc) {
+    constexpr int Z = decltype(Zc)::value;
+    const int z = geo.z0 + Z;
+    if (z >= geo.z1) return;
+    const auto ro = __builtin_amdgcn_make_buffer_rsrc(
+        out + (int64_t)z * g.plane, (short)0, (int)(uint32_t)(g.plane * 4), 0x00020000);
+    static_for<RY>([&](auto Jc) {
+      constexpr int J = decltype(Jc)::value;
+      static_for<NI>([&](auto Ic) {
+        constexpr int I = decltype(Ic)::value;
+        constexpr int P = J * NI + I;
+        float sx, sy, sz;
+        point_diffs<T, J, I, Z>(q, sm[Z], geo.wave, geo.lane, sx, sy, sz);
+        const float c = q[P][Z + 4];
+        const float lap = c0 * c + g.cx * sx + g.cy * sy + g.cz * sz;
+        float acc = VD ? 2.0f * c + kv[Z][P] * (lap - mv[Z][P] * c) : 2.0f * c + kv[Z][P] * lap;
+        if (z == src.z && ob[P] == src.offset) acc = __builtin_fmaf(sigma, wavelet, acc);
+        const float G = gxv[I] * gyv[J] * gzv[Z];
+        const float o = (!FS || z > g.zs) ? G * (acc - G * pv[Z][P]) : 0.0f;
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(o), ro, ob[P], 0, NT ? 2 : 0);
+      });
+    });
+  });
+}
+
+template <class S, bool VD, bool FS, bool NT>
+__device__ __forceinline__ void forward_block(const StepGrid &g, const float *__restrict__ cur,
+                                              const float *prev, float *out, const Source &src,
+                                              int n, const TileMap &map, int b) {
+  using T = Tile<S::RY, S::NG, S::NI, S::XW>;
+  __shared__ float sm[S::ZC > 0 ? S::ZC : 2][T::LY][T::LX];
+  if constexpr (S::ZC > 0)
+    forward_slab<T, S::ZC, VD, FS, NT>(sm, g, cur, prev, out, src, n, map, b);
+  else
+    forward_tile<T, VD, FS, NT>(sm, g, cur, prev, out, src, n, map, b);
+}
+
+// Blocks from map.nblocks on record row (sample n - 1).
+template <class S, bool VD, bool FS, bool NT>
+__global__ void __launch_bounds__(S::NTHREADS)
     k_forward(StepGrid g, const float *__restrict__ cur, const float *prev, float *out,
-              Source src, int n, RecTable rec, const float *__restrict__ rec_scale,
-              float *__restrict__ seis_tm, TileMap map) {
-  __shared__ float sm[2][T::LY][T::LX];
-  forward_tile<T, VD, FS, NT>(sm, g, cur, prev, out, src, n, rec, rec_scale, seis_tm, map,
-                                   blockIdx.x);
+              Source src, int n, Record rec, float *__restrict__ row, TileMap map) {
+  const int b = blockIdx.x;
+  if (b >= map.nblocks) return record_block(rec, cur, row, b - map.nblocks);
+  forward_block<S, VD, FS, NT>(g, cur, prev, out, src, n, map, b);
 }
 
 // Several grids (one per shot) advanced by one launch: block b belongs to the
-// window whose [block_begin, block_end) contains it.  Window ranges start at
-// multiples of 8 so that each window keeps the XCD-aware tile order.
-template <class T, bool VD, bool FS, bool NT>
-__global__ void __launch_bounds__(T::NTHREADS)
+// window whose [block_begin, block_end) contains it.  Ranges follow one another
+// without gaps: a window that starts off a multiple of 8 has its XCD ranges
+// rotated, while ranges padded to multiples of 8 gave XCD 0 up to twice the
+// blocks of the others (24 small windows, adjoint: 138 us a step instead of
+// 78).
+template <class S, bool VD, bool FS, bool NT>
+__global__ void __launch_bounds__(S::NTHREADS)
     k_forward_multi(const WindowStep *__restrict__ wins, int nwin, int n) {
-  __shared__ float sm[2][T::LY][T::LX];
   const int b = blockIdx.x;
   int w = 0;
   while (w + 1 < nwin && b >= wins[w + 1].block_begin) ++w;
   const WindowStep &d = wins[w];
-  if (b >= d.block_end) return;
-  forward_tile<T, VD, FS, NT>(sm, d.g, d.cur, d.prev, d.out, d.src, n, d.rec, d.rec_scale,
-                                   d.seis_tm, d.map, b - d.block_begin);
+  const int t = b - d.block_begin;
+  if (t >= d.map.nblocks) {
+    if (n > 0)
+      record_block(d.rec, d.cur, d.seis_tm + (int64_t)(n - 1) * d.rec.nrec, t - d.map.nblocks);
+    return;
+  }
+  forward_block<S, VD, FS, NT>(d.g, d.cur, d.prev, d.out, d.src, n, d.map, t);
 }
 
 // DL: halo delay-line depth of the adjoint's two fields (the tile shapes
@@ -453,14 +660,8 @@ __device__ __forceinline__ void adjoint_tile(
   for (int i = 0; i < NI; ++i) gxv[i] = geo.xs[i] < g.nx ? g.gx[geo.xs[i]] : 0.0f;
 #pragma unroll
   for (int j = 0; j < RY; ++j) gyv[j] = geo.yv[j] < g.ny ? g.gy[geo.yv[j]] : 0.0f;
-  ColCursor cc[NP];
-#pragma unroll
-  for (int j = 0; j < RY; ++j)
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-      cc[j * NI + i].init(rec, geo.yv[j] * g.nx + geo.xs[i], geo.z0, geo.in[j * NI + i]);
-  const float c0 = W0 * (g.cx + g.cy + g.cz);
   const float *res_row = res_tm + (int64_t)(m - 1) * rec.nrec;
+  const float c0 = W0 * (g.cx + g.cy + g.cz);
   const int iexp = ILLUM ? il.out_exp2 - 2 * il.sc->e : 0;  // (2^e w)^2 -> 2^out_exp2 w^2
   float gzv = g.gz[geo.z0];  // the z sponge factor, read one plane ahead
   float pv[NP], kv[NP], mv[NP], gv[NP];
@@ -471,6 +672,12 @@ __device__ __forceinline__ void adjoint_tile(
     mv[p] = VD ? ld_stream_nb<NT>(g.m2, g, geo.z0, geo.off[p], geo.in[p]) : 0.0f;
     gv[p] = ld_stream_nb<NT>(grad, g, geo.z0, geo.off[p], geo.in[p]);
   }
+  ColCursor cc[NP];
+#pragma unroll
+  for (int j = 0; j < RY; ++j)
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+      cc[j * NI + i].init(rec, res_row, geo.yv[j] * g.nx + geo.xs[i], geo.z0, geo.in[j * NI + i]);
   for (int z = geo.z0; z < geo.z1; ++z) {
     float(*sa)[T::LX] = sm[0][z & 1];
     float(*sw)[T::LX] = sm[1][z & 1];
@@ -502,11 +709,8 @@ __device__ __forceinline__ void adjoint_tile(
         const float lap_w = c0 * cw + g.cx * wx + g.cy * wy + g.cz * wz;
         float acc = VD ? 2.0f * ca + kv[P] * (lap_a - mv[P] * ca) : 2.0f * ca + kv[P] * lap_a;
         if (cc[P].ez == z) {  // receiver residuals injected at this node
-          float sum = 0.0f;
-          for (int r = rec.ent_rp[cc[P].e]; r < rec.ent_rp[cc[P].e + 1]; ++r)
-            sum += res_row[rec.perm[r]];
-          acc += sum;
-          cc[P].advance(rec);
+          acc += cc[P].sum;
+          cc[P].advance(rec, res_row);
         }
         const float G = gxv[I] * gyv[J] * gzv;
         const bool live = !FS || z > g.zs;  // at and above a free surface psi and w stay zero
@@ -555,14 +759,8 @@ __global__ void __launch_bounds__(T::NTHREADS)
   for (int i = 0; i < NI; ++i) gxv[i] = geo.xs[i] < g.nx ? g.gx[geo.xs[i]] : 0.0f;
 #pragma unroll
   for (int j = 0; j < RY; ++j) gyv[j] = geo.yv[j] < g.ny ? g.gy[geo.yv[j]] : 0.0f;
-  ColCursor cc[NP];
-#pragma unroll
-  for (int j = 0; j < RY; ++j)
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-      cc[j * NI + i].init(rec, geo.yv[j] * g.nx + geo.xs[i], geo.z0, geo.in[j * NI + i]);
-  const float c0 = W0 * (g.cx + g.cy + g.cz);
   const float *res_row = res_tm + (int64_t)(m - 1) * rec.nrec;
+  const float c0 = W0 * (g.cx + g.cy + g.cz);
   const int iexp = ILLUM ? il.out_exp2 - 2 * il.sc->e : 0;  // (2^e w)^2 -> 2^out_exp2 w^2
   float gzv = g.gz[geo.z0];  // the z sponge factor, read one plane ahead
   float pv[NP], kv[NP], mv[NP], gv[NP];
@@ -573,6 +771,12 @@ __global__ void __launch_bounds__(T::NTHREADS)
     mv[p] = VD ? ld_stream_nb<NT>(g.m2, g, geo.z0, geo.off[p], geo.in[p]) : 0.0f;
     gv[p] = ld_stream_nb<NT>(grad, g, geo.z0, geo.off[p], geo.in[p]);
   }
+  ColCursor cc[NP];
+#pragma unroll
+  for (int j = 0; j < RY; ++j)
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+      cc[j * NI + i].init(rec, res_row, geo.yv[j] * g.nx + geo.xs[i], geo.z0, geo.in[j * NI + i]);
   for (int z = geo.z0; z < geo.z1; ++z) {
     float(*sa)[T::LX] = sm[0][z & 1];
     float(*sw)[T::LX] = sm[1][z & 1];
@@ -604,11 +808,8 @@ __global__ void __launch_bounds__(T::NTHREADS)
         const float lap_w = c0 * cw + g.cx * wx + g.cy * wy + g.cz * wz;
         float acc = VD ? 2.0f * ca + kv[P] * (lap_a - mv[P] * ca) : 2.0f * ca + kv[P] * lap_a;
         if (cc[P].ez == z) {  // receiver residuals injected at this node
-          float sum = 0.0f;
-          for (int r = rec.ent_rp[cc[P].e]; r < rec.ent_rp[cc[P].e + 1]; ++r)
-            sum += res_row[rec.perm[r]];
-          acc += sum;
-          cc[P].advance(rec);
+          acc += cc[P].sum;
+          cc[P].advance(rec, res_row);
         }
         const float G = gxv[I] * gyv[J] * gzv;
         const bool live = !FS || z > g.zs;  // at and above a free surface psi and w stay zero
@@ -645,21 +846,35 @@ __device__ __forceinline__ float *pool_buffer(const GradWindow &d, int k) {
 // the window whose [fblock_begin, fblock_end) contains it; the step reads pool
 // buffers cur_k (w^n) and prev_k (w^{n-1}) and writes out_k, recording the
 // receivers when `record` is set.
-template <class T, bool VD, bool FS, bool NT>
-__global__ void __launch_bounds__(T::NTHREADS)
+template <class S, bool VD, bool FS, bool NT>
+__global__ void __launch_bounds__(S::NTHREADS)
     k_forward_pool(const GradWindow *__restrict__ wins, int nwin, int n, int cur_k, int prev_k,
                    int out_k, int record) {
-  __shared__ float sm[2][T::LY][T::LX];
   const int b = blockIdx.x;
   int w = 0;
   while (w + 1 < nwin && b >= wins[w + 1].fblock_begin) ++w;
   const GradWindow &d = wins[w];
-  if (b >= d.fblock_end) return;
-  const RecTable none{};
-  forward_tile<T, VD, FS, NT>(sm, d.g, pool_buffer(d, cur_k), pool_buffer(d, prev_k),
-                                   pool_buffer(d, out_k), d.src, n, record ? d.rec : none,
-                                   d.rec_scale, record ? d.seis_tm : nullptr, d.fmap,
-                                   b - d.fblock_begin);
+  const int t = b - d.fblock_begin;
+  const float *cur = pool_buffer(d, cur_k);
+  if (t >= d.fmap.nblocks) {
+    if (record && n > 0)
+      record_block(d.out, cur, d.seis_tm + (int64_t)(n - 1) * d.out.nrec, t - d.fmap.nblocks);
+    return;
+  }
+  forward_block<S, VD, FS, NT>(d.g, cur, pool_buffer(d, prev_k), pool_buffer(d, out_k), d.src, n,
+                               d.fmap, t);
+}
+
+// The last sample of every window, from its final state.
+__global__ void __launch_bounds__(kRecordBlock)
+    k_record_windows(const WindowStep *__restrict__ wins, int n) {
+  const WindowStep &d = wins[blockIdx.y];
+  record_block(d.rec, d.cur, d.seis_tm + (int64_t)n * d.rec.nrec, blockIdx.x);
+}
+__global__ void __launch_bounds__(kRecordBlock)
+    k_record_pool(const GradWindow *__restrict__ wins, int n, int cur_k) {
+  const GradWindow &d = wins[blockIdx.y];
+  record_block(d.out, pool_buffer(d, cur_k), d.seis_tm + (int64_t)n * d.out.nrec, blockIdx.x);
 }
 
 // One adjoint step (with imaging) of every window: psi^{m+1} is P1 (parity 0)
@@ -700,23 +915,26 @@ int blocks_per_cu(K kernel, int threads) {
 }
 
 // Forward tile shapes (rows per thread, row groups, column groups per thread,
-// lanes per row): 0 to 4 by tuning, 5 by the planner only.  Of the 64-wide tiles
-// 0 was the fastest at 576^3 (694 us per step against 793 us for 64 x 32 tiles
-// and 745 us for 4 x 4 with the same chunking rule).
+// lanes per row): 0 to 4 by tuning; the planner takes 0, 1 (with streaming hints)
+// or 5, 32 x 32 x 4 points in one go (without).
+template <int RY, int NG, int NI, int XW, int ZC_ = 0>
+struct Shape : Tile<RY, NG, NI, XW> {
+  static constexpr int ZC = ZC_;  // planes of a block that does not march, else 0
+};
 template <int V>
 struct FwdShape;
 template <>
-struct FwdShape<0> : Tile<2, 8, 1, 64> {};  // 64 x 16
+struct FwdShape<0> : Shape<2, 8, 1, 64> {};  // 64 x 16
 template <>
-struct FwdShape<1> : Tile<2, 16, 1, 64> {};  // 64 x 32
+struct FwdShape<1> : Shape<2, 16, 1, 64> {};  // 64 x 32
 template <>
-struct FwdShape<2> : Tile<2, 4, 1, 64> {};  // 64 x 8
+struct FwdShape<2> : Shape<2, 4, 1, 64> {};  // 64 x 8
 template <>
-struct FwdShape<3> : Tile<4, 4, 1, 64> {};  // 64 x 16
+struct FwdShape<3> : Shape<4, 4, 1, 64> {};  // 64 x 16
 template <>
-struct FwdShape<4> : Tile<1, 16, 3, 64> {};  // 192 x 16
+struct FwdShape<4> : Shape<1, 16, 3, 64> {};  // 192 x 16
 template <>
-struct FwdShape<5> : Tile<2, 16, 1, 32> {};  // 32 x 32
+struct FwdShape<5> : Shape<2, 16, 1, 32, 4> {};  // 32 x 32 x 4
 
 // Adjoint tile shapes, with their halo delay-line depth: 0 to 3 by tuning, 4 by
 // the planner only.  With two stenciled fields, the 64 x 32 tile (one halo value
@@ -771,7 +989,7 @@ auto with_forward(int shape, bool vd, bool fs, bool stream, F f) {
         case 2: return f(FwdShape<2>{}, VD, FS, Bool<true>{});
         case 3: return f(FwdShape<3>{}, VD, FS, Bool<true>{});
         case 4: return f(FwdShape<4>{}, VD, FS, Bool<true>{});
-        case 5: return both(FwdShape<5>{});
+        case 5: return f(FwdShape<5>{}, VD, FS, Bool<false>{});
         default: return both(FwdShape<0>{});
       }
     });
@@ -802,25 +1020,32 @@ auto with_adjoint(int shape, bool vd, bool illum, bool fs, bool stream, F f) {
 struct Candidate {
   int shape, tx, ty, per_cu;
   double weight;
+  int slab;  // planes of a block that does not march, else 0
 };
+
+template <class S, class = void>
+struct HasSlab : std::false_type {};
+template <class S>
+struct HasSlab<S, std::void_t<decltype(S::ZC)>> : std::true_type {};
 
 template <class K, class S>
 Candidate candidate(int shape, K kernel, S, double weight) {
-  return Candidate{shape, S::TX, S::TY, blocks_per_cu(kernel, S::NTHREADS), weight};
+  int slab = 0;
+  if constexpr (HasSlab<S>::value) slab = S::ZC;
+  return Candidate{shape, S::TX, S::TY, blocks_per_cu(kernel, S::NTHREADS), weight, slab};
 }
 
-// Weights: 32-wide forward tiles against 64 x 16 where both waste no lanes,
-// 240 x 240 x 200 and 144^3 without streaming hints 39.8 / 41.1 and 19.8 / 20.3
-// us, 250 x 250 x 240 and 576^3 with them 67.5 / 61.2 and 730 / 704 (128-byte
-// rows); adjoint, 240 x 240 x 200: 64 x 16 tiles 91 / 87 us, 32 x 32 99 / 87 with
-// hints and 75 / 72 without.  They pay where a grid's last 64-wide tile is mostly
-// empty: 390 x 340 x 320 forward 166 us against 176.
+// Weights.  Forward, with streaming hints: 64 x 32 tiles against 64 x 16, 95 / 98
+// us at 296^3, 154 / 164 at 390 x 340 x 320, 330 / 341 at 448^3, 728 / 755 at
+// 576^3.  Adjoint, 240 x 240 x 200: 64 x 16 tiles 91 / 87 us, 32 x 32 99 / 87 with
+// hints and 75 / 72 without; those pay where a grid's last 64-wide tile is mostly
+// empty.
 Candidate forward_candidate(int shape, bool vd, bool fs, bool stream) {
   return with_forward(shape, vd, fs, stream, [&](auto S, auto VD, auto FS, auto NT) {
     using Sh = decltype(S);
     static const Candidate c = candidate(
-        shape, k_forward<TileOf<Sh>, decltype(VD)::value, decltype(FS)::value, decltype(NT)::value>,
-        S, shape == 5 ? (NT.value ? 1.08 : 0.98) : 1.0);
+        shape, k_forward<Sh, decltype(VD)::value, decltype(FS)::value, decltype(NT)::value>,
+        S, shape == 1 ? 0.95 : 1.0);
     return c;
   });
 }
@@ -857,8 +1082,14 @@ constexpr int kMinZc = 4;
 // instead of 240 us.)
 constexpr double kTailFloor = 0.9, kHalo = 4.0;
 
+// A block that does not march costs its share of the device's throughput: with
+// about 1.15 us a plane above, 80^3 (180 blocks) 5.9 us, 144^3 (900) 13.7, 240 x 240
+// x 200 (3200) 36; the marching tiles take 7.1, 14.6 and 33.
+constexpr double kSlabBase = 2.6, kSlabBlock = 0.0095;
+
 double launch_cost(const Candidate &c, int64_t blocks, int zc) {
   const int64_t cus = device_cus();
+  if (c.slab > 0) return kSlabBase + kSlabBlock * (double)blocks * 256.0 / (double)cus;
   const double R = (double)blocks / (double)(c.per_cu * cus), full = std::floor(R), f = R - full;
   double rounds;
   if (R <= 1.0) {
@@ -882,6 +1113,7 @@ TileMap map_of(const StepGrid &g, const Candidate &c, int nch) {
   m.zc = (g.nz + nch - 1) / nch;
   m.nchunks = (g.nz + m.zc - 1) / m.zc;
   m.nblocks = (int)((int64_t)m.tiles_x * m.tiles_y * m.nchunks);
+  m.spread = 0;
   return m;
 }
 
@@ -903,6 +1135,7 @@ int plan_maps(const StepGrid *const *grids, const int *rounds, int n, const Cand
     for (int nch = 1; nch <= (deepest + kMinZc - 1) / kMinZc; ++nch) {
       const int zc = (deepest + nch - 1) / nch;
       if ((deepest + zc - 1) / zc != nch) continue;  // same chunks as a smaller count
+      if (cand[k].slab > 0 && zc > cand[k].slab) continue;
       int64_t blocks = 0;
       for (int i = 0; i < n; ++i) blocks += tiles_of(*grids[i], cand[k]) * ((grids[i]->nz + zc - 1) / zc);
       const double cost = launch_cost(cand[k], blocks, zc);
@@ -930,6 +1163,8 @@ int plan_maps(const StepGrid *const *grids, const int *rounds, int n, const Cand
 // state w^m comes from memory all the same: 24 windows (175 MB) 99 -> 92 us, 240 x
 // 240 x 200 with illumination (276 MB) 85 -> 88.
 constexpr double kCachedBytes = 256e6;
+// Forward steps over more than this run their blocks in tile order (tile_of).
+constexpr double kSpreadBytes = 1e9;
 
 bool step_streams(const StepGrid *const *grids, int n, int volumes) {
   double bytes = 0.0;
@@ -954,8 +1189,10 @@ StepPlan plan_forward(const StepGrid *const *grids, const Tuning *const *tu, int
   p.stream = step_streams(grids, n, 3 + (vd ? 1 : 0) + (out_of_place ? 1 : 0));
   Candidate c[2] = {forward_candidate(tu[0]->variant, vd, fs, p.stream), {}};
   int nc = 1;
-  if (tu[0]->variant == 0 && !tuned) c[nc++] = forward_candidate(5, vd, fs, p.stream);
+  if (tu[0]->variant == 0 && !tuned) c[nc++] = forward_candidate(p.stream ? 1 : 5, vd, fs, p.stream);
   p.shape = plan_maps(grids, rounds.data(), n, c, nc, maps);
+  const double bytes = 4.0 * (vd ? 4 : 3) * (double)grids[0]->nx * grids[0]->ny * grids[0]->nz;
+  if (n == 1 && bytes > kSpreadBytes) maps[0].spread = 1;
   return p;
 }
 
@@ -984,27 +1221,41 @@ StepPlan plan_adjoint(const StepGrid *const *grids, const Tuning *const *tu, int
 
 hipError_t launch_forward_step(const StepPlan &plan, const TileMap &map, const StepGrid &g,
                                const float *cur, const float *prev, float *out, const Source &src,
-                               int n, const RecTable *rec, const float *rec_scale, float *seis_tm,
-                               hipStream_t stream) {
-  const RecTable none{};
-  const RecTable &r = rec ? *rec : none;
-  float *rec_out = rec ? seis_tm : nullptr;
+                               int n, const Record &rec, float *row, hipStream_t stream) {
   return with_forward(plan.shape, g.m2 != nullptr, g.zs != kNoSurface, plan.stream,
                       [&](auto S, auto VD, auto FS, auto NT) {
     using Sh = decltype(S);
-    hipLaunchKernelGGL((k_forward<TileOf<Sh>, decltype(VD)::value, decltype(FS)::value,
+    hipLaunchKernelGGL((k_forward<Sh, decltype(VD)::value, decltype(FS)::value,
                                   decltype(NT)::value>),
-                       dim3(map.nblocks), dim3(Sh::NTHREADS), 0, stream, g, cur, prev, out, src, n,
-                       r, rec_scale, rec_out, map);
+                       dim3(map.nblocks + (row ? record_blocks(rec.nrec) : 0)),
+                       dim3(Sh::NTHREADS), 0, stream, g, cur, prev, out, src, n, rec, row, map);
     return hipGetLastError();
   });
+}
+
+int window_blocks(const TileMap &map, int nrec) { return map.nblocks + record_blocks(nrec); }
+
+hipError_t launch_record_windows(const WindowStep *wins, int nwin, int nrec_max, int n,
+                                 hipStream_t stream) {
+  if (nrec_max <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_record_windows, dim3(record_blocks(nrec_max), nwin), dim3(kRecordBlock), 0,
+                     stream, wins, n);
+  return hipGetLastError();
+}
+
+hipError_t launch_record_pool(const GradWindow *wins, int nwin, int nrec_max, int n, int cur_k,
+                              hipStream_t stream) {
+  if (nrec_max <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_record_pool, dim3(record_blocks(nrec_max), nwin), dim3(kRecordBlock), 0,
+                     stream, wins, n, cur_k);
+  return hipGetLastError();
 }
 
 hipError_t launch_forward_multi(const StepPlan &plan, const WindowStep *wins, int nwin,
                                 int nblocks, int n, bool vd, bool fs, hipStream_t stream) {
   return with_forward(plan.shape, vd, fs, plan.stream, [&](auto S, auto VD, auto FS, auto NT) {
     using Sh = decltype(S);
-    hipLaunchKernelGGL((k_forward_multi<TileOf<Sh>, decltype(VD)::value, decltype(FS)::value,
+    hipLaunchKernelGGL((k_forward_multi<Sh, decltype(VD)::value, decltype(FS)::value,
                                         decltype(NT)::value>),
                        dim3(nblocks), dim3(Sh::NTHREADS), 0, stream, wins, nwin, n);
     return hipGetLastError();
@@ -1016,7 +1267,7 @@ hipError_t launch_forward_pool(const StepPlan &plan, const GradWindow *wins, int
                                bool fs, hipStream_t stream) {
   return with_forward(plan.shape, vd, fs, plan.stream, [&](auto S, auto VD, auto FS, auto NT) {
     using Sh = decltype(S);
-    hipLaunchKernelGGL((k_forward_pool<TileOf<Sh>, decltype(VD)::value, decltype(FS)::value,
+    hipLaunchKernelGGL((k_forward_pool<Sh, decltype(VD)::value, decltype(FS)::value,
                                        decltype(NT)::value>),
                        dim3(nblocks), dim3(Sh::NTHREADS), 0, stream, wins, nwin, n, cur_k, prev_k,
                        out_k, record);
