@@ -1345,9 +1345,11 @@ hipError_t launch_conv(int cin, int cout, const uint16_t *in, int nx, int ny, in
 
 int cnn_wgrad_blocks(int nx, int ny, int nz) { return std::min(wg_tiles(nx, ny, nz), WG_MAXB); }
 
-// one row of partials per block, for the layer with the longest row
+// The published size, which callers may have laid out: four rows of the longest
+// layer per block and one per 32 of those.  The kernels use one row per block.
 size_t cnn_wgrad_workspace_floats(int nx, int ny, int nz) {
-  return (size_t)cnn_wgrad_blocks(nx, ny, nz) * wg_row(16, 16);
+  const size_t rows = 4 * (size_t)cnn_wgrad_blocks(nx, ny, nz);
+  return (rows + (rows + 31) / 32) * wg_row(16, 16);
 }
 
 hipError_t launch_wgrad(int cin, int cout, const uint16_t *in, const uint16_t *dz, int nx, int ny,
