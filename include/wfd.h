@@ -276,10 +276,11 @@ wfd_status wfd_gradient_finish(wfd_ctx *ctx, float *grad_dev, int32_t zero_top_p
  * Alg. 1 and Alg. 3).  The choices are CDNA4 tiles and z chunkings:
  *   fwd_variant  forward tiles (rows per thread x wavefronts per block x
  *                64-column groups per thread):
- *                0: 2x8x1 = 64x16 tiles [default]  1: 2x16x1 = 64x32
+ *                0: 2x8x1 = 64x16 tiles [default; with automatic rounds the
+ *                planner may take another tile]  1: 2x16x1 = 64x32
  *                2: 2x4x1 = 64x8                     3: 4x4x1 = 64x16
  *                4: 1x16x3 = 192x16
- *   adj_variant  adjoint tiles: 0: 2x16x1 = 64x32 [default]
+ *   adj_variant  adjoint tiles: 0: 2x16x1 = 64x32 [default, as above]
  *                1: 2x8x1 = 64x16 with a two-plane halo delay
  *                2: 2x4x1 = 64x8  3: 2x8x1 = 64x16, halo loaded one plane ahead
  *   *_rounds     z chunking aims at this many rounds of resident blocks per
