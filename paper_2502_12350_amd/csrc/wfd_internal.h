@@ -30,6 +30,12 @@ struct StepGrid {
 };
 constexpr int kNoSurface = -(1 << 24);
 
+// Plane whose table entry a plane loop reads ahead at plane z, 0 <= z <= nz (the
+// last turn reads ahead from past the grid): the next plane, or the last one.
+__host__ __device__ inline int next_plane(int z, int nz) {
+  return z + 1 < nz ? z + 1 : nz - 1;
+}
+
 // Receivers grouped by (y, x) column of the padded grid.  Entry e is one
 // distinct receiver node at depth ent_z[e]; in the order of columns and depths,
 // the receivers sharing it are numbers ent_rp[e] .. ent_rp[e+1] - 1.  col_start

@@ -415,7 +415,7 @@ __device__ __forceinline__ void forward_tile(
 #pragma unroll
       for (int p = 0; p < NP; ++p) f.m[p] = ld_plane<NT>(rm, ob[p]);
     }
-    f.gz = g.gz[z + 1 < g.nz ? z + 1 : z];
+    f.gz = g.gz[next_plane(z, g.nz)];
   };
 #pragma unroll
   for (int i = 0; i < 9; ++i) {
