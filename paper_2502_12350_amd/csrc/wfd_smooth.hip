@@ -463,7 +463,10 @@ __global__ void __launch_bounds__(256)
   const double an = rint(a);
   const bool on = fabs(a - an) < 1e-12;  // on an input sample
   const double aw = on ? -0.5 : a;  // an on-sample column's weights are unused
-  const double scale = sin(M_PI * a) / M_PI;
+  // sin(pi a) of the exact remainder: of a itself its error is a ulp of a, as
+  // large as a position a rounding off its sample is away (1.2 or 0.1 for 1 past
+  // sample 8192)
+  const double scale = ((int64_t)an & 1 ? -sinpi(a - an) : sinpi(a - an)) / M_PI;
   const bool hit = on && an >= 0.0 && an < (double)nt_in;
   const int64_t rows = (int64_t)(gridDim.x / col_blocks) * (16 * RT);
   for (int64_t r0 = (int64_t)rb * (16 * RT); r0 < nrec; r0 += rows) {

@@ -146,3 +146,21 @@ def test_bessel_blocks(shape):
         assert np.linalg.norm(out.cpu().numpy() - ref) <= 1e-5 * np.linalg.norm(g)
     out, it = smooth(torch.zeros(shape, device="cuda"), "bessel", lens, H)
     assert it == 0 and float(out.abs().max()) == 0.0
+
+
+@pytest.mark.parametrize("dt_in, dt_out, nt_in, nt_out", [
+    (1.0e-3, 0.7e-3, 9000, 12600), (4.0e-3, 1.6e-3, 8600, 21300)])
+def test_sinc_resampling_far_along_a_trace(dt_in, dt_out, nt_in, nt_out):
+    """Positions past 8192 samples that miss their sample by a rounding of the
+    position (more than the 1e-12 within which a position counts as on it).
+    FP64 sums rounded once to FP32: 2^-24 of each value; the oracle's and the
+    kernel's positions differ by a few 1e-12 samples, which moves a value by
+    less than 1e-10 of the largest."""
+    torch = gpu_or_skip()
+    from oracle import resample as ors
+    from paper_2502_12350_amd import resample
+    d = np.random.default_rng(11).standard_normal((2, nt_in)).astype(np.float32)
+    ref = ors.resample(d, dt_in, nt_out, dt_out, "sinc")
+    got = resample(torch.from_numpy(d).cuda(), dt_in, nt_out, dt_out, "sinc").cpu().numpy()
+    err = np.abs(got - ref) - 2.0 ** -24 * np.abs(ref)
+    assert float(err.max()) <= 1e-9 * float(np.abs(d).max())
