@@ -2131,7 +2131,7 @@ wfd_status wfd_smooth(int32_t mode, const float *in, float *out, int32_t nx, int
     for (int d = 0; d < 3; ++d) {
       if (lengths[d] <= 0.0) continue;
       HIP_TRY(wfd::launch_tri_lines(src, out, d, len[d], lines[d], nx, ny,
-                                    spacing[d] / lengths[d], st));
+                                    spacing[d] / lengths[d], static_cast<double *>(work), st));
       src = out;
     }
     if (src != out)

@@ -270,8 +270,10 @@ hipError_t launch_pack_input(const float *grad, const float *illum, int64_t n, f
                              float *partial, int npart, uint16_t *out, hipStream_t stream);
 
 // ---- gradient smoothing kernels (wfd_smooth.hip) ----
+// Laplace filter along one axis.  table: 2 n doubles of scratch.
+int tri_tile_lines(int axis, int n, int64_t nlines);
 hipError_t launch_tri_lines(const float *in, float *out, int axis, int n, int64_t nlines, int nx,
-                            int ny, double h_over_l, hipStream_t stream);
+                            int ny, double h_over_l, double *table, hipStream_t stream);
 // Bessel filter: conjugate gradients with device-side scalars.  vols holds
 // three volumes (r and two of p), scratch cg_scratch_bytes() bytes.  start:
 // r = in, x = 0.  iteration k = 0, 1, ..: nothing once rr <= tol2 <in, in>.

@@ -24,6 +24,8 @@ namespace {
 
 constexpr int kCgBlocks = 2048;  // blocks of a conjugate-gradient kernel: 8 per CU
 constexpr size_t kTileBytes = 64 << 10;  // LDS of a block's lines: two blocks per CU at least
+constexpr size_t kCuLds = 160 << 10;
+constexpr double kCachedBytes = 256e6;  // last-level cache
 
 // Line L of an axis: first point and stride between consecutive points.
 __device__ __forceinline__ void line_of(int axis, int64_t L, int nx, int ny, int64_t &base,
@@ -134,10 +136,17 @@ __global__ void __launch_bounds__(256)
   }
 }
 
-// Lines too long for a tile (over kTileBytes even at 8 lines): one thread
+// The rows' coefficients, for the kernel below.
+__global__ void __launch_bounds__(256) k_tri_rows(TriRow *__restrict__ row, int n, double log_a,
+                                                  double a) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n) row[i] = tri_row(i, n, log_a, a);
+}
+
+// Lines that a tile does not take or takes longer (tri_tile_lines): one thread
 // marches each line in memory.
 __global__ void k_tri_lines(const float *in, float *out, int axis, int n, int64_t nlines, int nx,
-                            int ny, double log_a, double a) {
+                            int ny, const TriRow *__restrict__ row) {
   const int64_t L = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (L >= nlines) return;
   int64_t base, stride;
@@ -145,14 +154,13 @@ __global__ void k_tri_lines(const float *in, float *out, int axis, int n, int64_
   double d = 0.0;
   for (int i = 0; i < n; ++i) {
     const int64_t p = base + (int64_t)i * stride;
-    const TriRow t = tri_row(i, n, log_a, a);
-    d = fma(t.c, d, t.s * (double)in[p]);
+    d = fma(row[i].c, d, row[i].s * (double)in[p]);
     out[p] = (float)d;
   }
   double x = d;
   for (int i = n - 2; i >= 0; --i) {
     const int64_t p = base + (int64_t)i * stride;
-    x = fma(tri_row(i, n, log_a, a).c, x, (double)out[p]);
+    x = fma(row[i].c, x, (double)out[p]);
     out[p] = (float)x;
   }
 }
@@ -320,32 +328,75 @@ CgGrid cg_grid(int nx, int ny, int nz, float cx, float cy, float cz) {
   return g;
 }
 
+constexpr int tri_pad(int n) { return n | 1; }  // odd: a wavefront's x lines start in different banks
+
+size_t tri_tile_bytes(int axis, int n, int nl) {
+  return (size_t)n * sizeof(TriRow) + (size_t)nl * (axis == 0 ? tri_pad(n) : n) * sizeof(float);
+}
+
 }  // namespace
 
-hipError_t launch_tri_lines(const float *in, float *out, int axis, int n, int64_t nlines, int nx,
-                            int ny, double h_over_l, hipStream_t stream) {
-  const double a = std::exp(-h_over_l);
+// Lines of a tile of an axis' n-point lines, 0 where each line is marched in
+// memory.
+int tri_tile_lines(int axis, int n, int64_t nlines) {
   // As many lines per block, 64 at most, as fit the LDS tile; fewer where
   // that leaves compute units without a block (200 x 200 x 160, three axes: 78
   // us with at least one block a unit, 83 with two, 95 with four).
-  const int pad = n | 1;  // odd: a wavefront's x lines start in different banks
-  auto bytes = [&](int nl) {
-    return (size_t)n * sizeof(TriRow) + (size_t)nl * (axis == 0 ? pad : n) * sizeof(float);
-  };
   int nl = 64;
-  while (nl > 8 && (bytes(nl) > kTileBytes || nlines < (int64_t)nl * 256)) nl /= 2;
-  if (bytes(nl) > kTileBytes) {
+  while (nl > 8 && (tri_tile_bytes(axis, n, nl) > kTileBytes || nlines < (int64_t)nl * 256))
+    nl /= 2;
+  if (tri_tile_bytes(axis, n, nl) > kTileBytes) return 0;
+  if (axis == 0) return nl;  // 40000 lines of 1300: 760 us against 1340
+  // Along y and z a march is coalesced and every line is a thread, while a tile
+  // holds a few lines of a long axis and only they march.  In us per point of a
+  // line: tiles 0.093 a round of resident blocks plus 8 B a point at 5 TB/s; a
+  // march 0.55 (its latency) and more with the lines, less past 100000 of them.
+  // Calls over one axis, tile / march, y and z (the rule's choice first where
+  // both are given): 40000 lines of 816 points 424 / 515 and 415 / 471, of 1300
+  // march 1072 for 1203 and 859 for 1227; 90000 of 600 tile 524 for 616 on y, of
+  // 1000 march 1033 for 1440 and 975 for 1449; 250000 of 240 tile 310 for 361 and
+  // 301 for 330, of 400 march 601 for 730 and 550 for 718, of 1000 march 1508 for
+  // 3766 and 1421 for 3844.
+  const double resident = std::min<double>(8.0, std::floor(kCuLds / tri_tile_bytes(axis, n, nl)));
+  const double rounds = std::ceil((double)nlines / (256.0 * resident * nl));
+  const double tile = 0.093 * rounds + 1.6e-6 * (double)nlines;
+  const double few = std::min(1e5, (double)nlines), more = (double)nlines - few;
+  const double march = axis == 1 ? 0.55 + 5.0e-6 * few + 2.6e-6 * more
+                                 : 0.55 + 3.6e-6 * few + 2.2e-6 * more;
+  return tile <= march ? nl : 0;
+}
+
+hipError_t launch_tri_lines(const float *in, float *out, int axis, int n, int64_t nlines, int nx,
+                            int ny, double h_over_l, double *table, hipStream_t stream) {
+  const double a = std::exp(-h_over_l);
+  const int nl = tri_tile_lines(axis, n, nlines);
+  if (nl == 0) {
+    // In place along x (half the cache lines: 90000 lines of 1400 points 2816 us
+    // against 2946) and where the volume fits the last-level cache, which the copy
+    // leaves it in (40000 z lines of 1300 859 / 977; 90000 of 816, 294 MB, 862 /
+    // 788).
+    const int64_t points = (int64_t)n * nlines;
+    if (in != out && (axis == 0 || 4.0 * (double)points <= kCachedBytes)) {
+      const hipError_t e = hipMemcpyAsync(out, in, (size_t)points * sizeof(float),
+                                          hipMemcpyDeviceToDevice, stream);
+      if (e != hipSuccess) return e;
+      in = out;
+    }
+    TriRow *row = reinterpret_cast<TriRow *>(table);
+    hipLaunchKernelGGL(k_tri_rows, dim3((n + 255) / 256), dim3(256), 0, stream, row, n, -h_over_l,
+                       a);
     hipLaunchKernelGGL(k_tri_lines, dim3((unsigned)((nlines + 255) / 256)), dim3(256), 0, stream,
-                       in, out, axis, n, nlines, nx, ny, -h_over_l, a);
+                       in, out, axis, n, nlines, nx, ny, row);
     return hipGetLastError();
   }
   const dim3 grid((unsigned)((nlines + nl - 1) / nl));
+  const size_t lds = tri_tile_bytes(axis, n, nl);
   if (axis == 0)
-    hipLaunchKernelGGL(k_tri_tile<true>, grid, dim3(256), bytes(nl), stream, in, out, n, nlines,
-                       nx, ny, axis, nl, pad, -h_over_l, a);
+    hipLaunchKernelGGL(k_tri_tile<true>, grid, dim3(256), lds, stream, in, out, n, nlines, nx, ny,
+                       axis, nl, tri_pad(n), -h_over_l, a);
   else
-    hipLaunchKernelGGL(k_tri_tile<false>, grid, dim3(256), bytes(nl), stream, in, out, n, nlines,
-                       nx, ny, axis, nl, pad, -h_over_l, a);
+    hipLaunchKernelGGL(k_tri_tile<false>, grid, dim3(256), lds, stream, in, out, n, nlines, nx,
+                       ny, axis, nl, tri_pad(n), -h_over_l, a);
   return hipGetLastError();
 }
 

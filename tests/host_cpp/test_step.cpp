@@ -1,5 +1,6 @@
 // Host unit tests of the step kernels' host-side rules (csrc/wfd_internal.h,
-// csrc/wfd_step.hip): the index of the tables that a plane loop reads ahead.
+// csrc/wfd_step.hip) and of the filters': the index of the tables that a plane loop
+// reads ahead, and which Laplace lines go through tiles.
 // Built with g++ against libwfd.so and run without a GPU by
 // tests/test_host_step.py.
 #include <algorithm>
@@ -33,8 +34,23 @@ static void test_read_ahead() {
       }
 }
 
+// Laplace lines marched in memory (0) or in tiles of so many lines.
+static void test_laplace_rule() {
+  // long axes with many lines march, on either side of the rule
+  const int64_t march[][3] = {{1, 1300, 40000},  {2, 1300, 40000}, {2, 1000, 40000},
+                              {1, 1000, 90000},  {2, 700, 90000},  {1, 400, 250000},
+                              {2, 1000, 250000}, {1, 240, 490000}, {2, 1400, 1},
+                              {0, 1400, 40000}};
+  for (const auto &c : march) CHECK(wfd::tri_tile_lines((int)c[0], (int)c[1], c[2]) == 0);
+  const int64_t tile[][4] = {{0, 200, 32000, 64}, {1, 200, 32000, 64}, {2, 160, 40000, 64},
+                             {0, 1300, 90000, 8}, {1, 816, 40000, 16}, {2, 816, 40000, 16},
+                             {1, 600, 90000, 16}, {2, 240, 250000, 64}, {2, 1300, 400, 8}};
+  for (const auto &c : tile) CHECK(wfd::tri_tile_lines((int)c[0], (int)c[1], c[2]) == c[3]);
+}
+
 int main() {
   test_read_ahead();
+  test_laplace_rule();
   if (failures) return 1;
   std::printf("ALL PASSED\n");
   return 0;

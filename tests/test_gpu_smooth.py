@@ -164,3 +164,21 @@ def test_sinc_resampling_far_along_a_trace(dt_in, dt_out, nt_in, nt_out):
     got = resample(torch.from_numpy(d).cuda(), dt_in, nt_out, dt_out, "sinc").cpu().numpy()
     err = np.abs(got - ref) - 2.0 ** -24 * np.abs(ref)
     assert float(err.max()) <= 1e-9 * float(np.abs(d).max())
+
+
+@pytest.mark.parametrize("shape, axis", [
+    ((901, 190, 211), 2), ((30, 1100, 1500), 1), ((1402, 199, 251), 2), ((70, 31, 1399), 0)])
+def test_laplace_marched_lines(shape, axis):
+    """Lines marched in memory: copied first (a volume in the last-level cache, x
+    lines) or from the input, and in place.  Two FP32 roundings along the axis."""
+    torch = gpu_or_skip()
+    from paper_2502_12350_amd import smooth
+    g = np.random.default_rng(13).standard_normal(shape).astype(np.float32)
+    lens = [0.0, 0.0, 0.0]
+    lens[axis] = 30.0
+    ref = osm.laplace_filter(g, lens, H)
+    x = torch.from_numpy(g).cuda()
+    out, _ = smooth(x, "laplace", lens, H)
+    assert float(np.abs(out.cpu().numpy() - ref).max()) <= 2 * 2.0 ** -24 * float(np.abs(g).max())
+    smooth(x, "laplace", lens, H, out=x)
+    assert torch.equal(x, out)
