@@ -346,6 +346,8 @@ int tri_tile_lines(int axis, int n, int64_t nlines) {
   while (nl > 8 && (tri_tile_bytes(axis, n, nl) > kTileBytes || nlines < (int64_t)nl * 256))
     nl /= 2;
   if (tri_tile_bytes(axis, n, nl) > kTileBytes) return 0;
+  // a launch takes less than 2^32 threads (the march one a line)
+  if ((nlines + nl - 1) / nl * 256 >= (int64_t(1) << 32)) return 0;
   if (axis == 0) return nl;  // 40000 lines of 1300: 760 us against 1340
   // Along y and z a march is coalesced and every line is a thread, while a tile
   // holds a few lines of a long axis and only they march.  In us per point of a

@@ -42,6 +42,9 @@ static void test_laplace_rule() {
                               {2, 1000, 250000}, {1, 240, 490000}, {2, 1400, 1},
                               {0, 1400, 40000}};
   for (const auto &c : march) CHECK(wfd::tri_tile_lines((int)c[0], (int)c[1], c[2]) == 0);
+  // more blocks than a launch takes: planes of 2^30 points and more
+  CHECK(wfd::tri_tile_lines(2, 1, int64_t(1) << 30) == 0);
+  CHECK(wfd::tri_tile_lines(1, 3, (int64_t(1) << 30) + 5) == 0);
   const int64_t tile[][4] = {{0, 200, 32000, 64}, {1, 200, 32000, 64}, {2, 160, 40000, 64},
                              {0, 1300, 90000, 8}, {1, 816, 40000, 16}, {2, 816, 40000, 16},
                              {1, 600, 90000, 16}, {2, 240, 250000, 64}, {2, 1300, 400, 8}};
