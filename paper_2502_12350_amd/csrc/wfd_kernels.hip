@@ -242,22 +242,26 @@ __device__ __forceinline__ void fold_range(int i, int n, int border, int &lo, in
 // rows each; the others one inner row per wavefront.  Lanes run along x, and the
 // border cells of a row's two ends are summed across the lanes.  240 x 240 x 200
 // to 200 x 200 x 160: 61 us (1058 with one thread per model cell, whose corner
-// cells summed 9261 values each).
+// cells summed 9261 values each).  first_block: of this launch, where the fold
+// takes several (32 bits: a row of g is 256 bytes at least, so that 2^31 rows fit
+// no device).
 constexpr int kFoldWaves = 16;
+constexpr int64_t kFoldBlocks = 1 << 20;  // blocks of a launch: under 2^32 threads
 
 __global__ void __launch_bounds__(kFoldWaves * 64)
     k_grad_fold(const float *__restrict__ g, const float *__restrict__ k, int pitch, int pny,
                 int border, int mnx, int mny, int mnz, double dt,
                 const ShotScale *__restrict__ sc, int out_exp2, float *__restrict__ grad,
-                int face_rows) {
+                int face_rows, uint32_t first_block) {
   __shared__ double part[kFoldWaves][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t plane = (int64_t)pitch * pny;
-  const bool face = (int)blockIdx.x < face_rows;
+  const uint32_t block = first_block + blockIdx.x;
+  const bool face = (int)block < face_rows;
   int iy, iz;
   if (face) {  // rows of the z faces, then the y faces' others
     const int zf = mnz > 1 ? 2 : 1, yf = mny > 1 ? 2 : 1;
-    int r = blockIdx.x;
+    int r = (int)block;
     if (r < zf * mny) {
       iz = r < mny ? 0 : mnz - 1;
       iy = r < mny ? r : r - mny;
@@ -267,7 +271,7 @@ __global__ void __launch_bounds__(kFoldWaves * 64)
       iy = r % yf ? mny - 1 : 0;
     }
   } else {
-    const int64_t r = (int64_t)(blockIdx.x - face_rows) * kFoldWaves + wave;
+    const int64_t r = (int64_t)(block - face_rows) * kFoldWaves + wave;
     if (r >= (int64_t)(mny - 2) * (mnz - 2)) return;
     iz = 1 + (int)(r / (mny - 2));
     iy = 1 + (int)(r % (mny - 2));
@@ -396,13 +400,13 @@ hipError_t launch_transpose(const float *src_tm, float *dst_rm, int nrec, int nt
 hipError_t launch_grad_fold(const float *g, const float *k, int pitch, int pny, int border,
                             int mnx, int mny, int mnz, double dt, const ShotScale *sc,
                             int out_exp2, float *grad, hipStream_t stream) {
-  const int zf = mnz > 1 ? 2 : 1, yf = mny > 1 ? 2 : 1;
-  const int inner_y = std::max(0, mny - 2), inner_z = std::max(0, mnz - 2);
-  const int face_rows = zf * mny + yf * inner_z;
-  const int64_t inner = ((int64_t)inner_y * inner_z + kFoldWaves - 1) / kFoldWaves;
-  hipLaunchKernelGGL(k_grad_fold, dim3((unsigned)(face_rows + inner)), dim3(kFoldWaves * 64), 0,
-                     stream, g, k, pitch, pny, border, mnx, mny, mnz, dt, sc, out_exp2, grad,
-                     face_rows);
+  const int64_t inner_y = std::max(0, mny - 2), inner_z = std::max(0, mnz - 2);
+  const int64_t face_rows = (mnz > 1 ? 2 : 1) * (int64_t)mny + (mny > 1 ? 2 : 1) * inner_z;
+  const int64_t blocks = face_rows + (inner_y * inner_z + kFoldWaves - 1) / kFoldWaves;
+  for (int64_t b = 0; b < blocks; b += kFoldBlocks)
+    hipLaunchKernelGGL(k_grad_fold, dim3((unsigned)std::min(kFoldBlocks, blocks - b)),
+                       dim3(kFoldWaves * 64), 0, stream, g, k, pitch, pny, border, mnx, mny, mnz,
+                       dt, sc, out_exp2, grad, (int)face_rows, (uint32_t)b);
   return hipGetLastError();
 }
 

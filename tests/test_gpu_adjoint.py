@@ -402,3 +402,35 @@ def test_gradient_fold_edges_match_oracle(n, N, fs):
     say(f"[fold] model {n} border {N}: gradient rel-L2 {e:.2e}")
     assert e <= 1e-3
     assert abs(float(J.item()) - ref.misfit) <= 1e-4 * ref.misfit
+
+
+def test_gradient_fold_of_more_rows_than_one_launch_takes():
+    # 4.3 million rows of one cell: 1024 threads a row would pass the 2^32
+    # threads of a launch
+    torch = gpu_or_skip()
+    from paper_2502_12350_amd import GridSpec, Propagator
+    ny, nt, h = 4_300_000, 12, 10.0
+    vel = np.full((1, ny, 1), 2500.0, np.float32)
+    dt = 0.4 * h / 3000.0
+    wav = np.sin(0.5 * np.arange(nt)).astype(np.float32)
+    kw = dict(dx=h, dy=h, dz=h, border=0, dt=dt, nt=nt)
+    P = Propagator(0)
+    P.set_model(GridSpec(1, ny, 1, **kw), torch.from_numpy(vel).cuda())
+    for y in (3, 1_100_000, ny - 4):   # in the first launch, a later one and the last
+        lo = max(0, min(y - 100, ny - 201))   # the wave stays within 4 cells a step of y
+        gw = oracle.Grid(1, 201, 1, **kw)
+        ys, src = y - lo, [0.0, (y - lo) * h, 0.0]
+        rec = np.array([[0.0, (ys + d) * h, 0.0] for d in (-2, 0, 3)])
+        small = vel[:, :201]
+        dobs = (0.5 * oracle.forward(gw, small, None, wav, src, rec).seis).astype(np.float32)
+        ref = oracle.gradient(gw, small, None, wav, src, rec, dobs)
+        shift = np.array([0.0, lo * h, 0.0])
+        J, gr = P.gradient(torch.from_numpy(wav).cuda(), src + shift, rec + shift,
+                           torch.from_numpy(dobs).cuda(), ckpt="full")
+        torch.cuda.synchronize()
+        got = gr.cpu().numpy()
+        e = rel_l2(got[:, lo:lo + 201], ref.grad)
+        say(f"[fold] row {y} of {ny}: gradient rel-L2 {e:.2e}")
+        assert e <= GRAD_TOL and abs(float(J.item()) - ref.misfit) <= 1e-4 * ref.misfit
+        got[:, lo:lo + 201] = 0.0
+        assert not got.any()
