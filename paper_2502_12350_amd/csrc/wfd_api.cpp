@@ -438,7 +438,6 @@ Work work_layout(const wfd_ctx *c, int nrec, WorkKind kind, const wfd_ckpt *ck, 
     for (int i = 0; i < 6; ++i) w.mem[i] = cv.take<float>((size_t)mem_len(c, i));
     if (kind == WorkKind::Gradient && ck && ck->mode == WFD_CKPT_FULL)
       w.cstore = cv.take<float>((size_t)c->grid.nt * S);
-    if (kind != WorkKind::Gradient) w.lastc = cv.take<float>(std::max<size_t>(S, 1));
     if (kind == WorkKind::Gradient && ck && ck->mode == WFD_CKPT_REVOLVE) {
       for (int i = 0; i < 6; ++i) w.amem[i] = cv.take<float>((size_t)mem_len(c, i));
       w.smem = cv.take<float>((size_t)nsnap * (size_t)mem_set_len(c));
@@ -863,8 +862,7 @@ wfd_status cpml_forward_terms(wfd_ctx *c, const wfd::StepGrid &g, const Work &w,
                               float *const *mem = nullptr) {
   Timed t(c, WFD_K_OTHER);
   float *const *m = mem ? mem : w.mem;  // out == nullptr: only the memory variables and C
-  HIP_TRY(wfd::launch_cpml_forward(g, c->cpml_tab, c->shell, cur, m, out,
-                                   cstore ? cstore : w.lastc, cstore != nullptr, c->stream));
+  HIP_TRY(wfd::launch_cpml_forward(g, c->cpml_tab, c->shell, cur, m, out, cstore, c->stream));
   return WFD_OK;
 }
 

@@ -331,11 +331,10 @@ struct Shell {
 // cur.  mem: psi_x, psi_y, psi_z, zeta_x, zeta_y, zeta_z.  psi_d = b psi_d + a
 // D1_d w (w = cur) and zeta_d = b zeta_d + a (D2_d w + D1_d psi_d) on the
 // layer; C = sum_d (D1_d psi_d + zeta_d); out += k C below the free surface
-// (out nullptr: not).  cstore (sh.points floats) holds C afterwards with keep,
-// else it is scratch.
+// (out nullptr: not).  cstore (sh.points floats, or nullptr) holds C afterwards.
 hipError_t launch_cpml_forward(const StepGrid &g, const CpmlTables &t, const Shell &sh,
                                const float *cur, float *const mem[6], float *out, float *cstore,
-                               bool keep, hipStream_t stream);
+                               hipStream_t stream);
 // The layer's share of an adjoint step, after the step kernel wrote phi from
 // phi1.  mem: mu_x, mu_y, mu_z, nu_x, nu_y, nu_z.  nu_d = phi1 + b nu_d and
 // mu_d = b mu_d - D1_d (a nu_d + phi1) on the layer; phi += k [D2_d (a nu_d) -

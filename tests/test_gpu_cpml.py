@@ -255,3 +255,55 @@ def test_cpml_tile_shapes_match_oracle(n, N, fs):
     say(f"  seismograms rel-L2 {es:.2e}, gradient {eg:.2e}")
     assert es <= SEIS_TOL and eg <= GRAD_TOL
     assert abs(float(J.item()) - ref.misfit) <= SEIS_TOL * ref.misfit
+
+
+@pytest.mark.parametrize("n,N,fs", [
+    ((70, 18, 40), 8, False), ((33, 20, 17), 20, True), ((24, 40, 60), 32, False),
+    ((18, 17, 17), 50, False), ((16, 12, 14), 45, True), ((40, 30, 3), 8, True),
+    ((5, 40, 30), 8, False), ((30, 6, 40), 8, False), ((2, 3, 4), 30, False)])
+def test_cpml_forward_equals_the_gradients_forward_sweep_bitwise(n, N, fs):
+    # a forward sweep keeps no correction store and forms the terms of crossing
+    # layers again; the source and the receivers are on the model's edges and
+    # corners, next to the crossings
+    torch = gpu_or_skip()
+    from paper_2502_12350_amd import GridSpec, Propagator
+    nx, ny, nz = n
+    nt, h = 60, 10.0
+    vel = torch.from_numpy(seisgen.layered_model(7, n, 0.05)).cuda()
+    dt = 0.4 * h / float(vel.max())
+    t = np.arange(nt) * dt
+    a = (np.pi * 40.0 * (t - 0.02)) ** 2
+    wav = torch.from_numpy(((1 - 2 * a) * np.exp(-a)).astype(np.float32)).cuda()
+    src = [0.0, 0.0, min(2, nz - 1) * h]
+    rec = np.array([[h * i, h * j, h * k] for i in (0, nx // 2, nx - 1)
+                    for j in (0, ny // 2, ny - 1) for k in (0, nz // 2, nz - 1)])
+    say(f"[cpml forward] model {n} border {N} free surface {fs}")
+    P = Propagator(0)
+    P.set_model(GridSpec(nx, ny, nz, h, h, h, border=N, dt=dt, nt=nt, cpml=True, fpeak=FPEAK,
+                         cpml_vmax=VMAX, free_surface=fs), vel)
+    dobs = torch.zeros((len(rec), nt), device="cuda")
+    J, _, seis = P.gradient(wav, src, rec, dobs, ckpt="full", seis=True)
+    Jf, sm = P.forward_misfit(wav, src, rec, dobs, seis=True)
+    assert float(J) > 0.0
+    assert torch.equal(P.forward(wav, src, rec), seis)
+    assert torch.equal(sm, seis) and float(Jf) == float(J)
+
+
+def test_cpml_forward_workspace_holds_no_correction():
+    # two volumes, six memory variables and tables of a 150^3 grid: within the
+    # library's static scratch, and with a correction of the layer's 9 MB not
+    torch = gpu_or_skip()
+    from paper_2502_12350_amd import GridSpec, Propagator, _lib
+    from paper_2502_12350_amd.api import _dptr, _xyz
+    n, nt, h = 110, 20, 10.0
+    vel = torch.full((n, n, n), 2500.0, device="cuda")
+    wav = torch.sin(torch.arange(nt, device="cuda") * 0.5)
+    P = Propagator(0)
+    P.set_model(GridSpec(n, n, n, h, h, h, border=20, dt=1e-3, nt=nt, cpml=True, fpeak=FPEAK), vel)
+    src, rec = _xyz([20.0, 20.0, 20.0]), _xyz([[0.0, 0.0, 0.0], [50.0, 20.0, 40.0]])
+    assert P.workspace_bytes(2) <= _lib.NOALLOC_SCRATCH_BYTES
+    seis = torch.zeros((2, nt), device="cuda")
+    P._sync_stream()
+    _lib.check(_lib.lib().wfd_forward_noalloc(P._ctx, wav.data_ptr(), _dptr(src), 2, _dptr(rec),
+                                              seis.data_ptr(), None))
+    assert torch.equal(seis, P.forward(wav, src, rec)) and float(seis.abs().max()) > 0.0
