@@ -23,6 +23,7 @@ K_FORWARD, K_ADJOINT, K_OTHER = 0, 1, 2
 CNN_REDUCE_BYTES = 8192
 NOALLOC_SCRATCH_BYTES = 64 << 20
 SMOOTH_LAPLACE, SMOOTH_BESSEL = 1, 2
+SMOOTH_EXTRA_BYTES = 32768
 RESAMPLE_NEAREST, RESAMPLE_SINC = 1, 2
 
 

@@ -137,12 +137,13 @@ def smooth(x, mode: str, lengths, spacing, *, tol: float = 1e-6, max_iter: int =
         out = torch.empty_like(x)
     nb = C.c_size_t()
     check(L.wfd_smooth_workspace_bytes(m, nx, ny, nz, C.byref(nb)))
-    work = torch.empty(nb.value, dtype=torch.uint8, device=x.device)
+    nbytes = nb.value + (_lib.SMOOTH_EXTRA_BYTES if m == _lib.SMOOTH_BESSEL else 0)
+    work = torch.empty(nbytes, dtype=torch.uint8, device=x.device)
     lens = np.ascontiguousarray(lengths, dtype=np.float64)
     hs = np.ascontiguousarray(spacing, dtype=np.float64)
     it = C.c_int32()
     check(L.wfd_smooth(m, _ptr(x), _ptr(out), nx, ny, nz, _dptr(lens), _dptr(hs), float(tol),
-                       int(max_iter), _ptr(work), nb.value, C.byref(it),
+                       int(max_iter), _ptr(work), nbytes, C.byref(it),
                        C.c_void_p(torch.cuda.current_stream(x.device).cuda_stream)))
     return out, it.value
 

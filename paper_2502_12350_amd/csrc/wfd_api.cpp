@@ -2086,10 +2086,14 @@ wfd_status wfd_cnn_pack_input(const float *grad, const float *illum, int64_t n, 
 // ---- gradient smoothing ------------------------------------------------------
 
 namespace {
+// The published size of the solver's scratch, which callers may have laid out: the
+// sums of 252 blocks.
+constexpr size_t kCgScratchBytes = 4096;
+
 size_t smooth_bytes(int mode, int nx, int ny, int nz) {
   const size_t vol = (size_t)nx * ny * nz;
   if (mode == WFD_SMOOTH_LAPLACE) return align_up(2 * (size_t)(nx + ny + nz) * sizeof(double));
-  return align_up(3 * vol * sizeof(float)) + align_up(wfd::cg_scratch_bytes());
+  return align_up(3 * vol * sizeof(float)) + kCgScratchBytes;
 }
 }  // namespace
 
@@ -2143,12 +2147,13 @@ wfd_status wfd_smooth(int32_t mode, const float *in, float *out, int32_t nx, int
   if (max_iter < 1) return fail(WFD_E_ARG, "max_iter must be >= 1");
   if (!(tol > 0.0)) return fail(WFD_E_ARG, "tol must be > 0");
   float *vols = static_cast<float *>(work);
-  void *scratch = static_cast<char *>(work) + align_up(3 * (size_t)n * sizeof(float));
+  const size_t vols_bytes = align_up(3 * (size_t)n * sizeof(float));
+  void *scratch = static_cast<char *>(work) + vols_bytes;
   const float cx = (float)(lengths[0] * lengths[0] / (spacing[0] * spacing[0]));
   const float cy = (float)(lengths[1] * lengths[1] / (spacing[1] * spacing[1]));
   const float cz = (float)(lengths[2] * lengths[2] / (spacing[2] * spacing[2]));
   const double tol2 = tol * tol;
-  const int blocks = wfd::cg_blocks(nx, ny, nz);
+  const int blocks = wfd::cg_blocks(nx, ny, nz, work_bytes - vols_bytes);
   HIP_TRY(wfd::launch_cg_start(in, out, vols, n, blocks, scratch, st));
   // Iterations are enqueued in groups; the host looks after each at the
   // residual and sizes the next group from its decrease so far.  Iterations
@@ -2158,7 +2163,8 @@ wfd_status wfd_smooth(int32_t mode, const float *in, float *out, int32_t nx, int
   for (int k = 0;;) {
     const int end = (int)std::min<int64_t>(max_iter, (int64_t)k + group);
     for (; k < end; ++k)
-      HIP_TRY(wfd::launch_cg_iteration(k, tol2, nx, ny, nz, cx, cy, cz, out, vols, scratch, st));
+      HIP_TRY(wfd::launch_cg_iteration(k, tol2, nx, ny, nz, cx, cy, cz, out, vols, blocks,
+                                       scratch, st));
     double *dev = nullptr, host[3];
     HIP_TRY(wfd::launch_cg_check(blocks, scratch, &dev, st));
     HIP_TRY(hipMemcpyAsync(host, dev, sizeof(host), hipMemcpyDeviceToHost, st));

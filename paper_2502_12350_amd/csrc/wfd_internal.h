@@ -275,15 +275,16 @@ int tri_tile_lines(int axis, int n, int64_t nlines);
 hipError_t launch_tri_lines(const float *in, float *out, int axis, int n, int64_t nlines, int nx,
                             int ny, double h_over_l, double *table, hipStream_t stream);
 // Bessel filter: conjugate gradients with device-side scalars.  vols holds
-// three volumes (r and two of p), scratch cg_scratch_bytes() bytes.  start:
+// three volumes (r and two of p), scratch cg_scratch_bytes(blocks) bytes.  start:
 // r = in, x = 0.  iteration k = 0, 1, ..: nothing once rr <= tol2 <in, in>.
 // check writes {rr, <in, in>, iterations} to *out (device).
-size_t cg_scratch_bytes();
-int cg_blocks(int nx, int ny, int nz);
+constexpr int kCgMaxBlocks = 2048;  // blocks of a conjugate-gradient kernel: 8 per CU
+size_t cg_scratch_bytes(int blocks);
+int cg_blocks(int nx, int ny, int nz, size_t scratch_bytes);
 hipError_t launch_cg_start(const float *in, float *x, float *vols, int64_t n, int blocks,
                            void *scratch, hipStream_t stream);
 hipError_t launch_cg_iteration(int k, double tol2, int nx, int ny, int nz, float cx, float cy,
-                               float cz, float *x, float *vols, void *scratch,
+                               float cz, float *x, float *vols, int blocks, void *scratch,
                                hipStream_t stream);
 hipError_t launch_cg_check(int blocks, void *scratch, double **out, hipStream_t stream);
 hipError_t launch_resample(const float *in, int nrec, int nt_in, double dt_in, float *out,

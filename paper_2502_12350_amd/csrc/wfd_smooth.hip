@@ -22,7 +22,6 @@
 namespace wfd {
 namespace {
 
-constexpr int kCgBlocks = 2048;  // blocks of a conjugate-gradient kernel: 8 per CU
 constexpr size_t kTileBytes = 64 << 10;  // LDS of a block's lines: two blocks per CU at least
 constexpr size_t kCuLds = 160 << 10;
 constexpr double kCachedBytes = 256e6;  // last-level cache
@@ -320,7 +319,7 @@ CgGrid cg_grid(int nx, int ny, int nz, float cx, float cy, float cz) {
   g.plane = (int64_t)nx * ny;
   g.pblocks = (g.plane + kCgBlock - 1) / kCgBlock;
   // as many z chunks as make one item per block of a full device
-  const int64_t want = std::max<int64_t>(1, std::min<int64_t>(nz, kCgBlocks / g.pblocks));
+  const int64_t want = std::max<int64_t>(1, std::min<int64_t>(nz, kCgMaxBlocks / g.pblocks));
   g.zc = (int)((nz + want - 1) / want);
   g.nch = (nz + g.zc - 1) / g.zc;
   g.items = g.pblocks * g.nch;
@@ -402,7 +401,16 @@ hipError_t launch_tri_lines(const float *in, float *out, int axis, int n, int64_
   return hipGetLastError();
 }
 
-size_t cg_scratch_bytes() { return sizeof(Cg) + (2 * kCgBlocks + 4) * sizeof(double); }
+// Scratch: Cg, the two kernels' block sums, the check's three values.
+size_t cg_scratch_bytes(int blocks) { return sizeof(Cg) + (2 * (size_t)blocks + 4) * sizeof(double); }
+
+// Blocks of a kernel: an item each, as far as the scratch has room for their sums.
+int cg_blocks(int nx, int ny, int nz, size_t scratch_bytes) {
+  const int64_t room = ((int64_t)scratch_bytes - (int64_t)cg_scratch_bytes(0)) /
+                       (int64_t)(2 * sizeof(double));
+  return (int)std::min(std::min<int64_t>(kCgMaxBlocks, room),
+                       cg_grid(nx, ny, nz, 0, 0, 0).items);
+}
 
 hipError_t launch_cg_start(const float *in, float *x, float *vols, int64_t n, int blocks,
                            void *scratch, hipStream_t stream) {
@@ -412,18 +420,13 @@ hipError_t launch_cg_start(const float *in, float *x, float *vols, int64_t n, in
   return hipGetLastError();
 }
 
-int cg_blocks(int nx, int ny, int nz) {
-  return (int)std::min<int64_t>(kCgBlocks, cg_grid(nx, ny, nz, 0, 0, 0).items);
-}
-
 hipError_t launch_cg_iteration(int k, double tol2, int nx, int ny, int nz, float cx, float cy,
-                               float cz, float *x, float *vols, void *scratch,
+                               float cz, float *x, float *vols, int blocks, void *scratch,
                                hipStream_t stream) {
   const CgGrid g = cg_grid(nx, ny, nz, cx, cy, cz);
   const int64_t n = g.plane * nz;
-  const int blocks = (int)std::min<int64_t>(kCgBlocks, g.items);
   Cg *cg = static_cast<Cg *>(scratch);
-  double *rr = reinterpret_cast<double *>(cg + 1), *pap = rr + kCgBlocks;
+  double *rr = reinterpret_cast<double *>(cg + 1), *pap = rr + blocks;
   float *r = vols, *p = vols + n * (1 + (k & 1)), *p_old = vols + n * (2 - (k & 1));
   if (k == 0)
     hipLaunchKernelGGL(k_cg_direction<true>, dim3(blocks), dim3(kCgBlock), 0, stream, g, k, tol2,
@@ -441,7 +444,7 @@ hipError_t launch_cg_iteration(int k, double tol2, int nx, int ny, int nz, float
 hipError_t launch_cg_check(int blocks, void *scratch, double **out, hipStream_t stream) {
   Cg *cg = static_cast<Cg *>(scratch);
   double *rr = reinterpret_cast<double *>(cg + 1);
-  *out = rr + 2 * kCgBlocks;
+  *out = rr + 2 * blocks;
   hipLaunchKernelGGL(k_cg_check, dim3(1), dim3(kCgBlock), 0, stream, blocks, rr, cg, *out);
   return hipGetLastError();
 }

@@ -182,3 +182,51 @@ def test_laplace_marched_lines(shape, axis):
     assert float(np.abs(out.cpu().numpy() - ref).max()) <= 2 * 2.0 ** -24 * float(np.abs(g).max())
     smooth(x, "laplace", lens, H, out=x)
     assert torch.equal(x, out)
+
+
+def _bessel_by_cosines(g, lens):
+    """B^-1 g in FP64 by the cosine bases that diagonalise the zero-flux second
+    differences (equal to the oracle's direct solve where that is feasible)."""
+    from scipy.fft import dctn, idctn
+    lam = 1.0
+    for axis in range(3):
+        n, l, h = g.shape[axis], lens[2 - axis], H[2 - axis]
+        e = (l / h) ** 2 * (2.0 - 2.0 * np.cos(np.pi * np.arange(n) / n))
+        lam = lam + e.reshape([n if a == axis else 1 for a in range(3)])
+    return idctn(dctn(g.astype(np.float64)) / lam)
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 1), (3, 5, 7), (40, 90, 70), (3, 730, 731),
+                                   (30, 200, 210)])
+def test_bessel_with_the_least_workspace(shape):
+    """Three volumes and the published 4096 bytes: fewer blocks, that take several
+    items each where there are more than 252 (and, with the full workspace, in
+    planes of more than 2048 blocks of 256 points).  Tolerance as above."""
+    torch = gpu_or_skip()
+    import ctypes as C
+    from paper_2502_12350_amd import _lib, smooth
+    from paper_2502_12350_amd.api import _dptr
+    g = np.random.default_rng(5).standard_normal(shape).astype(np.float32)
+    nz, ny, nx = shape
+    x = torch.from_numpy(g).cuda()
+    lens, h = np.array([20.0, 30.0, 12.0]), np.ascontiguousarray(H, dtype=np.float64)
+    ref = _bessel_by_cosines(g, lens)
+    if g.size < 200:
+        assert np.allclose(ref, osm.bessel_filter(g, lens, H), rtol=0, atol=1e-12)
+    nbytes = (12 * g.size + 255) // 256 * 256 + 4096
+    n = C.c_size_t()
+    _lib.check(_lib.lib().wfd_smooth_workspace_bytes(_lib.SMOOTH_BESSEL, nx, ny, nz, C.byref(n)))
+    assert n.value <= nbytes
+    out, it = torch.empty_like(x), C.c_int32()
+    # canaries on either side
+    buf = torch.full((nbytes + 2 * 4096,), 0x5a, dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    _lib.check(_lib.lib().wfd_smooth(_lib.SMOOTH_BESSEL, x.data_ptr(), out.data_ptr(), nx, ny, nz,
+                                     _dptr(lens), _dptr(h), 1e-7, 500, buf.data_ptr() + 4096,
+                                     nbytes, C.byref(it), None))
+    assert it.value >= 1
+    assert np.linalg.norm(out.cpu().numpy() - ref) <= 1e-5 * np.linalg.norm(g)
+    assert bool((buf[:4096] == 0x5a).all()) and bool((buf[4096 + nbytes:] == 0x5a).all())
+    full, it_full = smooth(x, "bessel", lens, H, tol=1e-7)
+    assert it_full == it.value
+    assert np.linalg.norm(full.cpu().numpy() - ref) <= 1e-5 * np.linalg.norm(g)
