@@ -51,7 +51,41 @@ static void test_laplace_rule() {
   for (const auto &c : tile) CHECK(wfd::tri_tile_lines((int)c[0], (int)c[1], c[2]) == c[3]);
 }
 
+// A batch whose contexts ask for rounds of the device: the windows fill it
+// together, so that each keeps chunks of 16 planes or more; a single shot takes
+// chunks down to 4.
+static void test_tuned_batch() {
+  constexpr int n = 24;
+  wfd::StepGrid g[n];
+  wfd::Tuning tu;
+  tu.rounds = tu.adj_rounds = 8;
+  const wfd::StepGrid *pg[n];
+  const wfd::Tuning *pt[n];
+  wfd::TileMap maps[n];
+  for (int i = 0; i < n; ++i) {
+    g[i] = wfd::StepGrid{};
+    g[i].nx = 60 + i, g[i].ny = 70, g[i].nz = i ? 50 + i : 9;
+    g[i].pitch = 128, g[i].plane = (int64_t)g[i].pitch * g[i].ny, g[i].zs = wfd::kNoSurface;
+    pg[i] = &g[i], pt[i] = &tu;
+  }
+  for (int adj = 0; adj < 2; ++adj) {
+    for (int count : {1, n}) {
+      if (adj)
+        wfd::plan_adjoint(pg + n - count, pt, count, false, maps);
+      else
+        wfd::plan_forward(pg + n - count, pt, count, true, maps);
+      for (int i = 0; i < count; ++i) {
+        const int nz = pg[n - count + i]->nz;
+        CHECK(maps[i].zc * maps[i].nchunks >= nz && maps[i].zc <= nz);
+        CHECK(count == 1 ? maps[i].zc == 4 : maps[i].zc >= std::min(nz, 13));
+        CHECK(count == 1 || maps[i].nchunks <= (nz + 15) / 16);
+      }
+    }
+  }
+}
+
 int main() {
+  test_tuned_batch();
   test_read_ahead();
   test_laplace_rule();
   if (failures) return 1;
