@@ -604,7 +604,7 @@ __device__ __forceinline__ void forward_block(const StepGrid &g, const float *__
 
 // Blocks from map.nblocks on record row (sample n - 1).
 template <class S, bool VD, bool FS, bool NT>
-__global__ void __launch_bounds__(S::NTHREADS)
+__global__ void __launch_bounds__(S::NTHREADS, S::WAVES)
     k_forward(StepGrid g, const float *__restrict__ cur, const float *prev, float *out,
               Source src, int n, Record rec, float *__restrict__ row, TileMap map) {
   const int b = blockIdx.x;
@@ -619,7 +619,7 @@ __global__ void __launch_bounds__(S::NTHREADS)
 // blocks of the others (24 small windows, adjoint: 138 us a step instead of
 // 78).
 template <class S, bool VD, bool FS, bool NT>
-__global__ void __launch_bounds__(S::NTHREADS)
+__global__ void __launch_bounds__(S::NTHREADS, S::WAVES)
     k_forward_multi(const WindowStep *__restrict__ wins, int nwin, int n) {
   const int b = blockIdx.x;
   int w = 0;
@@ -847,7 +847,7 @@ __device__ __forceinline__ float *pool_buffer(const GradWindow &d, int k) {
 // buffers cur_k (w^n) and prev_k (w^{n-1}) and writes out_k, recording the
 // receivers when `record` is set.
 template <class S, bool VD, bool FS, bool NT>
-__global__ void __launch_bounds__(S::NTHREADS)
+__global__ void __launch_bounds__(S::NTHREADS, S::WAVES)
     k_forward_pool(const GradWindow *__restrict__ wins, int nwin, int n, int cur_k, int prev_k,
                    int out_k, int record) {
   const int b = blockIdx.x;
@@ -920,6 +920,7 @@ int blocks_per_cu(K kernel, int threads) {
 template <int RY, int NG, int NI, int XW, int ZC_ = 0>
 struct Shape : Tile<RY, NG, NI, XW> {
   static constexpr int ZC = ZC_;  // planes of a block that does not march, else 0
+  static constexpr int WAVES = 0;  // least waves per SIMD (0: the compiler's choice)
 };
 template <int V>
 struct FwdShape;
@@ -930,7 +931,11 @@ struct FwdShape<1> : Shape<2, 16, 1, 64> {};  // 64 x 32
 template <>
 struct FwdShape<2> : Shape<2, 4, 1, 64> {};  // 64 x 8
 template <>
-struct FwdShape<3> : Shape<4, 4, 1, 64> {};  // 64 x 16
+struct FwdShape<3> : Shape<4, 4, 1, 64> {  // 64 x 16
+  // 163 VGPRs instead of 174: three blocks per CU, not two, without spills (two
+  // rounds at 296^3 VD: 102 us instead of 118; 448^3 with four 356 and 343)
+  static constexpr int WAVES = 3;
+};
 template <>
 struct FwdShape<4> : Shape<1, 16, 3, 64> {};  // 192 x 16
 template <>
