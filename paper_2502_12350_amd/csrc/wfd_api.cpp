@@ -1497,7 +1497,6 @@ wfd_status wfd_batch_create(wfd_batch **out, int32_t nshot, wfd_ctx *const *ctxs
     d.rec = record_of(w, nrec[i]);
     d.seis_tm = w.seis_tm;
     d.block_begin = offset;
-    d.block_end = offset + nb;
     offset += nb;
     for (int p = 0; p < 2; ++p) {
       wfd::WindowStep e = d;
@@ -1710,9 +1709,7 @@ wfd_status wfd_gbatch_create(wfd_gbatch **out, int32_t nshot, wfd_ctx *const *ct
     d.il = wfd::IllumOut{illum ? illum_dev_or_null[i] : nullptr, c->grid.border, c->grid.nx,
                          c->grid.ny, c->grid.nz, w.scale, 0};
     d.fblock_begin = foff;
-    d.fblock_end = foff + nf;
     d.ablock_begin = aoff;
-    d.ablock_end = aoff + na;
     foff += nf;
     aoff += na;
     b->ctxs.push_back(c);

@@ -113,7 +113,7 @@ struct WindowStep {
   Source src;
   Record rec;
   float *seis_tm;
-  int block_begin, block_end;
+  int block_begin;
 };
 
 // Illumination output of the adjoint step: illum[model cell] += 2^(out_exp2 -
@@ -141,7 +141,7 @@ struct GradWindow {
   int64_t vol;           // floats per pitched volume
   float *P1, *P2, *gimg;  // adjoint pair and imaging sum
   IllumOut il;
-  int fblock_begin, fblock_end, ablock_begin, ablock_end;
+  int fblock_begin, ablock_begin;
 };
 
 // The kernel of a step launch: its tile shape and whether its single-use

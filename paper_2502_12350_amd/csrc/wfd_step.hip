@@ -613,11 +613,10 @@ __global__ void __launch_bounds__(S::NTHREADS, S::WAVES)
 }
 
 // Several grids (one per shot) advanced by one launch: block b belongs to the
-// window whose [block_begin, block_end) contains it.  Ranges follow one another
-// without gaps: a window that starts off a multiple of 8 has its XCD ranges
-// rotated, while ranges padded to multiples of 8 gave XCD 0 up to twice the
-// blocks of the others (24 small windows, adjoint: 138 us a step instead of
-// 78).
+// last window whose block_begin it reaches.  Ranges follow one another without
+// gaps: a window that starts off a multiple of 8 has its XCD ranges rotated, while
+// ranges padded to multiples of 8 gave XCD 0 up to twice the blocks of the others
+// (24 small windows, adjoint: 138 us a step instead of 78).
 template <class S, bool VD, bool FS, bool NT>
 __global__ void __launch_bounds__(S::NTHREADS, S::WAVES)
     k_forward_multi(const WindowStep *__restrict__ wins, int nwin, int n) {
@@ -843,9 +842,9 @@ __device__ __forceinline__ float *pool_buffer(const GradWindow &d, int k) {
 }
 
 // One forward step of every window of a batched gradient: block b belongs to
-// the window whose [fblock_begin, fblock_end) contains it; the step reads pool
-// buffers cur_k (w^n) and prev_k (w^{n-1}) and writes out_k, recording the
-// receivers when `record` is set.
+// the last window whose fblock_begin it reaches; the step reads pool buffers
+// cur_k (w^n) and prev_k (w^{n-1}) and writes out_k, recording the receivers when
+// `record` is set.
 template <class S, bool VD, bool FS, bool NT>
 __global__ void __launch_bounds__(S::NTHREADS, S::WAVES)
     k_forward_pool(const GradWindow *__restrict__ wins, int nwin, int n, int cur_k, int prev_k,
@@ -886,7 +885,6 @@ __global__ void __launch_bounds__(T::NTHREADS)
   int w = 0;
   while (w + 1 < nwin && b >= wins[w + 1].ablock_begin) ++w;
   const GradWindow &d = wins[w];
-  if (b >= d.ablock_end) return;
   float *a1 = parity ? d.P2 : d.P1, *a2 = parity ? d.P1 : d.P2;
   adjoint_tile<T, DL, VD, ILLUM, FS, NT>(d.g, a1, a2, a2, d.rec, d.res_tm, m,
                                               pool_buffer(d, wm_k), d.gimg, d.il, d.amap,
@@ -1131,12 +1129,8 @@ TileMap map_of(const StepGrid &g, const Candidate &c, int nch, int min_zc) {
 // chunk count to that many rounds of the device instead.  Returns the shape.
 int plan_maps(const StepGrid *const *grids, const int *rounds, int n, const Candidate *cand,
               int ncand, TileMap *maps) {
-  bool fixed = false;
   int deepest = 1;
-  for (int i = 0; i < n; ++i) {
-    fixed = fixed || rounds[i] > 0;
-    deepest = std::max(deepest, grids[i]->nz);
-  }
+  for (int i = 0; i < n; ++i) deepest = std::max(deepest, grids[i]->nz);
   const Candidate *best = &cand[0];
   int best_zc = deepest;
   double best_cost = 1e300;
