@@ -84,7 +84,48 @@ static void test_tuned_batch() {
   }
 }
 
-int main() {
+// The plans of padded grids on the device (MI355X): the shapes that
+// tests/test_gpu_batch.py compares bitwise, for one shot and a batch of three.
+struct Plan {
+  int fwd, fwd_stream, spread, adj, adj_stream;
+};
+static void test_device_plans() {
+  const struct {
+    int nx, ny, nz;
+    Plan one, three;
+  } cases[] = {
+      {176, 176, 176, {0, 0, 0, 3, 0}, {0, 1, 0, 3, 1}},
+      {160, 200, 176, {5, 0, 0, 4, 0}, {1, 1, 0, 0, 1}},
+      {90, 180, 260, {5, 0, 0, 4, 0}, {5, 0, 0, 4, 1}},
+      {97, 300, 200, {0, 0, 0, 0, 0}, {1, 1, 0, 0, 1}},
+      {420, 400, 400, {1, 1, 1, 0, 1}, {1, 1, 0, 0, 1}},
+  };
+  for (const auto &c : cases)
+    for (int zs : {wfd::kNoSurface, 8}) {
+      const float k = 0.0f;
+      wfd::StepGrid g{};
+      g.nx = c.nx, g.ny = c.ny, g.nz = c.nz, g.pitch = (c.nx + 63) / 64 * 64;
+      g.plane = (int64_t)g.pitch * c.ny, g.zs = zs, g.k = &k, g.m2 = &k;
+      const wfd::Tuning tu;
+      const wfd::StepGrid *pg[3] = {&g, &g, &g};
+      const wfd::Tuning *pt[3] = {&tu, &tu, &tu};
+      for (int n : {1, 3}) {
+        const Plan &want = n == 1 ? c.one : c.three;
+        wfd::TileMap f[3], a[3];
+        const wfd::StepPlan pf = wfd::plan_forward(pg, pt, n, true, f);
+        const wfd::StepPlan pa = wfd::plan_adjoint(pg, pt, n, false, a);
+        CHECK(pf.shape == want.fwd && pf.stream == want.fwd_stream && f[0].spread == want.spread);
+        CHECK(pa.shape == want.adj && pa.stream == want.adj_stream);
+      }
+    }
+}
+
+int main(int argc, char **) {
+  if (argc > 1) {
+    test_device_plans();
+    if (!failures) std::printf("ALL PASSED\n");
+    return failures != 0;
+  }
   test_tuned_batch();
   test_read_ahead();
   test_laplace_rule();

@@ -423,3 +423,56 @@ def test_planned_launches_equal_fixed_tiles_bitwise(n, N):
     m, gb = GradientBatch([prop() for _ in range(3)], wav, [src] * 3, [rec] * 3, [dobs] * 3, 4).run()
     for i in range(3):
         assert torch.equal(gb[i], gr) and float(m[i]) == float(Jr)
+
+
+def test_device_plans(tmp_path):
+    # which kernels the grids of the next test take
+    gpu_or_skip()
+    from test_host_step import run_units
+    run_units(tmp_path, "device")
+
+
+@pytest.mark.parametrize("n,N,fs", [
+    ((160, 160, 160), 8, True),    # marching 64 x 16 tiles without hints; batched with them
+    ((144, 184, 160), 8, False),   # 32-wide adjoint tiles; batched 64 x 32 both ways
+    ((74, 164, 244), 8, True),     # 32-wide adjoint tiles, batched with streaming hints
+    ((81, 284, 184), 8, False),    # 64 x 32 adjoint tiles without hints
+    ((404, 384, 384), 8, False)])  # over 1 GB a step: blocks in tile order
+def test_planned_marching_launches_equal_fixed_tiles_bitwise(n, N, fs):
+    # the planner's marching tiles (chunks of 10 planes and more), shot by shot and
+    # batched, against 64 x 8 tiles with a fixed number of rounds
+    torch = gpu_or_skip()
+    from paper_2502_12350_amd import GradientBatch, GridSpec, Propagator
+    nx, ny, nz = n
+    nt, h = 40 if nz < 300 else 20, 10.0
+    rng = torch.Generator(device="cuda").manual_seed(2)
+    vel = 1500.0 + 3000.0 * torch.rand((nz, ny, nx), generator=rng, device="cuda")
+    rho = 1000.0 + 0.3 * vel
+    dt = 0.4 * h / 4500.0
+    t = np.arange(nt) * dt
+    a = (np.pi * 30.0 * (t - 0.03)) ** 2
+    wav = torch.from_numpy(((1 - 2 * a) * np.exp(-a)).astype(np.float32)).cuda()
+    src = np.array([[nx // 2 * h, ny // 2 * h, nz // 2 * h]])
+    rec = np.array([[h * i, h * j, h * (nz // 2 + k)] for i in range(0, nx, 9)
+                    for j in range(0, ny, 7) for k in (-30, 11)])
+    dobs = torch.randn((len(rec), nt), generator=rng, device="cuda") * 1e-12
+    gs = GridSpec(nx, ny, nz, h, h, h, border=N, dt=dt, nt=nt, free_surface=fs)
+
+    def prop():
+        P = Propagator(0)
+        P.set_model(gs, vel, rho)
+        return P
+
+    say(f"[plan] model {n} border {N} free surface {fs}")
+    ref = prop()
+    ref.set_tuning(2, 3, 2, 2)
+    Jr, gr, sr = ref.gradient(wav, src, rec, dobs, ckpt=("revolve", 4), seis=True)
+    fr = ref.forward(wav, src, rec)
+    P = prop()
+    J, g, s = P.gradient(wav, src, rec, dobs, ckpt=("revolve", 4), seis=True)
+    assert float(sr.abs().max()) > 0.0 and float(gr.abs().max()) > 0.0
+    assert torch.equal(s, sr) and torch.equal(g, gr) and float(J) == float(Jr)
+    assert torch.equal(P.forward(wav, src, rec), fr) and torch.equal(fr, sr)
+    m, gb = GradientBatch([prop() for _ in range(3)], wav, [src] * 3, [rec] * 3, [dobs] * 3, 4).run()
+    for i in range(3):
+        assert torch.equal(gb[i], gr) and float(m[i]) == float(Jr)

@@ -230,3 +230,25 @@ def test_bessel_with_the_least_workspace(shape):
     full, it_full = smooth(x, "bessel", lens, H, tol=1e-7)
     assert it_full == it.value
     assert np.linalg.norm(full.cpu().numpy() - ref) <= 1e-5 * np.linalg.norm(g)
+
+
+@pytest.mark.parametrize("nrec, nt_in, nt_out", [
+    (2100, 40, 1030),         # four row tiles a wavefront
+    (1300, 50, 700),          # two
+    (67_200_000, 1, 1)])      # more row blocks than a launch takes: rows in turn
+def test_sinc_resampling_row_tiles(nrec, nt_in, nt_out):
+    """As test_sinc_resampling_tiles, at sizes that take several row tiles; the
+    last one's single weight is sinc(dt_out / dt_in - 1)."""
+    torch = gpu_or_skip()
+    from oracle import resample as ors
+    from paper_2502_12350_amd import resample
+    rng = torch.Generator(device="cuda").manual_seed(nrec)
+    d = torch.randn((nrec, nt_in), generator=rng, device="cuda")
+    dt_out = 0.7e-3
+    got = resample(d, 1.0e-3, nt_out, dt_out, "sinc")
+    if nt_in > 1:
+        ref = ors.resample(d.cpu().numpy(), 1.0e-3, nt_out, dt_out, "sinc")
+        assert rel_l2(got.cpu().numpy(), ref) <= 1e-7
+    else:
+        ref = d.double() * float(np.sinc(dt_out / 1.0e-3 - 1.0))
+        assert float(((got - ref).abs() - 2.0 ** -24 * ref.abs()).max()) <= 1e-14

@@ -11,7 +11,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 ROCM = "/opt/rocm"
 
 
-def test_step_host_units(tmp_path):
+def run_units(tmp_path, *args):
     gxx = shutil.which("g++")
     lib = os.path.join(ROOT, "paper_2502_12350_amd", "libwfd.so")
     if gxx is None or not os.path.isdir(os.path.join(ROCM, "include")):
@@ -25,6 +25,10 @@ def test_step_host_units(tmp_path):
            f"-Wl,-rpath,{os.path.dirname(lib)}", f"-Wl,-rpath,{ROCM}/lib", "-o", exe]
     r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
-    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    r = subprocess.run([exe, *args], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
     assert "ALL PASSED" in r.stdout
+
+
+def test_step_host_units(tmp_path):
+    run_units(tmp_path)
