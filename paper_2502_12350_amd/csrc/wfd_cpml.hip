@@ -91,6 +91,7 @@ struct AxisJob {
   int nseg;            // segments (1: the whole axis, or the far end only)
   int rows;            // x kernels: rows of a plane per block
   int tiles;           // tiles of a plane's y range (x kernels) or x range
+  uint32_t first;      // first block of this launch
 };
 
 // b u + a t.  The rounding of every forward sum is written out (which product
@@ -140,7 +141,7 @@ struct PlaneTile {
   bool ok;
   int64_t fb, fs, mb, ms;  // field and memory element of cell 0, step per cell
   __device__ __forceinline__ PlaneTile(const StepGrid &g, const AxisJob &j) {
-    int b = blockIdx.x;
+    int b = blockIdx.x + j.first;
     s0 = j.s0[b % j.nseg];
     b /= j.nseg;
     other = b / j.tiles;
@@ -360,8 +361,9 @@ struct RowTile {
   int64_t fb, mb;     // field and memory element of the first row
   int line[N], pos[N];
   __device__ __forceinline__ RowTile(const StepGrid &g, const AxisJob &j) {
-    z = blockIdx.x / j.tiles;
-    y0 = (blockIdx.x - z * j.tiles) * j.rows;
+    const uint32_t b = blockIdx.x + j.first;
+    z = b / j.tiles;
+    y0 = (b - z * j.tiles) * j.rows;
     pitch = j.L + 8;
     P = j.nseg * j.L;
     total = min(j.rows, g.ny - y0) * P;
@@ -616,8 +618,11 @@ hipError_t launch_cpml_forward(const StepGrid &g, const CpmlTables &t, const She
   bool fits = row_shape(g, j, [&](auto nt) {
     const size_t lds = 2 * sizeof(float) * (size_t)j.rows * j.nseg * (j.L + 8);
     constexpr int NT = decltype(nt)::value;
-    hipLaunchKernelGGL((k_cpml_forward_x<NT, 3>), dim3((unsigned)(j.tiles * g.nz)), dim3(NT), lds,
-                       stream, g, j, sh, cur, mem[0], mem[3], out, cstore);
+    for_launches((int64_t)j.tiles * g.nz, NT, [&](uint32_t first, uint32_t count) {
+      j.first = first;
+      hipLaunchKernelGGL((k_cpml_forward_x<NT, 3>), dim3(count), dim3(NT), lds, stream, g, j, sh,
+                         cur, mem[0], mem[3], out, cstore);
+    });
   });
   auto crossed = [&](const AxisJob &q, int d) {
     return Crossed{mem[d], mem[3 + d], q.ih, q.n, q.half, q.len};
@@ -631,9 +636,12 @@ hipError_t launch_cpml_forward(const StepGrid &g, const CpmlTables &t, const She
       constexpr bool IMG = decltype(img)::value, STORE = decltype(store)::value;
       if constexpr (A == 2 || !IMG) {
         p.tiles = (g.nx + T - 1) / T;
-        const unsigned blocks = (unsigned)(p.tiles * (A == 1 ? g.nz : g.ny) * p.nseg);
-        hipLaunchKernelGGL((k_cpml_forward<A, NT, T, R, IMG, STORE>), dim3(blocks), dim3(NT), 0,
-                           stream, g, p, sh, cur, mem[A], mem[3 + A], out, cstore, cx, cy);
+        const int64_t blocks = (int64_t)p.tiles * (A == 1 ? g.nz : g.ny) * p.nseg;
+        for_launches(blocks, NT, [&](uint32_t first, uint32_t count) {
+          p.first = first;
+          hipLaunchKernelGGL((k_cpml_forward<A, NT, T, R, IMG, STORE>), dim3(count), dim3(NT), 0,
+                             stream, g, p, sh, cur, mem[A], mem[3 + A], out, cstore, cx, cy);
+        });
       }
     });
   };
@@ -654,8 +662,11 @@ hipError_t launch_cpml_adjoint(const StepGrid &g, const CpmlTables &t, const She
   bool fits = row_shape(g, j, [&](auto nt) {
     const size_t lds = 2 * sizeof(float) * (size_t)j.rows * j.nseg * (j.L + 8);
     constexpr int NT = decltype(nt)::value;
-    hipLaunchKernelGGL((k_cpml_adjoint_x<NT, 3>), dim3((unsigned)(j.tiles * g.nz)), dim3(NT), lds,
-                       stream, g, j, sh, phi1, mem[3], mem[0], phi, cstore, grad);
+    for_launches((int64_t)j.tiles * g.nz, NT, [&](uint32_t first, uint32_t count) {
+      j.first = first;
+      hipLaunchKernelGGL((k_cpml_adjoint_x<NT, 3>), dim3(count), dim3(NT), lds, stream, g, j, sh,
+                         phi1, mem[3], mem[0], phi, cstore, grad);
+    });
   });
   auto plane = [&](auto ax) {
     constexpr int A = decltype(ax)::value;
@@ -665,9 +676,12 @@ hipError_t launch_cpml_adjoint(const StepGrid &g, const CpmlTables &t, const She
       constexpr bool IMG = decltype(img)::value;
       if constexpr (A == 2 || !IMG) {
         p.tiles = (g.nx + T - 1) / T;
-        const unsigned blocks = (unsigned)(p.tiles * (A == 1 ? g.nz : g.ny) * p.nseg);
-        hipLaunchKernelGGL((k_cpml_adjoint<A, NT, T, R, IMG>), dim3(blocks), dim3(NT), 0, stream,
-                           g, p, sh, phi1, mem[3 + A], mem[A], phi, cstore, grad);
+        const int64_t blocks = (int64_t)p.tiles * (A == 1 ? g.nz : g.ny) * p.nseg;
+        for_launches(blocks, NT, [&](uint32_t first, uint32_t count) {
+          p.first = first;
+          hipLaunchKernelGGL((k_cpml_adjoint<A, NT, T, R, IMG>), dim3(count), dim3(NT), 0, stream,
+                             g, p, sh, phi1, mem[3 + A], mem[A], phi, cstore, grad);
+        });
       }
     });
   };

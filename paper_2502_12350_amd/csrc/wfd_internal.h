@@ -14,6 +14,15 @@ namespace wfd {
 int ctx_device(const wfd_ctx *c);
 wfd_status set_error(wfd_status status, const char *message);
 
+// Calls f(first, count) for the launches that `blocks` blocks of `threads` threads
+// take: one has less than 2^32 threads.
+template <class F>
+void for_launches(int64_t blocks, int threads, F f) {
+  const int64_t most = ((int64_t(1) << 32) - 1) / threads;
+  for (int64_t b = 0; b < blocks; b += most)
+    f((uint32_t)b, (uint32_t)(blocks - b < most ? blocks - b : most));
+}
+
 // Padded-grid geometry and coefficient volumes seen by every step kernel.
 // Volumes are [Nz][Ny][pitch] FP32 with pitch >= Nx (rows 256-byte aligned).
 struct StepGrid {

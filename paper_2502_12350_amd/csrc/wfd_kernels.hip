@@ -246,7 +246,6 @@ __device__ __forceinline__ void fold_range(int i, int n, int border, int &lo, in
 // takes several (32 bits: a row of g is 256 bytes at least, so that 2^31 rows fit
 // no device).
 constexpr int kFoldWaves = 16;
-constexpr int64_t kFoldBlocks = 1 << 20;  // blocks of a launch: under 2^32 threads
 
 __global__ void __launch_bounds__(kFoldWaves * 64)
     k_grad_fold(const float *__restrict__ g, const float *__restrict__ k, int pitch, int pny,
@@ -403,10 +402,10 @@ hipError_t launch_grad_fold(const float *g, const float *k, int pitch, int pny, 
   const int64_t inner_y = std::max(0, mny - 2), inner_z = std::max(0, mnz - 2);
   const int64_t face_rows = (mnz > 1 ? 2 : 1) * (int64_t)mny + (mny > 1 ? 2 : 1) * inner_z;
   const int64_t blocks = face_rows + (inner_y * inner_z + kFoldWaves - 1) / kFoldWaves;
-  for (int64_t b = 0; b < blocks; b += kFoldBlocks)
-    hipLaunchKernelGGL(k_grad_fold, dim3((unsigned)std::min(kFoldBlocks, blocks - b)),
-                       dim3(kFoldWaves * 64), 0, stream, g, k, pitch, pny, border, mnx, mny, mnz,
-                       dt, sc, out_exp2, grad, (int)face_rows, (uint32_t)b);
+  for_launches(blocks, kFoldWaves * 64, [&](uint32_t first, uint32_t count) {
+    hipLaunchKernelGGL(k_grad_fold, dim3(count), dim3(kFoldWaves * 64), 0, stream, g, k, pitch,
+                       pny, border, mnx, mny, mnz, dt, sc, out_exp2, grad, (int)face_rows, first);
+  });
   return hipGetLastError();
 }
 

@@ -1,8 +1,9 @@
-// Host unit tests of the step kernels' host-side rules (csrc/wfd_internal.h,
-// csrc/wfd_step.hip) and of the filters': the index of the tables that a plane loop
-// reads ahead, and which Laplace lines go through tiles.
-// Built with g++ against libwfd.so and run without a GPU by
-// tests/test_host_step.py.
+// Host unit tests of the kernels' host-side rules (csrc/wfd_internal.h,
+// csrc/wfd_step.hip, csrc/wfd_smooth.hip): the index of the tables that a plane
+// loop reads ahead, the launches of many blocks, the chunks of a tuned batch, and
+// which Laplace lines go through tiles; with an argument, the plans of grids on the
+// device.
+// Built with g++ against libwfd.so by tests/test_host_step.py.
 #include <algorithm>
 #include <cstdio>
 
@@ -84,6 +85,23 @@ static void test_tuned_batch() {
   }
 }
 
+// The launches of a count of blocks cover it in order, each under 2^32 threads (the
+// CPML layer of a 2050^3 grid with over 380 border cells, x lines: 2050 * 2050
+// blocks of 1024).
+static void test_launches() {
+  const int64_t counts[] = {1, 4194303, 4194304, 2050 * 2050, 20000000};
+  for (int64_t blocks : counts)
+    for (int threads : {256, 512, 1024}) {
+      int64_t next = 0;
+      wfd::for_launches(blocks, threads, [&](uint32_t first, uint32_t count) {
+        CHECK(first == next && count > 0);
+        CHECK((uint64_t)count * threads < (uint64_t(1) << 32));
+        next += count;
+      });
+      CHECK(next == blocks);
+    }
+}
+
 // The plans of padded grids on the device (MI355X): the shapes that
 // tests/test_gpu_batch.py compares bitwise, for one shot and a batch of three.
 struct Plan {
@@ -126,6 +144,7 @@ int main(int argc, char **) {
     if (!failures) std::printf("ALL PASSED\n");
     return failures != 0;
   }
+  test_launches();
   test_tuned_batch();
   test_read_ahead();
   test_laplace_rule();
