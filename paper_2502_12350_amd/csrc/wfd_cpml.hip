@@ -352,6 +352,198 @@ __global__ void __launch_bounds__(NT)
   }
 }
 
+// ---- y and z: segments too long for a tile (plane_shape) ----------------------
+// A thread marches kLongCells cells of a line with the nine values around the
+// present one in registers; a block is 64 lines in each of four planes.  Between
+// the recursions the arrays go through memory: each kernel writes only what no
+// other thread of it reads.
+constexpr int kLongCells = 16;
+
+template <int AXIS>
+struct LongLine {
+  int i0, i1;  // cells of this thread
+  int x, other;
+  bool ok;
+  int64_t fb, fs, mb, ms;  // field and memory element of cell 0, step per cell
+  __device__ __forceinline__ LongLine(const StepGrid &g, const AxisJob &j) {
+    int b = blockIdx.x + j.first;
+    const int chunks = (j.L + kLongCells - 1) / kLongCells;
+    x = b % j.tiles * 64 + threadIdx.x % 64;
+    b /= j.tiles;
+    const int s0 = j.s0[b / chunks % j.nseg];
+    i0 = s0 + b % chunks * kLongCells;
+    i1 = min(i0 + kLongCells, s0 + j.L);
+    other = b / (chunks * j.nseg) * 4 + threadIdx.x / 64;
+    ok = x < g.nx && other < (AXIS == 1 ? g.nz : g.ny);
+    fb = (AXIS == 1 ? (int64_t)other * g.plane : (int64_t)other * g.pitch) + x;
+    fs = AXIS == 1 ? (int64_t)g.pitch : g.plane;
+    mb = (AXIS == 1 ? (int64_t)other * j.len * g.nx : (int64_t)other * g.nx) + x;
+    ms = AXIS == 1 ? (int64_t)g.nx : (int64_t)g.ny * g.nx;
+  }
+  __device__ __forceinline__ int64_t field(int i) const { return fb + i * fs; }
+  __device__ __forceinline__ int64_t mem(const AxisJob &j, int i) const {
+    return mb + cidx(i, j.half, j.len, j.n) * ms;
+  }
+  __device__ __forceinline__ int y(int i) const { return AXIS == 1 ? i : other; }
+  __device__ __forceinline__ int z(int i) const { return AXIS == 1 ? other : i; }
+  // Cell i of a field or a memory variable u: zero outside the grid (and where the
+  // variable is not stored: cells that no point of the layer's reach uses), with
+  // `image` the negated mirror before a free surface.
+  __device__ __forceinline__ float cell(const float *u, const StepGrid &g, const AxisJob &j, int i,
+                                        bool image = false) const {
+    if (image && AXIS == 2 && i < g.zs) {
+      const int m = 2 * g.zs - i;
+      return m < j.n ? -u[field(m)] : 0.0f;
+    }
+    return i >= 0 && i < j.n ? u[field(i)] : 0.0f;
+  }
+  __device__ __forceinline__ bool stored(const AxisJob &j, int i) const {
+    return i >= 0 && i < j.n && (i < j.half || i >= j.n - (j.len - j.half));
+  }
+};
+
+// f(cell) of cells i - 4 .. i + 4: v[4] is cell i.
+struct Window {
+  float v[9];
+  template <class F>
+  __device__ __forceinline__ void prime(F f, int i) {
+#pragma unroll
+    for (int c = 0; c < 9; ++c) v[c] = f(i - 4 + c);
+  }
+  template <class F>
+  __device__ __forceinline__ void advance(F f, int i) {  // to cell i + 1
+#pragma unroll
+    for (int c = 0; c < 8; ++c) v[c] = v[c + 1];
+    v[8] = f(i + 5);
+  }
+};
+
+template <int AXIS>
+__global__ void __launch_bounds__(256)
+    k_cpml_psi_long(StepGrid g, AxisJob j, const float *__restrict__ w, float *__restrict__ psi) {
+  const LongLine<AXIS> t(g, j);
+  if (!t.ok) return;
+  auto fw = [&](int i) { return t.cell(w, g, j, i); };
+  Window q;
+  q.prime(fw, t.i0);
+  for (int i = t.i0; i < t.i1; ++i) {
+    if (j.a[i] != 0.0f) {
+      float &u = psi[t.mem(j, i)];
+      u = recursion<AXIS>(j.b[i], u, j.a[i], j.ih * first_diff(q.v + 4, 1));
+    }
+    q.advance(fw, i);
+  }
+}
+
+// As the last part of k_cpml_forward.
+template <int AXIS>
+__global__ void __launch_bounds__(256)
+    k_cpml_zeta_long(StepGrid g, AxisJob j, Shell sh, const float *__restrict__ w,
+                     const float *__restrict__ psi, float *__restrict__ zeta,
+                     float *__restrict__ out, float *__restrict__ cstore, Crossed cx, Crossed cy) {
+  const LongLine<AXIS> t(g, j);
+  if (!t.ok) return;
+  auto fw = [&](int i) { return t.cell(w, g, j, i, true); };
+  auto fp = [&](int i) { return t.stored(j, i) ? psi[t.mem(j, i)] : 0.0f; };
+  const bool near_x = near(sh, 0, t.x);
+  Window qw, qp;
+  qw.prime(fw, t.i0);
+  qp.prime(fp, t.i0);
+  for (int i = t.i0; i < t.i1; ++i) {
+    if (near(sh, AXIS, i)) {
+      const int y = t.y(i), z = t.z(i);
+      const bool near_y = AXIS == 2 && near(sh, 1, y), more = AXIS == 1 && near(sh, 2, z);
+      const int64_t q = shell_row(sh, row_box(sh, y, z), y, z) + t.x;
+      float c = 0.0f;
+      if (cstore) {
+        if (near_x || near_y) c = cstore[q];
+      } else if (!more) {
+        if (near_x) c = cx.add(c, ((int64_t)z * g.ny + y) * cx.len, 1, t.x);
+        if (near_y) c = cy.add(c, (int64_t)z * cy.len * g.nx + t.x, g.nx, y);
+      }
+      const float d1 = first_diff(qp.v + 4, 1), d1p = j.ih * d1;
+      c = __builtin_fmaf(j.ih, d1, c);
+      if (j.a[i] != 0.0f) {
+        float &u = zeta[t.mem(j, i)];
+        u = recursion<AXIS>(j.b[i], u, j.a[i], __builtin_fmaf(j.c2, second_diff(qw.v + 4, 1), d1p));
+        c += u;
+      }
+      if (out && !more && z > g.zs)
+        out[t.field(i)] = __builtin_fmaf(c, g.k[t.field(i)], out[t.field(i)]);
+      if (cstore) cstore[q] = c;
+    }
+    qw.advance(fw, i);
+    qp.advance(fp, i);
+  }
+}
+
+// nu = phi1 + b nu, and the imaging term (k_cpml_adjoint).
+template <int AXIS>
+__global__ void __launch_bounds__(256)
+    k_cpml_nu_long(StepGrid g, AxisJob j, Shell sh, const float *__restrict__ phi1,
+                   float *__restrict__ nu, const float *__restrict__ cstore,
+                   float *__restrict__ grad) {
+  const LongLine<AXIS> t(g, j);
+  if (!t.ok) return;
+  for (int i = t.i0; i < t.i1; ++i) {
+    const float f = phi1[t.field(i)];
+    const int y = t.y(i), z = t.z(i);
+    if (j.a[i] != 0.0f) {
+      float &u = nu[t.mem(j, i)];
+      u = f + j.b[i] * u;
+    }
+    if (cstore && near(sh, AXIS, i) && (AXIS == 2 || !near(sh, 2, z)))
+      grad[t.field(i)] += f * cstore[shell_row(sh, row_box(sh, y, z), y, z) + t.x];
+  }
+}
+
+template <int AXIS>
+__global__ void __launch_bounds__(256)
+    k_cpml_mu_long(StepGrid g, AxisJob j, const float *__restrict__ phi1,
+                   const float *__restrict__ nu, float *__restrict__ mu) {
+  const LongLine<AXIS> t(g, j);
+  if (!t.ok) return;
+  auto f = [&](int i) {
+    const float an = t.stored(j, i) ? j.a[i] * nu[t.mem(j, i)] : 0.0f;
+    return t.cell(phi1, g, j, i) + an;
+  };
+  Window q;
+  q.prime(f, t.i0);
+  for (int i = t.i0; i < t.i1; ++i) {
+    if (j.a[i] != 0.0f) {
+      float &u = mu[t.mem(j, i)];
+      u = j.b[i] * u - first_diff(q.v + 4, 1) * j.ih;
+    }
+    q.advance(f, i);
+  }
+}
+
+template <int AXIS>
+__global__ void __launch_bounds__(256)
+    k_cpml_phi_long(StepGrid g, AxisJob j, Shell sh, const float *__restrict__ nu,
+                    const float *__restrict__ mu, float *__restrict__ phi) {
+  const LongLine<AXIS> t(g, j);
+  if (!t.ok) return;
+  auto weighted = [&](const float *u, int i) {
+    return t.stored(j, i) ? j.a[i] * u[t.mem(j, i)] : 0.0f;
+  };
+  auto fn = [&](int i) {  // before a free surface the negated image
+    if (AXIS == 2 && i < g.zs) return -weighted(nu, 2 * g.zs - i);
+    return weighted(nu, i);
+  };
+  auto fm = [&](int i) { return weighted(mu, i); };
+  Window qn, qm;
+  qn.prime(fn, t.i0);
+  qm.prime(fm, t.i0);
+  for (int i = t.i0; i < t.i1; ++i) {
+    if (near(sh, AXIS, i) && t.z(i) > g.zs)
+      phi[t.field(i)] +=
+          g.k[t.field(i)] * (j.c2 * second_diff(qn.v + 4, 1) - first_diff(qm.v + 4, 1) * j.ih);
+    qn.advance(fn, i);
+    qm.advance(fm, i);
+  }
+}
+
 // ---- x: rows of a plane, both segments, consecutive elements along x ---------
 // Element e = thread + NT k of the block's rows x segments x cells.
 template <int NT, int N>
@@ -559,11 +751,13 @@ AxisJob axis_job(const StepGrid &g, const CpmlTables &t, const Shell &sh, int d)
 }
 
 // Calls f(threads, tile width T, cells per thread R, image) with the smallest
-// tile that takes a segment of L cells: 64 lines up to 96 cells (borders to 92),
-// fewer lines for longer ones, so that a tile's LDS stays below 64 KB and a
-// thread's cells in registers.  The last covers every border whose volumes fit
-// the device (each axis is longer than twice the border).  Whole axes with
-// image cells are short (under 2 B + 16 cells) and rare: fewer shapes.
+// tile that takes a segment of L cells: 64 lines up to 96 cells (borders to 92), 32
+// up to 192, so that a tile's LDS stays below 64 KB and a thread's cells in
+// registers; false for longer ones, whose lines are marched in memory (forward
+// steps of 320^3 with a layer of 100 cells: 772 us in 32 lines, 1451 in tiles of 16;
+// 500^3 with 200: 4137 marched, 4768 in 16; 840^3 with 390: 23.6 ms, 81 in tiles of
+// 2; the kernels without tiles 854, 3972 and 21.9 ms).  Whole axes with image cells
+// are short (under 2 B + 16 cells) and rare: fewer shapes.
 template <class F>
 bool plane_shape(int L, bool img, F f) {
 #define WFD_PLANE(NT, T, R, IMG)                                                      \
@@ -575,7 +769,6 @@ bool plane_shape(int L, bool img, F f) {
   if (img) {
     WFD_PLANE(512, 64, 6, true)
     WFD_PLANE(1024, 64, 6, true)
-    WFD_PLANE(1024, 2, 6, true)
     return false;
   }
   WFD_PLANE(256, 64, 3, false)
@@ -584,10 +777,17 @@ bool plane_shape(int L, bool img, F f) {
   WFD_PLANE(512, 64, 5, false)
   WFD_PLANE(512, 64, 6, false)
   WFD_PLANE(1024, 64, 6, false)
-  WFD_PLANE(1024, 16, 6, false)
-  WFD_PLANE(1024, 2, 6, false)
+  WFD_PLANE(1024, 32, 4, false)
+  WFD_PLANE(1024, 32, 6, false)
 #undef WFD_PLANE
   return false;
+}
+
+// Blocks of the long segments' kernels.
+int64_t long_blocks(const StepGrid &g, AxisJob &p, int axis) {
+  p.tiles = (g.nx + 63) / 64;
+  const int chunks = (p.L + kLongCells - 1) / kLongCells;
+  return (int64_t)p.tiles * chunks * p.nseg * (((axis == 1 ? g.nz : g.ny) + 3) / 4);
 }
 
 // Calls f(threads) for an x job, three elements per thread: as many rows of a
@@ -615,7 +815,7 @@ hipError_t launch_cpml_forward(const StepGrid &g, const CpmlTables &t, const She
                                hipStream_t stream) {
   if (sh.points == 0) return hipSuccess;
   AxisJob j = axis_job(g, t, sh, 0);
-  bool fits = row_shape(g, j, [&](auto nt) {
+  const bool fits = row_shape(g, j, [&](auto nt) {
     const size_t lds = 2 * sizeof(float) * (size_t)j.rows * j.nseg * (j.L + 8);
     constexpr int NT = decltype(nt)::value;
     for_launches((int64_t)j.tiles * g.nz, NT, [&](uint32_t first, uint32_t count) {
@@ -624,6 +824,7 @@ hipError_t launch_cpml_forward(const StepGrid &g, const CpmlTables &t, const She
                          cur, mem[0], mem[3], out, cstore);
     });
   });
+  if (!fits) return hipErrorInvalidValue;
   auto crossed = [&](const AxisJob &q, int d) {
     return Crossed{mem[d], mem[3 + d], q.ih, q.n, q.half, q.len};
   };
@@ -631,7 +832,7 @@ hipError_t launch_cpml_forward(const StepGrid &g, const CpmlTables &t, const She
   auto plane = [&](auto ax, auto store) {
     constexpr int A = decltype(ax)::value;
     AxisJob p = axis_job(g, t, sh, A);
-    fits = fits && plane_shape(p.L, image_axis(g, p, A), [&](auto nt, auto t_, auto r, auto img) {
+    const bool tiled = plane_shape(p.L, image_axis(g, p, A), [&](auto nt, auto t_, auto r, auto img) {
       constexpr int NT = decltype(nt)::value, T = decltype(t_)::value, R = decltype(r)::value;
       constexpr bool IMG = decltype(img)::value, STORE = decltype(store)::value;
       if constexpr (A == 2 || !IMG) {
@@ -644,6 +845,17 @@ hipError_t launch_cpml_forward(const StepGrid &g, const CpmlTables &t, const She
         });
       }
     });
+    if (tiled) return;
+    const int64_t blocks = long_blocks(g, p, A);
+    for_launches(blocks, 256, [&](uint32_t first, uint32_t count) {
+      p.first = first;
+      hipLaunchKernelGGL(k_cpml_psi_long<A>, dim3(count), dim3(256), 0, stream, g, p, cur, mem[A]);
+    });
+    for_launches(blocks, 256, [&](uint32_t first, uint32_t count) {
+      p.first = first;
+      hipLaunchKernelGGL(k_cpml_zeta_long<A>, dim3(count), dim3(256), 0, stream, g, p, sh, cur,
+                         mem[A], mem[3 + A], out, cstore, cx, cy);
+    });
   };
   auto planes = [&](auto store) {
     plane(std::integral_constant<int, 1>{}, store);
@@ -651,7 +863,7 @@ hipError_t launch_cpml_forward(const StepGrid &g, const CpmlTables &t, const She
   };
   if (cstore) planes(std::true_type{});
   else planes(std::false_type{});
-  return fits ? hipGetLastError() : hipErrorInvalidValue;
+  return hipGetLastError();
 }
 
 hipError_t launch_cpml_adjoint(const StepGrid &g, const CpmlTables &t, const Shell &sh,
@@ -659,7 +871,7 @@ hipError_t launch_cpml_adjoint(const StepGrid &g, const CpmlTables &t, const She
                                const float *cstore, float *grad, hipStream_t stream) {
   if (sh.points == 0) return hipSuccess;
   AxisJob j = axis_job(g, t, sh, 0);
-  bool fits = row_shape(g, j, [&](auto nt) {
+  const bool fits = row_shape(g, j, [&](auto nt) {
     const size_t lds = 2 * sizeof(float) * (size_t)j.rows * j.nseg * (j.L + 8);
     constexpr int NT = decltype(nt)::value;
     for_launches((int64_t)j.tiles * g.nz, NT, [&](uint32_t first, uint32_t count) {
@@ -668,10 +880,11 @@ hipError_t launch_cpml_adjoint(const StepGrid &g, const CpmlTables &t, const She
                          phi1, mem[3], mem[0], phi, cstore, grad);
     });
   });
+  if (!fits) return hipErrorInvalidValue;
   auto plane = [&](auto ax) {
     constexpr int A = decltype(ax)::value;
     AxisJob p = axis_job(g, t, sh, A);
-    fits = fits && plane_shape(p.L, image_axis(g, p, A), [&](auto nt, auto t_, auto r, auto img) {
+    const bool tiled = plane_shape(p.L, image_axis(g, p, A), [&](auto nt, auto t_, auto r, auto img) {
       constexpr int NT = decltype(nt)::value, T = decltype(t_)::value, R = decltype(r)::value;
       constexpr bool IMG = decltype(img)::value;
       if constexpr (A == 2 || !IMG) {
@@ -684,10 +897,27 @@ hipError_t launch_cpml_adjoint(const StepGrid &g, const CpmlTables &t, const She
         });
       }
     });
+    if (tiled) return;
+    const int64_t blocks = long_blocks(g, p, A);
+    for_launches(blocks, 256, [&](uint32_t first, uint32_t count) {
+      p.first = first;
+      hipLaunchKernelGGL(k_cpml_nu_long<A>, dim3(count), dim3(256), 0, stream, g, p, sh, phi1,
+                         mem[3 + A], cstore, grad);
+    });
+    for_launches(blocks, 256, [&](uint32_t first, uint32_t count) {
+      p.first = first;
+      hipLaunchKernelGGL(k_cpml_mu_long<A>, dim3(count), dim3(256), 0, stream, g, p, phi1,
+                         mem[3 + A], mem[A]);
+    });
+    for_launches(blocks, 256, [&](uint32_t first, uint32_t count) {
+      p.first = first;
+      hipLaunchKernelGGL(k_cpml_phi_long<A>, dim3(count), dim3(256), 0, stream, g, p, sh,
+                         mem[3 + A], mem[A], phi);
+    });
   };
   plane(std::integral_constant<int, 1>{});
   plane(std::integral_constant<int, 2>{});
-  return fits ? hipGetLastError() : hipErrorInvalidValue;
+  return hipGetLastError();
 }
 
 hipError_t launch_record(const float *field, const int64_t *idx, const float *scale, int nrec,

@@ -307,3 +307,54 @@ def test_cpml_forward_workspace_holds_no_correction():
     _lib.check(_lib.lib().wfd_forward_noalloc(P._ctx, wav.data_ptr(), _dptr(src), 2, _dptr(rec),
                                               seis.data_ptr(), None))
     assert torch.equal(seis, P.forward(wav, src, rec)) and float(seis.abs().max()) > 0.0
+
+
+@pytest.mark.parametrize("n,N,fs", [
+    ((18, 20, 17), 100, False),   # 104 cells: tiles of 32 lines, 4 cells per thread
+    ((18, 20, 19), 150, True),    # 154 cells: 32 lines, 6 per thread
+    ((20, 18, 22), 190, False),   # 194 cells: lines marched in memory, two segments
+    ((6, 20, 7), 190, True),      # whole axes marched, one with image cells
+    ((70, 5, 18), 200, False)])
+def test_cpml_wide_layers_match_oracle(n, N, fs, monkeypatch):
+    # A layer far wider than the wave gets in nt steps (at most eight cells a step):
+    # the oracle keeps its first 8 nt cells, with the full layer's profile.  vmax
+    # makes those cells absorb (d dt about 0.5 in the first one), so that without
+    # the layer the traces would differ by far more than the tolerance.
+    torch = gpu_or_skip()
+    from paper_2502_12350_amd import GridSpec, Propagator
+    nx, ny, nz = n
+    nt, h = 5, 10.0
+    T = 8 * nt
+    full = ocpml.profile
+
+    def first_cells(m, border, *args, **kw):
+        a, b = full(m, N, *args, **kw)
+        assert border == T
+        return a[N - T:N + m + T], b[N - T:N + m + T]
+
+    monkeypatch.setattr(ocpml, "profile", first_cells)
+    vel = seisgen.layered_model(7, n, 0.05)
+    dt = 0.4 * h / float(vel.max())
+    vmax = 0.5 / dt * N * N * 2 * N * h / (3.0 * np.log(1.0e3))
+    wav = np.cos(0.3 * np.arange(nt)).astype(np.float32)
+    src = [0.0, 0.0, min(2, nz - 1) * h]
+    rec = np.array([[h * i, h * j, h * k] for i in (0, min(2, nx - 1), nx - 1)
+                    for j in (0, 1) for k in (0, min(3, nz - 1))])
+    g = oracle.Grid(nx, ny, nz, h, h, h, border=T, dt=dt, nt=nt)
+    g.free_surface = fs
+    say(f"[cpml wide] model {n} border {N} free surface {fs}")
+    kw = dict(vmax=vmax, fpeak=FPEAK)
+    dobs = (0.5 * ocpml.forward(g, vel, None, wav, src, rec, **kw).seis).astype(np.float32)
+    ref = ocpml.gradient(g, vel, None, wav, src, rec, dobs, **kw)
+    open_ = ocpml.forward(g, vel, None, wav, src, rec, vmax=0.0, fpeak=FPEAK).seis
+    assert rel_l2(open_, ref.seis) > 1e-2
+    P = Propagator(0)
+    P.set_model(GridSpec(nx, ny, nz, h, h, h, border=N, dt=dt, nt=nt, cpml=True, fpeak=FPEAK,
+                         cpml_vmax=vmax, free_surface=fs), torch.from_numpy(vel).cuda())
+    J, gr, seis = P.gradient(torch.from_numpy(wav).cuda(), src, rec,
+                             torch.from_numpy(dobs).cuda(), ckpt="full", seis=True)
+    es, eg = rel_l2(seis.cpu().numpy(), ref.seis), rel_l2(gr.cpu().numpy(), ref.grad)
+    say(f"  seismograms rel-L2 {es:.2e}, gradient {eg:.2e}")
+    assert es <= SEIS_TOL and eg <= GRAD_TOL
+    assert abs(float(J.item()) - ref.misfit) <= SEIS_TOL * ref.misfit
+    assert torch.equal(P.forward(torch.from_numpy(wav).cuda(), src, rec), seis)
