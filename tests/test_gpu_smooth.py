@@ -252,3 +252,16 @@ def test_sinc_resampling_row_tiles(nrec, nt_in, nt_out):
     else:
         ref = d.double() * float(np.sinc(dt_out / 1.0e-3 - 1.0))
         assert float(((got - ref).abs() - 2.0 ** -24 * ref.abs()).max()) <= 1e-14
+
+
+@pytest.mark.parametrize("nrec, nt_in, nt_out", [(1, 1, 1), (3, 7, 85), (5, 300, 256), (700, 33, 257)])
+def test_nearest_resampling_edges(nrec, nt_in, nt_out):
+    """Below, at and above a block of 256 output elements across traces: exact."""
+    torch = gpu_or_skip()
+    from oracle import resample as ors
+    from paper_2502_12350_amd import resample
+    d = np.random.default_rng(nrec).standard_normal((nrec, nt_in)).astype(np.float32)
+    for dt_out in (0.4e-3, 1.3e-3):
+        ref = ors.resample(d, 1.0e-3, nt_out, dt_out, "nearest")
+        got = resample(torch.from_numpy(d).cuda(), 1.0e-3, nt_out, dt_out, "nearest")
+        assert np.array_equal(got.cpu().numpy(), ref)
