@@ -1702,7 +1702,6 @@ wfd_status wfd_gbatch_create(wfd_gbatch **out, int32_t nshot, wfd_ctx *const *ct
     d.W1 = w.W1;
     d.W2 = w.W2;
     d.store = w.store;
-    d.vol = c->vol;
     d.P1 = w.P1;
     d.P2 = w.P2;
     d.gimg = w.g;

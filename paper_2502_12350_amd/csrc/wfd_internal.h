@@ -146,8 +146,7 @@ struct GradWindow {
   Record out;
   float *seis_tm;        // [nt][nrec] recorded traces
   const float *res_tm;   // [nt][nrec] scaled residuals, node by node
-  float *W1, *W2, *store;
-  int64_t vol;           // floats per pitched volume
+  float *W1, *W2, *store;  // pitched volumes of g.plane * g.nz floats
   float *P1, *P2, *gimg;  // adjoint pair and imaging sum
   IllumOut il;
   int fblock_begin, ablock_begin;

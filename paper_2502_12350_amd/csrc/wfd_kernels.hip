@@ -241,7 +241,7 @@ __device__ __forceinline__ void fold_range(int i, int n, int border, int &lo, in
 // `face_rows` blocks take one face row each, their 16 wavefronts a share of its
 // rows each; the others one inner row per wavefront.  Lanes run along x, and the
 // border cells of a row's two ends are summed across the lanes.  240 x 240 x 200
-// to 200 x 200 x 160: 61 us (1058 with one thread per model cell, whose corner
+// to 200 x 200 x 160: 64 us (1058 with one thread per model cell, whose corner
 // cells summed 9261 values each).  first_block: of this launch, where the fold
 // takes several (32 bits: a row of g is 256 bytes at least, so that 2^31 rows fit
 // no device).

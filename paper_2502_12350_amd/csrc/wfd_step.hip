@@ -838,7 +838,7 @@ __global__ void __launch_bounds__(T::NTHREADS)
 // Buffer k of a batched gradient's forward pool: W1, W2, then the stored
 // checkpoint volumes.
 __device__ __forceinline__ float *pool_buffer(const GradWindow &d, int k) {
-  return k == 0 ? d.W1 : (k == 1 ? d.W2 : d.store + (int64_t)(k - 2) * d.vol);
+  return k == 0 ? d.W1 : (k == 1 ? d.W2 : d.store + (int64_t)(k - 2) * d.g.plane * d.g.nz);
 }
 
 // One forward step of every window of a batched gradient: block b belongs to

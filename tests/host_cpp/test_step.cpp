@@ -102,6 +102,13 @@ static void test_launches() {
     }
 }
 
+// The batch descriptors inside a shot's workspace: no larger than when its sizes
+// were published, which callers may have kept.
+static void test_workspace_structs() {
+  CHECK(sizeof(wfd::GradWindow) <= 328);
+  CHECK(sizeof(wfd::WindowStep) <= 224);
+}
+
 // The plans of padded grids on the device (MI355X): the shapes that
 // tests/test_gpu_batch.py compares bitwise, for one shot and a batch of three.
 struct Plan {
@@ -144,6 +151,7 @@ int main(int argc, char **) {
     if (!failures) std::printf("ALL PASSED\n");
     return failures != 0;
   }
+  test_workspace_structs();
   test_launches();
   test_tuned_batch();
   test_read_ahead();
